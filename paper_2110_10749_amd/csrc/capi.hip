@@ -26,24 +26,34 @@ int64_t next_pow2(int64_t n) {
 
 struct Layout {
     size_t x, nrm, w, wn, px, pn, pw, px32, boxes, uboxes, mask64, mask32, perm, keys, partial, rec, red, scal, vecs,
-        basis_in, basis_out, image_out, basis_rc, sym_items[2], sym_blocks[2], sym_fwd_start[2], sym_rev_start[2],
-        sym_fwd, sym_rev, total;
+        basis_in, basis_out, image_out, basis_rc, sym_items[3], sym_blocks[3], sym_fwd_start[3], sym_rev_start[3],
+        sym_rows, sym_fwd, sym_rev, total;
 };
 
-// bounds of the symmetric far-field lists: at most T (T - 1) / 2 far tile
-// pairs, and at most pairs / kSymChunk + T blocks.  The lists and partial
-// slots grow as T^2 (about 3469 bytes per tile pair), so plans of more than
-// kSymMaxTiles tiles hold none and run every pass one direction at a time.
-constexpr int64_t kSymMaxTiles = 2048;  // 524288 nodes: 14.6 GB of lists and slots
+// bounds of the lists of the symmetric passes: T (T + 1) / 2 tile pairs in
+// double (a tile against itself counts as one) and up to T^2 in float (near
+// pairs in both orders), each in up to sym_parts(T) items, and a forward slot
+// per block.  The lists and partial slots grow as T^2 (about 3495 bytes per
+// tile pair), so plans of more than kSymMaxTiles tiles hold none and run every
+// pass one direction at a time.
+constexpr int64_t kSymMaxTiles = 2048;  // 524288 nodes: 14.7 GB of lists and slots
 bool sym_fits(int64_t nt) { return nt <= kSymMaxTiles; }
 int64_t sym_max_pairs(int64_t nt) { return nt * (nt - 1) / 2; }
-int64_t sym_max_blocks(int64_t nt) { return sym_max_pairs(nt) / kSymChunk + nt; }
+int64_t sym_max_items(int64_t nt, int k) {
+    return k == kSymFar64 ? sym_max_pairs(nt) : (k == kSymF32 ? nt * nt : nt * (nt + 1) / 2) * sym_parts(nt);
+}
+int64_t sym_max_slots(int64_t nt) { return (sym_max_pairs(nt) + nt) / kSymChunk + 2 * nt; }
+
+// partial slots of a plan at least: the forward and reverse slots of 16 parts
+// to a tile pair up to 11 tiles (n = 2816)
+constexpr size_t kMinPartial = (size_t)12 << 20;
 
 // the node data, staging and pair-pass scratch every plan holds: nsplit
 // source splits with up to `comps` components per partial slot, m the
-// longest GMRES restart the reduction buffer serves
+// longest GMRES restart the reduction buffer serves, min_partial the least
+// bytes of partial slots
 template <class Take>
-void layout_common(Layout& L, Take& take, int64_t n, int m, int nsplit, int comps) {
+void layout_common(Layout& L, Take& take, int64_t n, int m, int nsplit, int comps, size_t min_partial) {
     const size_t d = sizeof(double), f = sizeof(float);
     L.x = take(3 * n * d);
     L.nrm = take(3 * n * d);
@@ -60,7 +70,7 @@ void layout_common(Layout& L, Take& take, int64_t n, int m, int nsplit, int comp
     L.mask32 = take(nt * nt);
     L.perm = take(n * sizeof(int32_t));
     L.keys = take(next_pow2(n) * sizeof(uint64_t));
-    L.partial = take((size_t)2 * nsplit * comps * n * d);
+    L.partial = take(std::max((size_t)2 * nsplit * comps * n * d, min_partial));
     L.rec = take((size_t)npad * kRecBytes);
     L.red = take((size_t)kRedBlocks * (m + 2) * d);
     L.scal = take((size_t)(kScalGmres + 6 * (m + 2) + 64 > 1024 ? kScalGmres + 6 * (m + 2) + 64 : 1024) * d);
@@ -75,7 +85,7 @@ Layout layout(int64_t n, int m) {
         return o;
     };
     const size_t d = sizeof(double);
-    layout_common(L, take, n, m, choose_splits(n), 6);  // up to six components per pass (adjoint)
+    layout_common(L, take, n, m, choose_splits(n), 6, kMinPartial);  // up to six components per pass (adjoint)
     L.vecs = take((size_t)kNumVec * 3 * n * d);
     L.basis_in = take((size_t)(m + 1) * 3 * n * d);
     L.basis_out = take((size_t)(m + 1) * n * d);
@@ -83,14 +93,17 @@ Layout layout(int64_t n, int m) {
     L.basis_rc = take((size_t)(m + 1) * 3 * n * d);
     const int64_t nt = (n + kTile - 1) / kTile;
     if (sym_fits(nt)) {
-        for (int k = 0; k < 2; ++k) {
-            L.sym_items[k] = take((size_t)sym_max_pairs(nt) * 3 * sizeof(int32_t));
-            L.sym_blocks[k] = take((size_t)sym_max_blocks(nt) * 2 * sizeof(int32_t));
+        // every block has a forward slot, in the partial buffer or in sym_fwd
+        const size_t blocks = std::max<size_t>(sym_max_slots(nt), (L.rec - L.partial) / kSymSlotBytes);
+        for (int k = 0; k < 3; ++k) {
+            L.sym_items[k] = take((size_t)sym_max_items(nt, k) * 4 * sizeof(int32_t));
+            L.sym_blocks[k] = take((k == kSymFar64 ? (size_t)sym_max_slots(nt) : blocks) * 3 * sizeof(int32_t));
             L.sym_fwd_start[k] = take((size_t)(nt + 1) * sizeof(int32_t));
             L.sym_rev_start[k] = take((size_t)(nt + 1) * sizeof(int32_t));
         }
-        L.sym_fwd = take((size_t)sym_max_blocks(nt) * 3 * kTile * d);
-        L.sym_rev = take((size_t)sym_max_pairs(nt) * 3 * kTile * d);  // double partials for the FP64 passes
+        L.sym_rows = take((size_t)nt * kSymRowInts * sizeof(int32_t));
+        L.sym_fwd = take((size_t)sym_max_slots(nt) * kSymSlotBytes);
+        L.sym_rev = take((size_t)sym_max_pairs(nt) * kSymSlotBytes);  // double partials for the FP64 passes
     }
     L.total = off;
     return L;
@@ -174,7 +187,7 @@ Layout layer_layout(int64_t n, int nsplit_cap) {
         off = align256(off + bytes);
         return o;
     };
-    layout_common(L, take, n, 1, layer_splits(n, nsplit_cap), 3);
+    layout_common(L, take, n, 1, layer_splits(n, nsplit_cap), 3, 0);
     L.vecs = take((size_t)3 * n * sizeof(double));
     L.total = off;
     return L;
@@ -206,6 +219,16 @@ void carve_common(Plan& P, const Layout& L, char* b) {
 
 }  // namespace
 
+// Tile pairs of small surfaces are cut so that a symmetric pass has about
+// SDBIE_SYM_TARGET blocks (8 per CU): 16 parts of 16 steps up to 16 tiles
+// (n = 4096), one part from 64 tiles on.
+int sym_parts(int64_t nt) {
+    const int64_t pairs = nt * (nt + 1) / 2;
+    int parts = 1;
+    while (parts < kSymParts && pairs * parts < SDBIE_SYM_TARGET) parts *= 2;
+    return parts;
+}
+
 size_t workspace_bytes(int64_t n, int max_restart) { return layout(n, max_restart).total; }
 
 void carve_workspace(Plan& P, void* ws) {
@@ -220,14 +243,17 @@ void carve_workspace(Plan& P, void* ws) {
     P.image_out = reinterpret_cast<double*>(b + L.image_out);
     P.basis_rc = reinterpret_cast<double*>(b + L.basis_rc);
     if (!sym_fits((P.n + kTile - 1) / kTile)) return;  // no symmetric lists: every pass one direction
-    for (int k = 0; k < 2; ++k) {
-        P.sym_items[k] = reinterpret_cast<int32_t*>(b + L.sym_items[k]);
-        P.sym_blocks[k] = reinterpret_cast<int32_t*>(b + L.sym_blocks[k]);
-        P.sym_fwd_start[k] = reinterpret_cast<int32_t*>(b + L.sym_fwd_start[k]);
-        P.sym_rev_start[k] = reinterpret_cast<int32_t*>(b + L.sym_rev_start[k]);
+    for (int k = 0; k < 3; ++k) {
+        P.sym[k].items = reinterpret_cast<int32_t*>(b + L.sym_items[k]);
+        P.sym[k].blocks = reinterpret_cast<int32_t*>(b + L.sym_blocks[k]);
+        P.sym[k].fwd_start = reinterpret_cast<int32_t*>(b + L.sym_fwd_start[k]);
+        P.sym[k].rev_start = reinterpret_cast<int32_t*>(b + L.sym_rev_start[k]);
     }
-    P.sym_fwd = reinterpret_cast<double*>(b + L.sym_fwd);
-    P.sym_rev = b + L.sym_rev;
+    P.sym_rows = reinterpret_cast<int32_t*>(b + L.sym_rows);
+    P.partial_bytes = L.rec - L.partial;
+    P.sym_fwd_mem = b + L.sym_fwd;
+    P.sym_fwd_bytes = L.sym_rev - L.sym_fwd;
+    P.sym_rev_mem = b + L.sym_rev;
 }
 
 size_t layer_workspace_bytes(int64_t n, int nsplit_cap) { return layer_layout(n, nsplit_cap).total; }
@@ -453,6 +479,7 @@ int ddm_solve(sdbie_plan plan, const sdbie_params* prm, const double U[3], const
         double* us = P.vec(kVecU);
         double* fx = f_extra ? P.vec(kVecFx) : nullptr;
         if (fx) dev_gather(P, f_extra, fx, 3, c.s);
+        c.keep_order();
         c.ddm(*prm, U, fx, ps, us, drag);
         dev_scatter(P, ps, p, 1, c.s);
         dev_scatter(P, us, u, 3, c.s);
@@ -482,6 +509,7 @@ int ddm_adjoint(sdbie_plan plan, const sdbie_params* prm, const double U[3], con
         dev_gather(P, p, ps, 1, c.s);
         dev_gather(P, u, us, 3, c.s);
         if (fx) dev_gather(P, f_extra, fx, 3, c.s);
+        c.keep_order();
         c.adjoint(*prm, U, fx, ps, us, dJ_ddrag, gs, dJ_dlogK, dJ_dalpha);
         dev_scatter(P, gs, dJ_dx, 3, c.s);
         SDBIE_HIP(hipStreamSynchronize(c.s));

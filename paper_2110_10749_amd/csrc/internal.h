@@ -49,7 +49,17 @@ constexpr int kRecBytes = 128;   // largest per-source record of a pair pass
 #define SDBIE_GROUP_BYTES_F64 128
 #endif
 constexpr int kMaxRestart = 1000; // largest GMRES restart length of a plan
-constexpr int kSymChunk = 8;      // far tile pairs per block of the symmetric far field
+// symmetric passes (sym_body): tile pairs per block at most, parts a tile pair
+// is cut into at most, blocks a pass aims for, and the bits of an item's steps:
+// 16 row rotations, whether the pair may hold pairs within the cutoff, and the
+// rotations of a tile against itself
+constexpr int kSymChunk = 8;
+constexpr int kSymParts = 16;
+#ifndef SDBIE_SYM_TARGET
+#define SDBIE_SYM_TARGET 2048
+#endif
+constexpr int kSymAll = 0xffff, kSymNear = 0x10000, kSymSelf = 0x03ff;
+constexpr size_t kSymSlotBytes = (size_t)3 * kTile * sizeof(double);
 #ifndef SDBIE_SPLIT_TARGET
 #define SDBIE_SPLIT_TARGET 4096      // far-field blocks a pass kernel aims for (the near-field blocks double them)
 #endif
@@ -100,6 +110,29 @@ struct GradDesc {
     double* out;                                // sorted [3][n]
 };
 
+// Work of a symmetric pass: the tile pairs {a <= b}, each cut into parts, as
+// items (a, b, reverse slot, steps); blocks of items of one target tile, near
+// pairs first (they take longest); the first forward slot (one per block) of
+// each target tile and the first reverse slot (one per part of a pair a < b,
+// column by column) of each source tile.
+// The far-only set holds the far tile pairs alone, kSymChunk to a block; its
+// passes evaluate the near tile pairs in one-direction near-field blocks.
+// FP64 coupled solves and adjoints run on it: their inexact interface products
+// make the result within tol_ddm a function of every rounding of the pair
+// sums (the same solve with the near pairs summed in another order moves by
+// 1e-8 at the default tolerance), and these sums keep their order.
+enum : int { kSymF64 = 0, kSymF32 = 1, kSymFar64 = 2 };
+struct SymSet {
+    int nblocks = 0, parts = 1;
+    int32_t* items = nullptr;      // [nitems][4]
+    int32_t* blocks = nullptr;     // [nblocks][3]: first item, item count, forward slot
+    int32_t* fwd_start = nullptr;  // [ntiles + 1]
+    int32_t* rev_start = nullptr;  // [ntiles + 1]
+    double* fwd = nullptr;         // [nblocks][C][kTile] forward partials of the target tile, C <= 3
+    void* rev = nullptr;           // [slots][C][kTile] reverse partials of the source tile (pass precision)
+};
+constexpr int kSymRowInts = 16;
+
 struct Plan {
     int64_t n = 0;
     int max_restart = 0;
@@ -141,20 +174,15 @@ struct Plan {
     double* host_pinned = nullptr;  // not used (host buffers are plain)
     // (target, source) pairs of real nodes in the near tile pairs (double, float masks)
     double near_pairs64 = 0.0, near_pairs32 = 0.0;
-    // target-source symmetric far field (for the pass kinds whose
-    // SDBIE_SYM_* bit is set in `symmetric`): per
-    // precision (index 0 double, 1 float) the far tile pairs {a < b} numbered
-    // in column order (pair p owns a reverse slot), the work items (a, b, p) in
-    // row order cut into blocks of at most kSymChunk items, the first block of
-    // each target tile and the first pair of each source tile
+    // target-source symmetric passes (for the pass kinds whose SDBIE_SYM_* bit is
+    // set in `symmetric`): double, float, and the double far pairs alone
     int symmetric = SDBIE_SYM_DEFAULT;
-    int32_t* sym_items[2] = {};      // [npairs][3]
-    int32_t* sym_blocks[2] = {};     // [nblocks][2]: first item, item count
-    int32_t* sym_fwd_start[2] = {};  // [ntiles + 1]
-    int32_t* sym_rev_start[2] = {};  // [ntiles + 1]
-    int sym_nblocks[2] = {0, 0}, sym_npairs[2] = {0, 0};
-    double* sym_fwd = nullptr;       // [nblocks][C][kTile] forward partials of the target tile, C <= 3
-    void* sym_rev = nullptr;         // [npairs][C][kTile] reverse partials of the source tile (pass precision)
+    SymSet sym[3];
+    bool far_only64 = false;         // double passes take sym[2] and the near-field blocks (see SymSet)
+    void* sym_fwd_mem = nullptr;     // the workspace regions the slots are placed in (stage.hip), besides `partial`
+    void* sym_rev_mem = nullptr;
+    size_t partial_bytes = 0, sym_fwd_bytes = 0;
+    int32_t* sym_rows = nullptr;     // staging scratch [ntiles][kSymRowInts]
     // bookkeeping for info
     int64_t applies_fp64 = 0, applies_mixed = 0;
     double pairs = 0.0;
@@ -164,6 +192,8 @@ struct Plan {
 constexpr int kNumVec = 31;
 constexpr int kImageStride = 8;  // doubles per node of one image-basis slot: p, u, b_D, b_S
 
+// parts a tile pair of a symmetric pass is cut into on a surface of nt tiles
+int sym_parts(int64_t nt);
 size_t workspace_bytes(int64_t n, int max_restart);
 void carve_workspace(Plan& P, void* ws);
 // layer applies only (no solver vectors), at most nsplit_cap source splits and

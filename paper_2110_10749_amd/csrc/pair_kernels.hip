@@ -1214,6 +1214,34 @@ struct SymLaplace {
         acc[0] += f;
         racc[0] += rot<(16 - K) & 15>(rv);
     }
+    // the same pair with the smoothed factors: f for the target and, with REV,
+    // rv for the source s (field F at s(F))
+    template <bool REV, class Field>
+    __device__ __forceinline__ static void near(const T (&tr)[R], const Field& s, T id, T id2, T rc2, T (&f)[C],
+                                                T (&rv)[C]) {
+        const T dx = tr[0] - s(0), dy = tr[1] - s(1), dz = tr[2] - s(2);
+        const T r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+        const T ir = rsq(r2);
+        T k1 = ir, k2 = ir * ir * ir, k3, k4;
+        if (r2 < rc2) near_factors<T, SL, DL, false, false>(r2, ir, id, id2, k1, k2, k3, k4);
+        f[0] = rv[0] = T(0);
+        if constexpr (DL) {
+            const T dns = fma(dx, s(NX), fma(dy, s(NY), dz * s(NZ)));
+            const T dnt = fma(dx, tr[NX], fma(dy, tr[NY], dz * tr[NZ]));
+            if constexpr (SUB) {
+                const T dq = (s(Q) - tr[Q]) * k2;
+                f[0] = dq * dns;
+                rv[0] = dq * dnt;
+            } else {
+                f[0] = s(Q) * dns * k2;
+                rv[0] = -tr[Q] * dnt * k2;
+            }
+        }
+        if constexpr (SL) {
+            f[0] = fma(s(G), k1, f[0]);
+            rv[0] = fma(tr[G], k1, rv[0]);
+        }
+    }
 };
 
 // One step of the symmetric Stokes far field (records as StokesOp's: n and f
@@ -1276,6 +1304,44 @@ struct SymStokes {
         racc[1] += rot<(16 - K) & 15>(rc[1]);
         racc[2] += rot<(16 - K) & 15>(rc[2]);
     }
+    // the same pair with the smoothed factors (see SymLaplace::near)
+    template <bool REV, class Field>
+    __device__ __forceinline__ static void near(const T (&tr)[R], const Field& s, T id, T id2, T rc2, T (&f)[C],
+                                                T (&rv)[C]) {
+        const T dx = tr[0] - s(0), dy = tr[1] - s(1), dz = tr[2] - s(2);
+        const T r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+        const T ir = rsq(r2);
+        const T ir2 = ir * ir;
+        T k1 = ir, k2, k3 = ir * ir2, k4 = k3 * ir2;
+        if (r2 < rc2) near_factors<T, SL, false, SL, DL>(r2, ir, id, id2, k1, k2, k3, k4);
+        T cf = T(0), cr = T(0);
+        if constexpr (DL) {
+            const T ux = s(UX) - (SUB ? tr[UX] : T(0)), uy = s(UY) - (SUB ? tr[UY] : T(0)),
+                    uz = s(UZ) - (SUB ? tr[UZ] : T(0));
+            const T ud = fma(ux, dx, fma(uy, dy, uz * dz));
+            const T udr = SUB ? ud : -fma(tr[UX], dx, fma(tr[UY], dy, tr[UZ] * dz));
+            cf = ud * fma(dx, s(NX), fma(dy, s(NY), dz * s(NZ))) * k4;
+            cr = udr * fma(dx, tr[NX], fma(dy, tr[NY], dz * tr[NZ])) * k4;
+        }
+        f[0] = f[1] = f[2] = rv[0] = rv[1] = rv[2] = T(0);
+        if constexpr (SL) {
+            const T fsx = s(FX), fsy = s(FY), fsz = s(FZ);
+            cf = fma(fma(dx, fsx, fma(dy, fsy, dz * fsz)), k3, cf);
+            cr = fma(fma(dx, tr[FX], fma(dy, tr[FY], dz * tr[FZ])), k3, cr);
+            f[0] = fsx * k1;
+            f[1] = fsy * k1;
+            f[2] = fsz * k1;
+            rv[0] = tr[FX] * k1;
+            rv[1] = tr[FY] * k1;
+            rv[2] = tr[FZ] * k1;
+        }
+        f[0] = fma(cf, dx, f[0]);
+        f[1] = fma(cf, dy, f[1]);
+        f[2] = fma(cf, dz, f[2]);
+        rv[0] = fma(cr, dx, rv[0]);
+        rv[1] = fma(cr, dy, rv[1]);
+        rv[2] = fma(cr, dz, rv[2]);
+    }
 };
 
 template <class Op> struct SymOf { using type = void; };
@@ -1320,27 +1386,53 @@ constexpr unsigned sym_dpp_fields() { return sizeof(T) == 4 ? SDBIE_SYM_DPP_F32 
 
 struct SymArgs {
     int nblocks;
-    const int32_t* items;   // [npairs][3]: target tile a, source tile b, pair index p
-    const int32_t* blocks;  // [nblocks][2]: first item, item count
-    double* fwd;            // [nblocks][C][kTile]
-    void* rev;              // [npairs][C][kTile] of T
+    const int32_t* items;   // [nitems][4]: target tile a, source tile b >= a, reverse slot, steps (kSym*)
+    const int32_t* blocks;  // [nblocks][3]: first item, item count, forward slot
+    double* fwd;            // [slots][C][kTile]
+    void* rev;              // [slots][C][kTile] of T
 };
 
-template <class Sym, typename T>
-__device__ __forceinline__ void sym_far_body(const KArgs& a, const SymArgs& sa, int blk) {
+// The (wave, quarter, row rotation) steps of one tile pair: bit 4 ph + rr of an
+// item's mask runs row rotation rr of phase ph, in which wave w meets source
+// quarter (w + ph) mod 4.  A block may take a part of them: on a small surface
+// a tile pair is cut into as many as 16 parts (stage.hip), or a few blocks
+// would walk through 256 dependent steps each while most of the chip idles.
+//
+// Near tile pairs run here too: each (wave, quarter) of a near pair whose unit
+// boxes are at least the cutoff apart takes the far steps, the others a loop of
+// steps with the smoothed factors.
+//   double: those steps serve both directions as well (the smoothing is most of
+//   a near pair's work).  The reverse sums go to the source's sum in LDS with
+//   one LDS add each; a wave owns its quarter during a phase and its 64 lanes
+//   meet 64 distinct sources, so the order of the additions is fixed.  A tile
+//   against itself (b = a): phase 0 is each wave's unit with itself (one
+//   direction, self pairs included), phase 1 the unit pairs (w, w + 1), phase 2
+//   the pairs (0, 2) and (1, 3), half of whose rotations each of the two waves
+//   takes; the reverse sums are the tile's own.
+//   float: one direction, from items of both orders (b > a with the far steps
+//   of the pair, b < a without), so that each direction's close pairs keep
+//   coordinates in the frame of their own source tile: the raw double layer of
+//   a rough density moves by 1e-6 of its largest value with the frame.  A tile
+//   against itself takes all 16 rotations, one direction.
+// NEAR = false: a set without near pairs.
+template <class Sym, typename T, bool NEAR>
+__device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int blk) {
     constexpr int R = Sym::R, C = Sym::C;
     static_assert(kTile == kTPB && kTile == 256, "one target and one staged source per thread, four waves");
+    static_assert(kNearUnit == 64, "a wave's targets and a quarter of the sources are units");
     static_assert(block_terms<T>() >= 16, "a row rotation of 16 steps sums in T");
+    constexpr bool kNearBoth = sizeof(T) == 8;  // near steps serve both directions
     __shared__ T srec[R * kTile];  // the source tile, field-major: field f of source j at srec[f * kTile + j]
     __shared__ double sracc[C * kTile];  // reverse sums of the tile pair, one 16-step rotation at a time
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int first = sa.blocks[2 * blk], cnt = sa.blocks[2 * blk + 1];
-    const int ta = sa.items[3 * first];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int first = sa.blocks[3 * blk], cnt = sa.blocks[3 * blk + 1], slot = sa.blocks[3 * blk + 2];
+    const int ta = sa.items[4 * first];
     const T* rec = static_cast<const T*>(a.rec);
     T tr[R];
 #pragma unroll
     for (int f = 0; f < R; ++f) tr[f] = rec[((int64_t)ta * kTile + tid) * R + f];
     const T x0[3] = {tr[0], tr[1], tr[2]};  // the targets in their own tile's frame
+    const T id = T(a.inv_delta), id2 = id * id, rc2 = T(a.rc2);
     double acc[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) acc[c] = 0.0;
@@ -1350,7 +1442,8 @@ __device__ __forceinline__ void sym_far_body(const KArgs& a, const SymArgs& sa, 
     src.lds = srec;
     src.l16 = lane & 15;
     for (int it = first; it < first + cnt; ++it) {
-        const int tb = sa.items[3 * it + 1], p = sa.items[3 * it + 2];
+        const int tb = sa.items[4 * it + 1], p = sa.items[4 * it + 2], steps = sa.items[4 * it + 3];
+        const bool self = tb == ta;
         if constexpr (sizeof(T) == 4) {  // the targets in the source tile's frame
 #pragma unroll
             for (int c = 0; c < 3; ++c) tr[c] = x0[c] + (float)(tile_centre(a, ta, c) - tile_centre(a, tb, c));
@@ -1361,53 +1454,120 @@ __device__ __forceinline__ void sym_far_body(const KArgs& a, const SymArgs& sa, 
 #pragma unroll
         for (int c = 0; c < C; ++c) sracc[c * kTile + tid] = 0.0;
         __syncthreads();
+        // whether the pairs of this wave's targets and quarter q may lie within the cutoff
+        auto unit_near = [&](int q) {
+            if (!NEAR || !(steps & kSymNear)) return false;
+            if (!kNearBoth && self) return true;
+            const src_ptr<double> A = (src_ptr<double>)a.uboxes + (ta * 4 + wave) * 6;
+            const src_ptr<double> B = (src_ptr<double>)a.uboxes + (tb * 4 + q) * 6;
+            double d2 = 0.0;
+            for (int c = 0; c < 3; ++c) {
+                const double gap = fmax(0.0, fmax(A[2 * c] - B[2 * c + 1], B[2 * c] - A[2 * c + 1]));
+                d2 += gap * gap;
+            }
+            return !(d2 >= a.rcu2);
+        };
+        // 16 steps with the smoothed factors against the row of sources from jb on
+        auto near_steps = [&](int jb, bool reverse) {
+            T facc[C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) facc[c] = T(0);
 #pragma unroll 1
-        for (int ph = 0; ph < 4; ++ph) {
-            const int q = (wave + ph) & 3;  // the four waves take the four quarters of the sources
-#pragma unroll 1
-            for (int rr = 0; rr < 4; ++rr) {
-                // row r of the wave holds row (r + rr) mod 4 of the quarter
-                src.jb = 64 * q + ((((lane >> 4) + rr) & 3) << 4);
-                const int j = src.jb + src.l16;
+            for (int k = 0; k < 16; ++k) {
+                const int j = jb + ((src.l16 - k) & 15);
+                T f[C], rv[C];
+                Sym::template near<kNearBoth>(
+                    tr, [&](int fld) { return srec[fld * kTile + j]; }, id, id2, rc2, f, rv);
 #pragma unroll
-                for (int f = 0; f < R; ++f)
-                    if ((DPP >> f) & 1u) src.own[f] = srec[f * kTile + j];
-                T facc[C], racc[C];
+                for (int c = 0; c < C; ++c) facc[c] += f[c];
+                if (kNearBoth && reverse) {
 #pragma unroll
-                for (int c = 0; c < C; ++c) facc[c] = racc[c] = T(0);
-                SymSteps<Sym, T, 0>::run(tr, src, facc, racc);
-                // 16 terms of each sum in T, then into the double sums
-#pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    acc[c] += (double)facc[c];
-                    sracc[c * kTile + j] += (double)racc[c];
+                    for (int c = 0; c < C; ++c) unsafeAtomicAdd(&sracc[c * kTile + j], (double)rv[c]);
                 }
             }
-            __syncthreads();  // each quarter's reverse sums go to the wave that takes it next
-        }
 #pragma unroll
-        for (int c = 0; c < C; ++c) rev[((int64_t)p * C + c) * kTile + tid] = T(sracc[c * kTile + tid]);
+            for (int c = 0; c < C; ++c) acc[c] += (double)facc[c];
+        };
+        if (kNearBoth || tb > ta) {
+#pragma unroll 1
+            for (int ph = 0; ph < 4; ++ph) {
+                const int rots = (steps >> (4 * ph)) & 15;
+                if (!rots) continue;  // uniform over the block
+                const int q = (wave + ph) & 3;  // the four waves take the four quarters of the sources
+                const bool near = unit_near(q);
+#pragma unroll 1
+                for (int rr = 0; rr < 4; ++rr) {
+                    if (!((rots >> rr) & 1) || (near && !kNearBoth)) continue;
+                    // row r of the wave holds row (r + turn) mod 4 of the quarter
+                    const int turn = kNearBoth && self && ph == 2 && wave >= 2 ? 2 - rr : rr;
+                    src.jb = 64 * q + ((((lane >> 4) + turn) & 3) << 4);
+                    if (NEAR && kNearBoth && near) {
+                        near_steps(src.jb, !(self && ph == 0));
+                        continue;
+                    }
+                    const int j = src.jb + src.l16;
+#pragma unroll
+                    for (int f = 0; f < R; ++f)
+                        if ((DPP >> f) & 1u) src.own[f] = srec[f * kTile + j];
+                    T facc[C], racc[C];
+#pragma unroll
+                    for (int c = 0; c < C; ++c) facc[c] = racc[c] = T(0);
+                    SymSteps<Sym, T, 0>::run(tr, src, facc, racc);
+                    // 16 terms of each sum in T, then into the double sums
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        acc[c] += (double)facc[c];
+                        sracc[c * kTile + j] += (double)racc[c];
+                    }
+                }
+                __syncthreads();  // each quarter's reverse sums go to the wave that takes it next
+            }
+        }
+        if (NEAR && !kNearBoth && (steps & kSymNear)) {
+            // one direction: nothing is handed over, so the waves need not wait for each other
+#pragma unroll 1
+            for (int ph = 0; ph < 4; ++ph) {
+                const int rots = (steps >> (4 * ph)) & 15;
+                const int q = (wave + ph) & 3;
+                if (!rots || !unit_near(q)) continue;
+#pragma unroll 1
+                for (int rr = 0; rr < 4; ++rr)
+                    if ((rots >> rr) & 1) near_steps(64 * q + ((((lane >> 4) + rr) & 3) << 4), false);
+            }
+        }
+        if (self) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) acc[c] += sracc[c * kTile + tid];
+        } else if (kNearBoth || tb > ta) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) rev[((int64_t)p * C + c) * kTile + tid] = T(sracc[c * kTile + tid]);
+        }
     }
 #pragma unroll
-    for (int c = 0; c < C; ++c) sa.fwd[((int64_t)blk * C + c) * kTile + tid] = acc[c];
+    for (int c = 0; c < C; ++c) sa.fwd[((int64_t)slot * C + c) * kTile + tid] = acc[c];
 }
 
-// symmetric far blocks first, then the near-field blocks of the pass.  Left
-// alone, the compiler hoists the LDS reads of a whole row rotation ahead of
-// its 16 steps (up to 134 VGPRs, 3 waves per SIMD for the float Laplace double
-// layer); the float passes are held to 8 waves per SIMD.
-template <class Op, class Sym, typename T>
+// Left alone, the compiler hoists the LDS reads of a whole row rotation ahead
+// of its 16 steps (up to 134 VGPRs, 3 waves per SIMD for the float Laplace
+// double layer); the float passes are held to 8 waves per SIMD.
+template <class Sym, typename T>
 __global__ __launch_bounds__(kTPB) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 8 : 1)))
 void sym_pass_pairs(KArgs a, SymArgs sa) {
-    if ((int)blockIdx.x < sa.nblocks) sym_far_body<Sym, T>(a, sa, blockIdx.x);
-    else near_body<Op, T>(a, (int)blockIdx.x - sa.nblocks);
+    sym_body<Sym, T, true>(a, sa, blockIdx.x);
+}
+
+// far pairs alone, then the one-direction near-field blocks (double)
+template <class Op, class Sym>
+__global__ __launch_bounds__(kTPB) void sym_far_near_pairs(KArgs a, SymArgs sa) {
+    if ((int)blockIdx.x < sa.nblocks) sym_body<Sym, double, false>(a, sa, blockIdx.x);
+    else near_body<Op, double>(a, (int)blockIdx.x - sa.nblocks);
 }
 
 // Sum of the symmetric pass per target, in a fixed order, then the terms of
 // epilogue(): the forward slots of its tile's blocks, the reverse slots of the
-// far tile pairs with its tile as the source tile (about T/2 of them), the
-// near-field split slots; each kind split over the 8 thread groups of the
-// target as in epilogue().
+// tile pairs with its tile as the source tile (about T/2 of them) and, of a
+// far-only set, the near-field split slots (nsplit = 0 otherwise); each kind
+// split over the 8 thread groups of the target as in epilogue().
 template <int C, typename RT>
 __global__ __launch_bounds__(kEpiThreads) void sym_epilogue(
     int64_t n, const int32_t* __restrict__ fwd_start, const double* __restrict__ fwd,
@@ -1424,9 +1584,11 @@ __global__ __launch_bounds__(kEpiThreads) void sym_epilogue(
     if (i < n) {
         const int64_t t = i / kTile, j = i % kTile;
         const int b1 = fwd_start[t + 1], p1 = rev_start[t + 1];
+#pragma unroll 4
         for (int b = fwd_start[t] + g; b < b1; b += kEpiGroups)
 #pragma unroll
             for (int c = 0; c < C; ++c) v[c] += fwd[((int64_t)b * C + c) * kTile + j];
+#pragma unroll 4
         for (int p = rev_start[t] + g; p < p1; p += kEpiGroups)
 #pragma unroll
             for (int c = 0; c < C; ++c) v[c] += (double)rev[((int64_t)p * C + c) * kTile + j];
@@ -1474,6 +1636,10 @@ struct family_is_gradient { static constexpr bool value = false; };
 template <bool SWAP>
 struct family_is_gradient<GradOp<SWAP>> { static constexpr bool value = true; };
 
+const SymSet& sym_set(const Plan& P, bool mixed) {
+    return P.sym[mixed ? kSymF32 : P.far_only64 ? kSymFar64 : kSymF64];
+}
+
 // pack and pair kernels of one pass, each timed on its own when kernel timing
 // is on (pairs: all N^2 for a pass kernel; with separate far and near
 // launches, the real-node pairs of the far / near tile pairs)
@@ -1492,18 +1658,25 @@ bool launch_pair_kernels(const Plan& P, const KArgs& a, hipStream_t st, int fami
     }
     using Sym = typename SymOf<Op>::type;
     if constexpr (!std::is_same<Sym, void>::value) {
-        const int k = mixed ? 1 : 0;
         const int kind = mixed ? Sym::kFamilyBit : Sym::kFamilyBit << 2;  // SDBIE_SYM_* of this pass
-        if ((P.symmetric & kind) && P.sym_items[k] && P.sym_nblocks[k] > 0 && !a.dl_tgt) {
+        const SymSet& S = sym_set(P, mixed);
+        if ((P.symmetric & kind) && S.nblocks > 0 && !a.dl_tgt) {
             SymArgs sa;
-            sa.nblocks = P.sym_nblocks[k];
-            sa.items = P.sym_items[k];
-            sa.blocks = P.sym_blocks[k];
-            sa.fwd = P.sym_fwd;
-            sa.rev = P.sym_rev;
+            sa.nblocks = S.nblocks;
+            sa.items = S.items;
+            sa.blocks = S.blocks;
+            sa.fwd = S.fwd;
+            sa.rev = S.rev;
             ProfScope prof(prof_variant(family, mixed, code, 4), all, st);
-            hipLaunchKernelGGL((sym_pass_pairs<Op, Sym, T>), dim3((unsigned)(sa.nblocks + a.ntiles * a.nsplit)),
-                               dim3(kTPB), 0, st, a, sa);
+            if constexpr (sizeof(T) == 8) {
+                if (P.far_only64) {
+                    hipLaunchKernelGGL((sym_far_near_pairs<Op, Sym>),
+                                       dim3((unsigned)(sa.nblocks + a.ntiles * a.nsplit)), dim3(kTPB), 0, st, a, sa);
+                    SDBIE_LAUNCHED();
+                    return true;
+                }
+            }
+            hipLaunchKernelGGL((sym_pass_pairs<Sym, T>), dim3((unsigned)sa.nblocks), dim3(kTPB), 0, st, a, sa);
             SDBIE_LAUNCHED();
             return true;
         }
@@ -1548,17 +1721,16 @@ void launch_epilogue(const Plan& P, const PassDesc& d, int S, bool sym, hipStrea
     const double* tw = d.target_weight ? (const double*)P.w : nullptr;
     const int32_t* perm = d.scatter ? (const int32_t*)P.perm : nullptr;
     if (sym) {
-        const int k = d.mixed ? 1 : 0;
+        const SymSet& Y = sym_set(P, d.mixed);
+        const int nsplit = !d.mixed && P.far_only64 ? S : 0;
         if (d.mixed)
-            hipLaunchKernelGGL((sym_epilogue<C, float>), dim3(eb), et, 0, st, P.n,
-                               (const int32_t*)P.sym_fwd_start[k], (const double*)P.sym_fwd,
-                               (const int32_t*)P.sym_rev_start[k], (const float*)P.sym_rev, S,
+            hipLaunchKernelGGL((sym_epilogue<C, float>), dim3(eb), et, 0, st, P.n, (const int32_t*)Y.fwd_start,
+                               (const double*)Y.fwd, (const int32_t*)Y.rev_start, (const float*)Y.rev, nsplit,
                                (const double*)P.partial, tw, d.base, d.base_scale, d.comp, d.comp_scale,
                                (const double*)P.nrm, a0, a1, a2, d.out, perm);
         else
-            hipLaunchKernelGGL((sym_epilogue<C, double>), dim3(eb), et, 0, st, P.n,
-                               (const int32_t*)P.sym_fwd_start[k], (const double*)P.sym_fwd,
-                               (const int32_t*)P.sym_rev_start[k], (const double*)P.sym_rev, S,
+            hipLaunchKernelGGL((sym_epilogue<C, double>), dim3(eb), et, 0, st, P.n, (const int32_t*)Y.fwd_start,
+                               (const double*)Y.fwd, (const int32_t*)Y.rev_start, (const double*)Y.rev, nsplit,
                                (const double*)P.partial, tw, d.base, d.base_scale, d.comp, d.comp_scale,
                                (const double*)P.nrm, a0, a1, a2, d.out, perm);
     } else {

@@ -51,7 +51,7 @@ enum : int {
     kScalMean = 2,
     kScalNorm = 3,
     kScalDrag = 4,   // 3 slots
-    kScalStage = 16, // staging: finite flag (16), bounding box (18..23), weight sum (24), near-pair counts (26, 27)
+    kScalStage = 16, // staging: finite flag (16), bounding box (18..23), weight sum (24), near-pair counts (26, 27), list counts (28 .. 31)
     kScalGmres = 32, // inner and outer Hessenberg columns / coefficients
 };
 
@@ -122,6 +122,11 @@ struct Ctx {
     Recycle* rc_cur = nullptr;
 
     Ctx(Plan& plan, hipStream_t st, const sdbie_opts& opts);
+    ~Ctx() { P.far_only64 = false; }
+    Ctx(const Ctx&) = delete;
+    Ctx& operator=(const Ctx&) = delete;
+    // FP64 coupled solves and adjoints: the pair sums keep their order (see SymSet)
+    void keep_order() { P.far_only64 = o.prec == SDBIE_FP64; }
     void finish();
 
     double norm(const double* a, int64_t len);

@@ -14,7 +14,6 @@
 // coordinates in the frame of each node's tile; and the near-field masks of
 // tile pairs (box distance below rho_cut delta, one mask for the double cutoff
 // and one for the float cutoff).
-#include <vector>
 
 #include "smoothing_coeffs.h"
 #include "solver.h"
@@ -198,58 +197,303 @@ __global__ void k_near_masks(int nt, int64_t n, const double* __restrict__ boxes
     }
 }
 
-// Work lists of the symmetric far field, from the near masks (host side):
-// the far tile pairs {a < b} numbered column by column (pair p of column b
-// owns a reverse-partial slot of source tile b; rev_start[b] is the first),
-// and the same pairs as work items (a, b, p) row by row, cut into blocks of at
-// most kSymChunk items of one target tile a (fwd_start[a] is its first block).
-void build_symmetric_lists(Plan& P, hipStream_t st) {
-    const int T = P.ntiles;
-    std::vector<uint8_t> m((size_t)T * T);
-    std::vector<int32_t> pid((size_t)T * T, -1), rev_start(T + 1), fwd_start(T + 1), items, blocks;
+// Work lists of the symmetric passes, from the near masks, in three kernels:
+// counts of each mask row, their prefix sums (one block), and the items and
+// blocks of each row.  Blocks hold as many pairs as leave about
+// SDBIE_SYM_TARGET of them for each kind of pair (at most kSymChunk while the
+// forward slots have room): with 8 pairs to a block the 2200 pairs of n = 17070
+// made 343 blocks for 256 CUs.
+
+// position of this thread's flag among the set flags of the block (256 threads), and their number
+__device__ __forceinline__ int block_rank(bool f, int* sh, int& total) {
+    const uint64_t bal = __ballot(f);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (lane == 0) sh[w] = __popcll(bal);
+    __syncthreads();
+    int before = __popcll(bal & ((1ull << lane) - 1));
+    total = 0;
+    for (int k = 0; k < 4; ++k) {
+        if (k < w) before += sh[k];
+        total += sh[k];
+    }
+    __syncthreads();
+    return before;
+}
+
+// ints of a row in sym_rows: counts, then (k_list_scan) starts
+enum : int {
+    kRowNear64 = 0,  // near pairs b > a (double)
+    kRowFar64,       // far pairs b > a
+    kRowColFar64,    // far pairs b < a
+    kRowNear32,      // near pairs b != a (float)
+    kRowFar32,       // far pairs b > a
+    kRowItem,        // first item: double, float, far-only (3)
+    kRowNearBlk = kRowItem + 3,    // first near block: double, float (2)
+    kRowFarBlk = kRowNearBlk + 2,  // first far block: double, float, far-only (3)
+};
+static_assert(kRowFarBlk + 3 <= kSymRowInts, "ints of a row");
+
+__global__ __launch_bounds__(256) void k_list_rows(int T, const uint8_t* __restrict__ m64,
+                                                   const uint8_t* __restrict__ m32, int32_t* __restrict__ rows,
+                                                   int32_t* __restrict__ colrank) {
+    __shared__ int sh[4];
+    const int a = blockIdx.x;
+    int cnt[5] = {0, 0, 0, 0, 0};
+    for (int b0 = 0; b0 < T; b0 += 256) {
+        const int b = b0 + threadIdx.x;
+        const bool in = b < T;
+        const bool n64 = in && m64[(int64_t)a * T + b], n32 = in && m32[(int64_t)a * T + b];
+        int t;
+        block_rank(in && b > a && n64, sh, t);
+        cnt[kRowNear64] += t;
+        block_rank(in && b > a && !n64, sh, t);
+        cnt[kRowFar64] += t;
+        // the masks are symmetric: row a, b < a, is the far-only column of source tile a
+        const bool cf = in && b < a && !n64;
+        const int r = block_rank(cf, sh, t);
+        if (cf) colrank[(int64_t)a * T + b] = cnt[kRowColFar64] + r;
+        cnt[kRowColFar64] += t;
+        block_rank(in && b != a && n32, sh, t);
+        cnt[kRowNear32] += t;
+        block_rank(in && b > a && !n32, sh, t);
+        cnt[kRowFar32] += t;
+    }
+    if (threadIdx.x < 5) rows[(int64_t)a * kSymRowInts + threadIdx.x] = cnt[threadIdx.x];
+}
+
+struct ListArgs {
+    int T;
+    int parts[2], self_parts[2];  // double, float
+    int room[2];                  // forward slots
+    const uint8_t* mask[2];
+    const int32_t* colrank;
+    int32_t* rows;
+    int32_t *items[3], *blocks[3], *fwd_start[3], *rev_start[3];
+    int32_t* out;  // number of blocks of the three sets, near and far chunk of double and float
+};
+
+constexpr int kScanRows = 8;  // rows per thread of the scan (2048 tiles)
+
+// exclusive prefix sums over the rows of v[0..kScanRows) (thread-consecutive), total over all
+__device__ __forceinline__ int block_scan(int (&v)[kScanRows], int* sh) {
+    int s = 0;
+#pragma unroll
+    for (int i = 0; i < kScanRows; ++i) {
+        const int t = v[i];
+        v[i] = s;
+        s += t;
+    }
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int o = 1; o < 256; o <<= 1) {
+        const int t = (int)threadIdx.x >= o ? sh[threadIdx.x - o] : 0;
+        __syncthreads();
+        sh[threadIdx.x] += t;
+        __syncthreads();
+    }
+    const int base = threadIdx.x ? sh[threadIdx.x - 1] : 0, total = sh[255];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kScanRows; ++i) v[i] += base;
+    return total;
+}
+
+__global__ __launch_bounds__(256) void k_list_scan(ListArgs A) {
+    __shared__ int sh[256];
+    const int r0 = threadIdx.x * kScanRows;
+    auto row = [&](int i, int what) { return r0 + i < A.T ? A.rows[(int64_t)(r0 + i) * kSymRowInts + what] : 0; };
+    auto put = [&](int i, int what, int v) {
+        if (r0 + i < A.T) A.rows[(int64_t)(r0 + i) * kSymRowInts + what] = v;
+    };
+    int v[kScanRows];
     for (int k = 0; k < 2; ++k) {
-        SDBIE_HIP(hipMemcpyAsync(m.data(), k ? P.mask32 : P.mask64, m.size(), hipMemcpyDeviceToHost, st));
-        SDBIE_HIP(hipStreamSynchronize(st));
-        int np = 0;
-        for (int b = 0; b < T; ++b) {
-            rev_start[b] = np;
-            for (int a = 0; a < b; ++a)
-                if (!m[(size_t)a * T + b]) pid[(size_t)a * T + b] = np++;
+        const int wn = k ? kRowNear32 : kRowNear64, wf = k ? kRowFar32 : kRowFar64, parts = A.parts[k];
+#pragma unroll
+        for (int i = 0; i < kScanRows; ++i) v[i] = r0 + i < A.T ? 1 + row(i, wn) : 0;
+        const int near = block_scan(v, sh);
+#pragma unroll
+        for (int i = 0; i < kScanRows; ++i) v[i] = row(i, wf);
+        const int far = block_scan(v, sh);
+        int nc = min(max(near / SDBIE_SYM_TARGET, 1), kSymChunk), fc = min(max(far / SDBIE_SYM_TARGET, 1), kSymChunk);
+        if (parts > 1) nc = fc = 1;
+        else
+            while (near / nc + far / fc + 2 * A.T > A.room[k]) {  // room holds 2 T slots and more
+                ++nc;
+                ++fc;
+            }
+        auto near_items = [&](int i) { return A.self_parts[k] + row(i, wn) * parts; };
+#pragma unroll
+        for (int i = 0; i < kScanRows; ++i) v[i] = r0 + i < A.T ? near_items(i) + row(i, wf) * parts : 0;
+        block_scan(v, sh);
+#pragma unroll
+        for (int i = 0; i < kScanRows; ++i) put(i, kRowItem + k, v[i]);
+#pragma unroll
+        for (int i = 0; i < kScanRows; ++i) v[i] = r0 + i < A.T ? (near_items(i) + nc - 1) / nc : 0;
+        const int nb = block_scan(v, sh);
+        int fwd[kScanRows];
+#pragma unroll
+        for (int i = 0; i < kScanRows; ++i) {
+            put(i, kRowNearBlk + k, v[i]);
+            fwd[i] = v[i];
         }
-        rev_start[T] = np;
-        items.clear();
-        blocks.clear();
-        for (int a = 0; a < T; ++a) {
-            fwd_start[a] = (int32_t)(blocks.size() / 2);
-            int cnt = 0;
-            for (int b = a + 1; b < T; ++b) {
-                if (m[(size_t)a * T + b]) continue;
-                if (cnt == 0) {
-                    blocks.push_back((int32_t)(items.size() / 3));
-                    blocks.push_back(0);
-                }
-                items.push_back(a);
-                items.push_back(b);
-                items.push_back(pid[(size_t)a * T + b]);
-                ++blocks.back();
-                if (++cnt == kSymChunk) cnt = 0;
+#pragma unroll
+        for (int i = 0; i < kScanRows; ++i) v[i] = (row(i, wf) * parts + fc - 1) / fc;
+        const int fb = block_scan(v, sh);
+#pragma unroll
+        for (int i = 0; i < kScanRows; ++i) {
+            put(i, kRowFarBlk + k, nb + v[i]);
+            const int b = r0 + i;
+            if (b < A.T) {
+                A.fwd_start[k][b] = fwd[i] + v[i];
+                A.rev_start[k][b] = b * (b - 1) / 2 * parts;
             }
         }
-        fwd_start[T] = (int32_t)(blocks.size() / 2);
-        P.sym_npairs[k] = np;
-        P.sym_nblocks[k] = (int)(blocks.size() / 2);
-        if (np > 0) {
-            SDBIE_HIP(hipMemcpyAsync(P.sym_items[k], items.data(), items.size() * sizeof(int32_t),
-                                     hipMemcpyHostToDevice, st));
-            SDBIE_HIP(hipMemcpyAsync(P.sym_blocks[k], blocks.data(), blocks.size() * sizeof(int32_t),
-                                     hipMemcpyHostToDevice, st));
+        if (threadIdx.x == 0) {
+            A.fwd_start[k][A.T] = nb + fb;
+            A.rev_start[k][A.T] = A.T * (A.T - 1) / 2 * parts;
+            A.out[k] = nb + fb;
+            A.out[3 + 2 * k] = nc;
+            A.out[4 + 2 * k] = fc;
         }
-        SDBIE_HIP(hipMemcpyAsync(P.sym_fwd_start[k], fwd_start.data(), (T + 1) * sizeof(int32_t),
-                                 hipMemcpyHostToDevice, st));
-        SDBIE_HIP(hipMemcpyAsync(P.sym_rev_start[k], rev_start.data(), (T + 1) * sizeof(int32_t),
-                                 hipMemcpyHostToDevice, st));
-        SDBIE_HIP(hipStreamSynchronize(st));  // the host vectors are reused
     }
+    // far pairs alone
+#pragma unroll
+    for (int i = 0; i < kScanRows; ++i) v[i] = row(i, kRowFar64);
+    block_scan(v, sh);
+#pragma unroll
+    for (int i = 0; i < kScanRows; ++i) put(i, kRowItem + 2, v[i]);
+#pragma unroll
+    for (int i = 0; i < kScanRows; ++i) v[i] = (row(i, kRowFar64) + kSymChunk - 1) / kSymChunk;
+    const int fb = block_scan(v, sh);
+#pragma unroll
+    for (int i = 0; i < kScanRows; ++i) {
+        put(i, kRowFarBlk + 2, v[i]);
+        if (r0 + i < A.T) A.fwd_start[2][r0 + i] = v[i];
+    }
+#pragma unroll
+    for (int i = 0; i < kScanRows; ++i) v[i] = row(i, kRowColFar64);
+    const int np = block_scan(v, sh);
+#pragma unroll
+    for (int i = 0; i < kScanRows; ++i)
+        if (r0 + i < A.T) A.rev_start[2][r0 + i] = v[i];
+    if (threadIdx.x == 0) {
+        A.fwd_start[2][A.T] = fb;
+        A.rev_start[2][A.T] = np;
+        A.out[2] = fb;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_list_fill(ListArgs A) {
+    __shared__ int sh[4];
+    const int a = blockIdx.x, T = A.T;
+    const int32_t* row = A.rows + (int64_t)a * kSymRowInts;
+    // item `idx` of `total` of one kind (near or far) of this row; `slot0`: the kind's first forward slot
+    auto item = [&](int k, int first, int idx, int total, int chunk, int blk0, int slot0, int b, int p, int steps) {
+        int32_t* it = A.items[k] + (int64_t)(first + idx) * 4;
+        it[0] = a;
+        it[1] = b;
+        it[2] = p;
+        it[3] = steps;
+        if (idx % chunk == 0) {
+            int32_t* bl = A.blocks[k] + (int64_t)(blk0 + idx / chunk) * 3;
+            bl[0] = first + idx;
+            bl[1] = total - idx < chunk ? total - idx : chunk;
+            bl[2] = slot0 + idx / chunk;
+        }
+    };
+    for (int k = 0; k < 2; ++k) {
+        const bool both = k == 1;
+        const int parts = A.parts[k], width = 16 / parts, one = (1 << width) - 1;
+        const int nc = A.out[3 + 2 * k], fc = A.out[4 + 2 * k];
+        const int nnear = A.self_parts[k] + row[both ? kRowNear32 : kRowNear64] * parts;
+        const int nfar = row[both ? kRowFar32 : kRowFar64] * parts;
+        const int first = row[kRowItem + k], slot = A.fwd_start[k][a], nblk = (nnear + nc - 1) / nc;
+        if ((int)threadIdx.x < A.self_parts[k])
+            item(k, first, threadIdx.x, nnear, nc, row[kRowNearBlk + k], slot, a, 0,
+                 ((one << (threadIdx.x * width)) & (both ? kSymAll : kSymSelf)) | kSymNear);
+        int near = 0, far = 0;
+        for (int b0 = 0; b0 < T; b0 += 256) {
+            const int b = b0 + threadIdx.x;
+            const bool m = b < T && A.mask[k][(int64_t)a * T + b];
+            int t;
+            const bool fn = m && (b > a || (both && b < a));
+            const int rn = block_rank(fn, sh, t);
+            if (fn)
+                for (int q = 0; q < parts; ++q)
+                    item(k, first, A.self_parts[k] + (near + rn) * parts + q, nnear, nc, row[kRowNearBlk + k], slot, b,
+                         b > a ? (b * (b - 1) / 2 + a) * parts + q : 0, (one << (q * width)) | kSymNear);
+            near += t;
+            const bool ff = b < T && b > a && !m;
+            const int rf = block_rank(ff, sh, t);
+            if (ff)
+                for (int q = 0; q < parts; ++q)
+                    item(k, first + nnear, (far + rf) * parts + q, nfar, fc, row[kRowFarBlk + k], slot + nblk, b,
+                         (b * (b - 1) / 2 + a) * parts + q, one << (q * width));
+            far += t;
+        }
+    }
+    int far = 0;
+    for (int b0 = 0; b0 < T; b0 += 256) {
+        const int b = b0 + threadIdx.x;
+        const bool f = b < T && b > a && !A.mask[0][(int64_t)a * T + b];
+        int t;
+        const int r = block_rank(f, sh, t);
+        if (f)
+            item(2, row[kRowItem + 2], far + r, row[kRowFar64], kSymChunk, row[kRowFarBlk + 2], A.fwd_start[2][a], b,
+                 A.rev_start[2][b] + A.colrank[(int64_t)b * T + a], kSymAll);
+        far += t;
+    }
+}
+
+// Enqueues the list kernels; the block counts arrive in out[0..2] (device).
+// Forward and reverse slots of several parts to a pair share the partial
+// buffer of the one-direction passes; of one part the reverse slots have their
+// own region, and the forward ones take the larger of the buffer and sym_fwd.
+void build_symmetric_lists(Plan& P, int32_t* out, hipStream_t st) {
+    const int T = P.ntiles;
+    if (T > 256 * kScanRows) throw Error(SDBIE_ERR_ARG, "internal: symmetric lists of too many tiles");
+    const int64_t pairs = (int64_t)T * (T - 1) / 2;
+    ListArgs A;
+    A.T = T;
+    A.mask[0] = P.mask64;
+    A.mask[1] = P.mask32;
+    A.rows = P.sym_rows;
+    A.colrank = static_cast<const int32_t*>(P.rec);  // T^2 ints; no pass runs yet
+    A.out = out;
+    const bool in_partial = P.partial_bytes > P.sym_fwd_bytes;
+    for (int k = 0; k < 2; ++k) {
+        SymSet& S = P.sym[k];
+        const int64_t items = k == kSymF32 ? (int64_t)T * T : pairs + T;  // at most, of one part
+        S.parts = sym_parts(T);
+        while (S.parts > 1 && (items + pairs) * S.parts * kSymSlotBytes > P.partial_bytes) S.parts /= 2;
+        A.parts[k] = S.parts;
+        const int width = 16 / S.parts;
+        A.self_parts[k] = k == kSymF32 ? S.parts : (10 + width - 1) / width;  // parts with a step of kSymSelf
+        if (S.parts > 1) {
+            S.fwd = P.partial;
+            S.rev = reinterpret_cast<char*>(P.partial) + (size_t)items * S.parts * kSymSlotBytes;
+            A.room[k] = (int)(items * S.parts);
+        } else {
+            S.fwd = in_partial ? P.partial : static_cast<double*>(P.sym_fwd_mem);
+            S.rev = P.sym_rev_mem;
+            A.room[k] = (int)((in_partial ? P.partial_bytes : P.sym_fwd_bytes) / kSymSlotBytes);
+        }
+    }
+    P.sym[kSymFar64].fwd = static_cast<double*>(P.sym_fwd_mem);  // the near blocks write to `partial`
+    P.sym[kSymFar64].rev = P.sym_rev_mem;
+    for (int k = 0; k < 3; ++k) {
+        A.items[k] = P.sym[k].items;
+        A.blocks[k] = P.sym[k].blocks;
+        A.fwd_start[k] = P.sym[k].fwd_start;
+        A.rev_start[k] = P.sym[k].rev_start;
+    }
+    hipLaunchKernelGGL(k_list_rows, dim3((unsigned)T), dim3(256), 0, st, T, (const uint8_t*)P.mask64,
+                       (const uint8_t*)P.mask32, P.sym_rows, static_cast<int32_t*>(P.rec));
+    SDBIE_LAUNCHED();
+    hipLaunchKernelGGL(k_list_scan, dim3(1), dim3(256), 0, st, A);
+    SDBIE_LAUNCHED();
+    hipLaunchKernelGGL(k_list_fill, dim3((unsigned)T), dim3(256), 0, st, A);
+    SDBIE_LAUNCHED();
 }
 
 }  // namespace
@@ -306,14 +550,21 @@ void stage_surface(Plan& P, const sdbie_surface* s, hipStream_t st) {
     hipLaunchKernelGGL(k_near_masks, dim3((unsigned)((nt2 + 255) / 256)), dim3(256), 0, st, P.ntiles, n,
                        (const double*)P.boxes, rc64, rc32, P.mask64, P.mask32, cnt);
     SDBIE_LAUNCHED();
-    unsigned long long hc[2] = {0, 0};
-    SDBIE_HIP(hipMemcpyAsync(hc, cnt, sizeof(hc), hipMemcpyDeviceToHost, st));
-    SDBIE_HIP(hipStreamSynchronize(st));
-    P.near_pairs64 = (double)hc[0];
-    P.near_pairs32 = (double)hc[1];
-    if (P.sym_items[0]) build_symmetric_lists(P, st);
+    const bool lists = P.sym[0].items != nullptr;
+    if (lists) build_symmetric_lists(P, reinterpret_cast<int32_t*>(P.scal + kScalStage + 12), st);
     dev_dot(P, P.w, nullptr, n, P.scal + kScalStage + 8, st);
-    P.area = host_read_scalar(P.scal + kScalStage + 8, st);
+    struct {
+        double area, pad;
+        unsigned long long near[2];
+        int32_t blocks[8];
+    } h;
+    static_assert(sizeof(h) == 8 * sizeof(double), "area (8), near-pair counts (10, 11), list counts (12 ..)");
+    SDBIE_HIP(hipMemcpyAsync(&h, P.scal + kScalStage + 8, sizeof(h), hipMemcpyDeviceToHost, st));
+    SDBIE_HIP(hipStreamSynchronize(st));
+    P.near_pairs64 = (double)h.near[0];
+    P.near_pairs32 = (double)h.near[1];
+    P.area = h.area;
+    for (int k = 0; lists && k < 3; ++k) P.sym[k].nblocks = h.blocks[k];
     if (!(P.area > 0.0)) throw Error(SDBIE_ERR_ARG, "the quadrature weights sum to zero");
 }
 
