@@ -4,6 +4,8 @@
 // partial per block (wave shuffles, then LDS in a fixed order) and a single
 // block adds the partials in a fixed order.  Results are bitwise
 // reproducible from run to run.
+#include <utility>
+
 #include "internal.h"
 
 namespace sdbie {
@@ -37,18 +39,18 @@ __global__ __launch_bounds__(256) void k_dot_partial(const double* __restrict__ 
     if (threadIdx.x == 0) part[blockIdx.x] = r;
 }
 
-// part: [nb][k] -> out[j] = sum_b part[b][j], one block per j
-__global__ __launch_bounds__(256) void k_reduce_cols(const double* __restrict__ part, int nb, int k,
+// part: [k][nb] -> out[j] = sum_b part[j][b], one block per j
+__global__ __launch_bounds__(256) void k_reduce_cols(const double* __restrict__ part, int nb,
                                                      double* __restrict__ out) {
     __shared__ double sh[4];
     const int j = blockIdx.x;
     double s = 0.0;
-    for (int b = threadIdx.x; b < nb; b += 256) s += part[(int64_t)b * k + j];
+    for (int b = threadIdx.x; b < nb; b += 256) s += part[(int64_t)j * nb + b];
     const double r = block_sum(s, sh);
     if (threadIdx.x == 0) out[j] = r;
 }
 
-// part[b][j] = sum over block b's chunk of V_j . w; blockIdx.y takes kDotCols
+// part[j][b] = sum over block b's chunk of V_j . w; blockIdx.y takes kDotCols
 // columns at a time, so w is read once per kDotCols columns (fixed order)
 constexpr int kDotCols = 8;
 __global__ __launch_bounds__(256) void k_multidot_partial(const double* __restrict__ V, int64_t ld, int k,
@@ -71,8 +73,149 @@ __global__ __launch_bounds__(256) void k_multidot_partial(const double* __restri
     }
     for (int c = 0; c < nc; ++c) {
         const double r = block_sum(acc[c], sh);
-        if (threadIdx.x == 0) part[(int64_t)blockIdx.x * k + j0 + c] = r;
+        if (threadIdx.x == 0) part[(int64_t)(j0 + c) * gridDim.x + blockIdx.x] = r;
     }
+}
+
+// ---- fused Gram-Schmidt ------------------------------------------------------
+// One Krylov step orthogonalises w against k columns twice and normalises it.
+// As separate kernels that is nine launches, most of them a few microseconds of
+// launch and drain around less work (n = 2650: 45 us of a 250 us iteration).
+// Here each kernel reduces the previous one's block partials itself (every block
+// redundantly: k columns of 512 partials from L2) and ends on the partials of the
+// next dot products: k_multidot_partial, k_cgs_step, k_cgs_last, k_cgs_scale.
+// The additions are those of k_reduce_cols, k_multi_axpy, k_multidot_partial and
+// k_dot_partial in their order, so the results are the same bit for bit.
+
+// sum of kRedBlocks block partials by one wave: k_reduce_cols' order (its four
+// waves' trees, then (0 + 1) + (2 + 3))
+__device__ __forceinline__ double reduce_blocks(const double* __restrict__ part) {
+    const int lane = threadIdx.x & 63;
+    static_assert(kRedBlocks == 512, "two partials per thread of a 256-thread block");
+    double r[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) r[v] = wave_sum(part[64 * v + lane] + part[64 * v + lane + 256]);
+    return (r[0] + r[1]) + (r[2] + r[3]);
+}
+
+// h[j] = sum of column j's partials, j < k (k <= kFuseCols); ends on a barrier
+__device__ __forceinline__ void reduce_columns(const double* __restrict__ part, int k, double* h) {
+    for (int j = threadIdx.x >> 6; j < k; j += 4) {
+        const double r = reduce_blocks(part + (int64_t)j * kRedBlocks);
+        if ((threadIdx.x & 63) == 0) h[j] = r;
+    }
+    __syncthreads();
+}
+
+// a b + c d with each product rounded (what the host computes; fma would not be)
+__device__ __forceinline__ double two_products(double a, double b, double c, double d) {
+#pragma clang fp contract(off)
+    const double x = a * b, y = c * d;
+    return x + y;
+}
+
+// w -= Vs h with h from part_in, on block b's chunk; then the partials of Vd . w.
+// With rot (the Givens rotations c[0..ks-1), s[0..ks-1) of a deflation space), h
+// is turned into e = Q^T h and the subtracted vector is V (Q e): what the host
+// did between two copies, unfused multiplies and adds as there.
+// Block 0 writes h (with rot: e) to hout, host memory.
+__global__ __launch_bounds__(256) void k_cgs_step(const double* __restrict__ Vs, int64_t lds, int ks,
+                                                  const double* __restrict__ part_in, const double* __restrict__ rot,
+                                                  double* __restrict__ hout, const double* __restrict__ Vd,
+                                                  int64_t ldd, int kd, double* w, int64_t len,
+                                                  double* __restrict__ part_out) {
+    __shared__ double h[kFuseCols], sc[2 * kFuseCols], sh[kDotCols][4];
+    const int tid = threadIdx.x;
+    if (rot)
+        for (int j = tid; j < 2 * (ks - 1); j += 256) sc[j] = rot[j];
+    reduce_columns(part_in, ks, h);
+    if (rot) {
+        const int kr = ks - 1;
+        if (tid == 0) {
+            const double *c = sc, *sn = sc + kr;
+            for (int j = 0; j < kr; ++j) {
+                const double t = two_products(c[j], h[j], sn[j], h[j + 1]);
+                h[j + 1] = two_products(-sn[j], h[j], c[j], h[j + 1]);
+                h[j] = t;
+            }
+            if (blockIdx.x == 0)
+                for (int j = 0; j < kr; ++j) hout[j] = h[j];
+            h[kr] = 0.0;
+            for (int j = kr - 1; j >= 0; --j) {
+                const double t = two_products(c[j], h[j], -sn[j], h[j + 1]);
+                h[j + 1] = two_products(sn[j], h[j], c[j], h[j + 1]);
+                h[j] = t;
+            }
+        }
+        __syncthreads();
+    } else if (blockIdx.x == 0 && tid < ks) {
+        hout[tid] = h[tid];
+    }
+    const int64_t chunk = (len + gridDim.x - 1) / gridDim.x;
+    const int64_t lo = (int64_t)blockIdx.x * chunk;
+    const int64_t hi = lo + chunk < len ? lo + chunk : len;
+    for (int64_t i = lo + tid; i < hi; i += 256) {
+        double s = 0.0;
+        for (int j = 0; j < ks; ++j) s = fma(h[j], Vs[(int64_t)j * lds + i], s);
+        w[i] -= s;
+    }
+    for (int j0 = 0; j0 < kd; j0 += kDotCols) {
+        const int nc = kd - j0 < kDotCols ? kd - j0 : kDotCols;
+        double acc[kDotCols];
+#pragma unroll
+        for (int c = 0; c < kDotCols; ++c) acc[c] = 0.0;
+        for (int64_t i = lo + tid; i < hi; i += 256) {
+            const double wi = w[i];
+#pragma unroll
+            for (int c = 0; c < kDotCols; ++c)
+                if (c < nc) acc[c] = fma(Vd[(int64_t)(j0 + c) * ldd + i], wi, acc[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < kDotCols; ++c) {
+            const double r = wave_sum(acc[c]);
+            if ((tid & 63) == 0) sh[c][tid >> 6] = r;
+        }
+        __syncthreads();
+        if (tid < nc)
+            part_out[(int64_t)(j0 + tid) * gridDim.x + blockIdx.x] = (sh[tid][0] + sh[tid][1]) + (sh[tid][2] + sh[tid][3]);
+        __syncthreads();
+    }
+}
+
+// w -= V h with h from part_in; then the partials of w . w
+__global__ __launch_bounds__(256) void k_cgs_last(const double* __restrict__ V, int64_t ld, int k,
+                                                  const double* __restrict__ part_in, double* __restrict__ hout,
+                                                  double* __restrict__ w, int64_t len, double* __restrict__ part_out) {
+    __shared__ double h[kFuseCols], sh[4];
+    reduce_columns(part_in, k, h);
+    if (blockIdx.x == 0 && (int)threadIdx.x < k) hout[threadIdx.x] = h[threadIdx.x];
+    double q = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < len; i += (int64_t)gridDim.x * 256) {
+        double s = 0.0;
+        for (int j = 0; j < k; ++j) s = fma(h[j], V[(int64_t)j * ld + i], s);
+        const double wi = w[i] - s;
+        w[i] = wi;
+        q = fma(wi, wi, q);
+    }
+    const double r = block_sum(q, sh);
+    if (threadIdx.x == 0) part_out[blockIdx.x] = r;
+}
+
+// out = w / ||w|| (nothing when w = 0); the squared norm to hout
+__global__ __launch_bounds__(256) void k_cgs_scale(const double* __restrict__ part_in, double* __restrict__ hout,
+                                                   const double* __restrict__ w, double* __restrict__ out, int64_t len) {
+    __shared__ double sh;
+    if (threadIdx.x < 64) {
+        const double r = reduce_blocks(part_in);
+        if (threadIdx.x == 0) {
+            sh = r;
+            if (blockIdx.x == 0) hout[0] = r;
+        }
+    }
+    __syncthreads();
+    if (!(sh > 0.0)) return;
+    const double a = 1.0 / sqrt(sh);
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < len; i += (int64_t)gridDim.x * 256) out[i] = a * w[i];
 }
 
 __global__ void k_multi_axpy(const double* __restrict__ V, int64_t ld, int k, const double* __restrict__ h,
@@ -220,7 +363,7 @@ inline unsigned nblk(int64_t len) { return (unsigned)((len + 255) / 256); }
 void dev_dot(const Plan& P, const double* a, const double* b, int64_t len, double* out, hipStream_t s) {
     hipLaunchKernelGGL(k_dot_partial, dim3(kRedBlocks), dim3(256), 0, s, a, b, len, P.red);
     SDBIE_LAUNCHED();
-    hipLaunchKernelGGL(k_reduce_cols, dim3(1), dim3(256), 0, s, (const double*)P.red, kRedBlocks, 1, out);
+    hipLaunchKernelGGL(k_reduce_cols, dim3(1), dim3(256), 0, s, (const double*)P.red, kRedBlocks, out);
     SDBIE_LAUNCHED();
 }
 
@@ -229,8 +372,53 @@ void dev_multidot(const Plan& P, const double* V, int64_t ld, int k, const doubl
     hipLaunchKernelGGL(k_multidot_partial, dim3(kRedBlocks, (unsigned)((k + kDotCols - 1) / kDotCols)), dim3(256), 0,
                        s, V, ld, k, w, len, P.red);
     SDBIE_LAUNCHED();
-    hipLaunchKernelGGL(k_reduce_cols, dim3(k), dim3(256), 0, s, (const double*)P.red, kRedBlocks, k, out);
+    hipLaunchKernelGGL(k_reduce_cols, dim3(k), dim3(256), 0, s, (const double*)P.red, kRedBlocks, out);
     SDBIE_LAUNCHED();
+}
+
+void dev_cgs2(const Plan& P, const double* Vr, int kr, const double* rot, const double* V, int k, double* w,
+              double* next, int64_t len, hipStream_t s) {
+    double* host = P.host_pinned;
+    double* pa = P.red;           // two sets of block partials in turn
+    double* pb = P.partial;       // free between the pair passes
+    static_assert((size_t)(kFuseCols + 1) * kRedBlocks * sizeof(double) <= kMinPartial, "block partials in `partial`");
+    const dim3 grid(kRedBlocks), th(256);
+    const int k0 = kr > 0 ? kr + 1 : k;
+    hipLaunchKernelGGL(k_multidot_partial, dim3(kRedBlocks, (unsigned)((k0 + kDotCols - 1) / kDotCols)), th, 0, s,
+                       kr > 0 ? Vr : V, len, k0, (const double*)w, len, pa);
+    SDBIE_LAUNCHED();
+    if (kr > 0) {
+        hipLaunchKernelGGL(k_cgs_step, grid, th, 0, s, Vr, len, kr + 1, (const double*)pa, rot, host + kHostE, V, len, k,
+                           w, len, pb);
+        SDBIE_LAUNCHED();
+        std::swap(pa, pb);
+    }
+    hipLaunchKernelGGL(k_cgs_step, grid, th, 0, s, V, len, k, (const double*)pa, (const double*)nullptr, host + kHostH1,
+                       V, len, k, w, len, pb);
+    SDBIE_LAUNCHED();
+    std::swap(pa, pb);
+    hipLaunchKernelGGL(k_cgs_last, grid, th, 0, s, V, len, k, (const double*)pa, host + kHostH2, w, len, pb);
+    SDBIE_LAUNCHED();
+    const unsigned sb = nblk(len) < kRedBlocks ? nblk(len) : kRedBlocks;
+    hipLaunchKernelGGL(k_cgs_scale, dim3(sb), th, 0, s, (const double*)pb, host + kHostNorm, (const double*)w, next, len);
+    SDBIE_LAUNCHED();
+}
+
+double dev_dot_host(const Plan& P, const double* a, const double* b, int64_t len, hipStream_t s) {
+    double* part = P.host_pinned + kHostDot;
+    hipLaunchKernelGGL(k_dot_partial, dim3(kRedBlocks), dim3(256), 0, s, a, b, len, part);
+    SDBIE_LAUNCHED();
+    SDBIE_HIP(hipStreamSynchronize(s));
+    // k_reduce_cols' order
+    double r[4];
+    for (int v = 0; v < 4; ++v) {
+        double t[64];
+        for (int l = 0; l < 64; ++l) t[l] = part[64 * v + l] + part[64 * v + l + 256];
+        for (int o = 32; o > 0; o >>= 1)
+            for (int l = 0; l < o; ++l) t[l] += t[l + o];
+        r[v] = t[0];
+    }
+    return (r[0] + r[1]) + (r[2] + r[3]);
 }
 
 void dev_multi_axpy_sub(const double* V, int64_t ld, int k, const double* h, double* w, int64_t len,
@@ -319,13 +507,6 @@ void dev_adj_rhs(const Plan& P, const double e[3], double beta, double* gp, doub
     hipLaunchKernelGGL(k_adj_rhs, dim3(nblk(P.n)), dim3(256), 0, s, P.n, (const double*)P.nrm, (const double*)P.w, e[0],
                        e[1], e[2], beta, gp, gu);
     SDBIE_LAUNCHED();
-}
-
-double host_read_scalar(const double* d, hipStream_t s) {
-    double v = 0.0;
-    SDBIE_HIP(hipMemcpyAsync(&v, d, sizeof(double), hipMemcpyDeviceToHost, s));
-    SDBIE_HIP(hipStreamSynchronize(s));
-    return v;
 }
 
 }  // namespace sdbie

@@ -44,10 +44,6 @@ int64_t sym_max_items(int64_t nt, int k) {
 }
 int64_t sym_max_slots(int64_t nt) { return (sym_max_pairs(nt) + nt) / kSymChunk + 2 * nt; }
 
-// partial slots of a plan at least: the forward and reverse slots of 16 parts
-// to a tile pair up to 11 tiles (n = 2816)
-constexpr size_t kMinPartial = (size_t)12 << 20;
-
 // the node data, staging and pair-pass scratch every plan holds: nsplit
 // source splits with up to `comps` components per partial slot, m the
 // longest GMRES restart the reduction buffer serves, min_partial the least
@@ -73,7 +69,7 @@ void layout_common(Layout& L, Take& take, int64_t n, int m, int nsplit, int comp
     L.partial = take(std::max((size_t)2 * nsplit * comps * n * d, min_partial));
     L.rec = take((size_t)npad * kRecBytes);
     L.red = take((size_t)kRedBlocks * (m + 2) * d);
-    L.scal = take((size_t)(kScalGmres + 6 * (m + 2) + 64 > 1024 ? kScalGmres + 6 * (m + 2) + 64 : 1024) * d);
+    L.scal = take(std::max((size_t)1024, (size_t)kScalGmres + 6 * (m + 2) + 2 * kFuseCols) * d);
 }
 
 Layout layout(int64_t n, int m) {
@@ -279,7 +275,8 @@ void apply_laplace_layer(Plan& P, sdbie_layer layer, const double* dens, double*
         case SDBIE_DL_SUB: d.dl = true; d.sub = true; d.c_dl = 1.0 / (4.0 * kPi); d.dl_dens = in; break;
         default: fail(SDBIE_ERR_ARG, "bad layer");
     }
-    dev_gather(P, dens, in, 1, st);
+    d.gather_src = dens;
+    d.gather_dst = in;
     d.mixed = prec == SDBIE_MIXED;
     d.out = out;
     d.scatter = true;
@@ -303,7 +300,8 @@ void apply_stokes_layer(Plan& P, double mu, sdbie_layer layer, const double* den
             break;
         default: fail(SDBIE_ERR_ARG, "bad layer");
     }
-    dev_gather(P, dens, in, 3, st);
+    d.gather_src = dens;
+    d.gather_dst = in;
     d.mixed = prec == SDBIE_MIXED;
     d.out = out;
     d.scatter = true;

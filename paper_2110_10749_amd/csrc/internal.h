@@ -68,6 +68,18 @@ constexpr size_t kSymSlotBytes = (size_t)3 * kTile * sizeof(double);
 constexpr double kMaxCoord = 1e15;
 constexpr double kMinDelta = 1e-15;
 constexpr int kRedBlocks = 512;  // blocks of the deterministic reductions
+// columns up to which a Krylov step runs the fused Gram-Schmidt kernels; past
+// that the redundant reductions of every block would take longer than the
+// launches they save
+constexpr int kFuseCols = 64;
+// host memory of a plan's solves (doubles): what the fused kernels write for the host
+enum : int {
+    kHostE = 0, kHostH1 = kFuseCols, kHostH2 = 2 * kFuseCols, kHostNorm = 3 * kFuseCols,
+    kHostDot = 3 * kFuseCols + 8, kHostDoubles = kHostDot + kRedBlocks,
+};
+// partial slots of a plan at least: the forward and reverse slots of 16 parts
+// to a tile pair up to 11 tiles (n = 2816)
+constexpr size_t kMinPartial = (size_t)12 << 20;
 
 // Pair-sum passes --------------------------------------------------------------
 // Laplace pass:  out_i = base_i + c_dl * sum_j w_j (q_j - sub*q_i)(D.n_j) k2
@@ -85,8 +97,16 @@ struct PassDesc {
     double slip_beta = 0.0;           // Stokes only
     const double* base = nullptr;     // sorted, [n] or [3][n], added to the result (nullable)
     double base_scale = 1.0;
-    const double* comp = nullptr;     // device scalar (nullable): completion coefficient
+    // completion (nullable): comp_scale (comp_a . comp_b) added to every node
+    // (Laplace) or times its normal (Stokes).  The dot product's block partials
+    // are taken by the packing kernel and summed by the epilogue.
+    const double* comp_a = nullptr;
+    const double* comp_b = nullptr;
     double comp_scale = 0.0;
+    // the density in the caller's order (nullable): gathered into dl_dens /
+    // sl_dens (gather_dst, all components) by the packing kernel
+    const double* gather_src = nullptr;
+    double* gather_dst = nullptr;
     const double* add_const = nullptr; // host double[3] added to every node (nullable)
     double* out = nullptr;            // sorted, or original order when scatter
     bool scatter = false;             // write out[perm[i]] instead of out[i]
@@ -171,7 +191,7 @@ struct Plan {
     double* image_out = nullptr;  // local solutions (p, u) and right-hand sides (b_D, b_S) of each outer
                                   // basis vector [(max_restart+1)][8n]
     double* basis_rc = nullptr;   // recycled inner basis (deflation space) [(max_restart+1)][3n]
-    double* host_pinned = nullptr;  // not used (host buffers are plain)
+    double* host_pinned = nullptr;  // [kHostDoubles] host memory the kernels write to (first solve on)
     // (target, source) pairs of real nodes in the near tile pairs (double, float masks)
     double near_pairs64 = 0.0, near_pairs32 = 0.0;
     // target-source symmetric passes (for the pass kinds whose SDBIE_SYM_* bit is
@@ -186,6 +206,12 @@ struct Plan {
     // bookkeeping for info
     int64_t applies_fp64 = 0, applies_mixed = 0;
     double pairs = 0.0;
+    Plan() = default;
+    Plan(const Plan&) = delete;
+    Plan& operator=(const Plan&) = delete;
+    ~Plan() {
+        if (host_pinned) (void)hipHostFree(host_pinned);
+    }
     double* vec(int k) const { return vecs + (size_t)k * 3 * n; }
 };
 
@@ -237,6 +263,15 @@ void dev_dot(const Plan& P, const double* a, const double* b, int64_t len, doubl
 // dots of w against k columns of V (column stride ld) -> out[0..k-1]
 void dev_multidot(const Plan& P, const double* V, int64_t ld, int k, const double* w, int64_t len,
                   double* out, hipStream_t s);
+// One Krylov step: w is orthogonalised against k columns V twice (CGS2; leading
+// dimension len) and next = w / ||w||; with kr > 0 first against the deflation
+// space Vr (kr + 1 columns, rotations rot on the device).  k, kr + 1 <= kFuseCols.
+// After a stream synchronisation host_pinned holds the coefficients (kHostE,
+// kHostH1, kHostH2) and the squared norm (kHostNorm).
+void dev_cgs2(const Plan& P, const double* Vr, int kr, const double* rot, const double* V, int k, double* w,
+              double* next, int64_t len, hipStream_t s);
+// dot product on the host (synchronises the stream), summed in dev_dot's order
+double dev_dot_host(const Plan& P, const double* a, const double* b, int64_t len, hipStream_t s);
 // w -= sum_j h[j] V_j  (h on device)
 void dev_multi_axpy_sub(const double* V, int64_t ld, int k, const double* h, double* w, int64_t len,
                         hipStream_t s);
@@ -268,7 +303,6 @@ void dev_axpy_w(const Plan& P, double* x, const double* d, double scale, hipStre
 void dev_adj_rhs(const Plan& P, const double e[3], double beta, double* gp, double* gu, hipStream_t s);
 
 // host-side helpers
-double host_read_scalar(const double* d, hipStream_t s);
 // eigenvalues of an upper Hessenberg matrix (n x n, row-major, overwritten); false if the QR iteration stalls
 bool hessenberg_eigenvalues(int n, double* A, double* wr, double* wi);
 

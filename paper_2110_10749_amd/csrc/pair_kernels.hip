@@ -200,6 +200,13 @@ struct KArgs {
     double* partial;    // [2 nsplit][C][n]
     void* rec;          // source records of the pass [npad][Op::R] (T)
     int unit_w;         // sources enter with weight 1 (transposed single layers)
+    const double *comp_a, *comp_b;  // completion: block partials of comp_a . comp_b go to comp_part
+    int64_t comp_len;
+    double* comp_part;  // [kRedBlocks]
+    const double* gather_src;  // density in the caller's order, gathered into gather_dst ([gather_c][n])
+    double* gather_dst;
+    const int32_t* perm;
+    int gather_c;
     const double* dl_tgt;  // target density of the subtracted double layer (nullable: dl_dens)
     // position-gradient pass
     const double *g_p, *g_v, *g_u, *g_f, *g_l1, *g_l2;
@@ -780,11 +787,40 @@ struct GradOp {
 
 static_assert(GradOp<false>::R * sizeof(double) <= kRecBytes, "record larger than its workspace slot");
 
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// sum of a 256-thread block (all lanes), the waves' sums added as (0 + 1) + (2 + 3)
+__device__ __forceinline__ double block_sum(double v) {
+    __shared__ double sh[4];
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
 // One thread per source (padding included): write the pass's source records.
+// The same launch gathers a density given in the caller's order and takes the
+// block partials of the completion's dot product (the first kRedBlocks blocks,
+// dev_dot's order), which the epilogue adds up: three launches less per product,
+// 12 us of the 36 us that a Stokes double layer takes at n = 2650.
 template <class Op, typename T>
 __global__ __launch_bounds__(256) void pack_sources(KArgs a) {
     const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (a.comp_a && blockIdx.x < kRedBlocks) {
+        double s = 0.0;
+        for (int64_t i = j; i < a.comp_len; i += (int64_t)kRedBlocks * 256) s += a.comp_a[i] * a.comp_b[i];
+        s = block_sum(s);
+        if (threadIdx.x == 0) a.comp_part[blockIdx.x] = s;
+    }
     if (j >= a.npad) return;
+    if (a.gather_src && j < a.n) {
+        const int64_t o = a.perm[j];
+        for (int c = 0; c < a.gather_c; ++c) a.gather_dst[c * a.n + j] = a.gather_src[c * a.n + o];
+    }
     Record<T, Op::R> rec;
     Op::pack(rec.v, j, a);
     reinterpret_cast<Record<T, Op::R>*>(a.rec)[j] = rec;
@@ -1065,15 +1101,20 @@ __device__ __forceinline__ void epi_combine(double (&v)[C], int g, int jj) {
     }
 }
 
+// the completion coefficient: comp_scale times the sum of its block partials
+__device__ __forceinline__ double epi_completion(const double* __restrict__ comp, double comp_scale) {
+    static_assert(kEpiThreads == 256 && kRedBlocks == 512, "two partials per thread");
+    if (!comp) return 0.0;
+    return comp_scale * block_sum(comp[threadIdx.x] + comp[threadIdx.x + 256]);
+}
+
 // the terms a pass adds to its pair sums v (target weight, base vector,
 // completion, constant) and the store in the caller's node order
 template <int C>
 __device__ __forceinline__ void epi_finish(int64_t n, int64_t i, const double (&v)[C],
                                            const double* __restrict__ tw, const double* base, double base_scale,
-                                           const double* __restrict__ comp, double comp_scale,
-                                           const double* __restrict__ nrm, double add0, double add1, double add2,
-                                           double* out, const int32_t* __restrict__ perm) {
-    const double cs = comp ? comp_scale * comp[0] : 0.0;
+                                           bool comp, double cs, const double* __restrict__ nrm, double add0,
+                                           double add1, double add2, double* out, const int32_t* __restrict__ perm) {
     const int64_t o = perm ? (int64_t)perm[i] : i;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
@@ -1095,6 +1136,7 @@ __global__ __launch_bounds__(kEpiThreads) void epilogue(int64_t n, int nslots, c
                                                         const int32_t* __restrict__ perm) {
     const int g = threadIdx.x / kEpiTargets, jj = threadIdx.x % kEpiTargets;
     const int64_t i = (int64_t)blockIdx.x * kEpiTargets + jj;
+    const double cs = epi_completion(comp, comp_scale);
     double v[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) v[c] = 0.0;
@@ -1103,7 +1145,7 @@ __global__ __launch_bounds__(kEpiThreads) void epilogue(int64_t n, int nslots, c
 #pragma unroll
             for (int c = 0; c < C; ++c) v[c] += partial[((int64_t)sl * C + c) * n + i];
     epi_combine<C>(v, g, jj);
-    if (g == 0 && i < n) epi_finish<C>(n, i, v, tw, base, base_scale, comp, comp_scale, nrm, add0, add1, add2, out, perm);
+    if (g == 0 && i < n) epi_finish<C>(n, i, v, tw, base, base_scale, comp != nullptr, cs, nrm, add0, add1, add2, out, perm);
 }
 
 // --------------------------------------------------------------------------
@@ -1578,6 +1620,7 @@ __global__ __launch_bounds__(kEpiThreads) void sym_epilogue(
     static_assert(kTile % kEpiTargets == 0, "a block's targets lie in one tile");
     const int g = threadIdx.x / kEpiTargets, jj = threadIdx.x % kEpiTargets;
     const int64_t i = (int64_t)blockIdx.x * kEpiTargets + jj;
+    const double cs = epi_completion(comp, comp_scale);
     double v[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) v[c] = 0.0;
@@ -1597,10 +1640,10 @@ __global__ __launch_bounds__(kEpiThreads) void sym_epilogue(
             for (int c = 0; c < C; ++c) v[c] += partial[((int64_t)(nsplit + sl) * C + c) * n + i];
     }
     epi_combine<C>(v, g, jj);
-    if (g == 0 && i < n) epi_finish<C>(n, i, v, tw, base, base_scale, comp, comp_scale, nrm, add0, add1, add2, out, perm);
+    if (g == 0 && i < n) epi_finish<C>(n, i, v, tw, base, base_scale, comp != nullptr, cs, nrm, add0, add1, add2, out, perm);
 }
 
-KArgs make_args(const Plan& P, const PassDesc& d, int nsplit, double cut) {
+KArgs make_args(const Plan& P, const PassDesc& d, int nsplit, double cut, int comps) {
     KArgs a;
     a.n = P.n;
     a.npad = P.npad;
@@ -1626,6 +1669,14 @@ KArgs make_args(const Plan& P, const PassDesc& d, int nsplit, double cut) {
     a.rec = P.rec;
     a.unit_w = d.unit_src_weight ? 1 : 0;
     a.dl_tgt = d.dl_target;
+    a.comp_a = d.comp_a;
+    a.comp_b = d.comp_b;
+    a.comp_len = comps * P.n;
+    a.comp_part = P.red;
+    a.gather_src = d.gather_src;
+    a.gather_dst = d.gather_dst;
+    a.perm = P.perm;
+    a.gather_c = comps;
     a.g_p = a.g_v = a.g_u = a.g_f = a.g_l1 = a.g_l2 = nullptr;
     a.g_mu = a.g_K = 1.0;
     return a;
@@ -1653,7 +1704,9 @@ bool launch_pair_kernels(const Plan& P, const KArgs& a, hipStream_t st, int fami
     const double near = mixed ? P.near_pairs32 : P.near_pairs64;
     {
         ProfScope prof(prof_variant(family, mixed, code, 2), 0.0, st);
-        hipLaunchKernelGGL((pack_sources<Op, T>), dim3((unsigned)(a.npad / 256)), dim3(256), 0, st, a);
+        const int64_t pb = a.npad / 256;
+        hipLaunchKernelGGL((pack_sources<Op, T>), dim3((unsigned)(a.comp_a && pb < kRedBlocks ? kRedBlocks : pb)),
+                           dim3(256), 0, st, a);
         SDBIE_LAUNCHED();
     }
     using Sym = typename SymOf<Op>::type;
@@ -1719,6 +1772,7 @@ void launch_epilogue(const Plan& P, const PassDesc& d, int S, bool sym, hipStrea
     const double* add = d.add_const;
     const double a0 = add ? add[0] : 0.0, a1 = add && C > 1 ? add[1] : 0.0, a2 = add && C > 2 ? add[2] : 0.0;
     const double* tw = d.target_weight ? (const double*)P.w : nullptr;
+    const double* comp = d.comp_a ? (const double*)P.red : nullptr;
     const int32_t* perm = d.scatter ? (const int32_t*)P.perm : nullptr;
     if (sym) {
         const SymSet& Y = sym_set(P, d.mixed);
@@ -1726,16 +1780,16 @@ void launch_epilogue(const Plan& P, const PassDesc& d, int S, bool sym, hipStrea
         if (d.mixed)
             hipLaunchKernelGGL((sym_epilogue<C, float>), dim3(eb), et, 0, st, P.n, (const int32_t*)Y.fwd_start,
                                (const double*)Y.fwd, (const int32_t*)Y.rev_start, (const float*)Y.rev, nsplit,
-                               (const double*)P.partial, tw, d.base, d.base_scale, d.comp, d.comp_scale,
+                               (const double*)P.partial, tw, d.base, d.base_scale, comp, d.comp_scale,
                                (const double*)P.nrm, a0, a1, a2, d.out, perm);
         else
             hipLaunchKernelGGL((sym_epilogue<C, double>), dim3(eb), et, 0, st, P.n, (const int32_t*)Y.fwd_start,
                                (const double*)Y.fwd, (const int32_t*)Y.rev_start, (const double*)Y.rev, nsplit,
-                               (const double*)P.partial, tw, d.base, d.base_scale, d.comp, d.comp_scale,
+                               (const double*)P.partial, tw, d.base, d.base_scale, comp, d.comp_scale,
                                (const double*)P.nrm, a0, a1, a2, d.out, perm);
     } else {
         hipLaunchKernelGGL((epilogue<C>), dim3(eb), et, 0, st, P.n, 2 * S, (const double*)P.partial, tw,
-                           d.base, d.base_scale, d.comp, d.comp_scale, (const double*)P.nrm, a0, a1, a2, d.out,
+                           d.base, d.base_scale, comp, d.comp_scale, (const double*)P.nrm, a0, a1, a2, d.out,
                            perm);
     }
     SDBIE_LAUNCHED();
@@ -1774,7 +1828,7 @@ void launch_laplace_pass(const Plan& P, const PassDesc& d, hipStream_t st) {
     trace("laplace", d);
     const int S = P.nsplit;
     const double cut = d.mixed ? (double)SDBIE_RHO_CUT_STOKES_F32 : SDBIE_RHO_CUT_STOKES_F64;
-    const KArgs a = make_args(P, d, S, cut);
+    const KArgs a = make_args(P, d, S, cut, 1);
     const int code = (d.dl ? 1 : 0) | (d.sl ? 2 : 0) | (d.sub ? 4 : 0);
     bool sym = false;
     if (d.target_normal) {
@@ -1815,13 +1869,13 @@ void launch_stokes_pass(const Plan& P, const PassDesc& d, hipStream_t st) {
     trace("stokes", d);
     const int S = P.nsplit;
     const double cut = d.mixed ? (double)SDBIE_RHO_CUT_STOKES_F32 : SDBIE_RHO_CUT_STOKES_F64;
-    const KArgs a = make_args(P, d, S, cut);
+    const KArgs a = make_args(P, d, S, cut, 3);
     const bool slip = d.sl && d.slip_beta != 0.0 && d.sl_dens == nullptr;
     const int code = (d.dl ? 1 : 0) | (d.sl ? 2 : 0) | (d.sub ? 4 : 0) | (slip ? 8 : 0);
     if (d.target_normal && d.sl) {
         // transposed stresslet and Stokeslet of one density: six outputs
         // [out | out + 3n] (the partial buffer holds six components per slot)
-        if (!d.dl || d.sub || d.sl_dens != d.dl_dens || !(d.c_dl != 0.0) || d.base || d.comp || d.add_const)
+        if (!d.dl || d.sub || d.sl_dens != d.dl_dens || !(d.c_dl != 0.0) || d.base || d.comp_a || d.add_const)
             throw Error(SDBIE_ERR_ARG, "transposed Stokes pass: double and single layer of one density");
         if (d.mixed) launch_pair_kernels<StokesTNSLOp<float>, float>(P, a, st, 1, 16 | 2 | 1, true);
         else launch_pair_kernels<StokesTNSLOp<double>, double>(P, a, st, 1, 16 | 2 | 1, false);
@@ -1874,7 +1928,7 @@ void launch_stokes_pass(const Plan& P, const PassDesc& d, hipStream_t st) {
 void launch_grad_pass(const Plan& P, const GradDesc& g, hipStream_t st) {
     const int S = P.nsplit;
     PassDesc d;
-    KArgs a = make_args(P, d, S, SDBIE_RHO_CUT_STOKES_F64);
+    KArgs a = make_args(P, d, S, SDBIE_RHO_CUT_STOKES_F64, 3);
     a.g_p = g.p;
     a.g_v = g.v;
     a.g_u = g.u;

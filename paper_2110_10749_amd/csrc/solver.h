@@ -46,13 +46,14 @@ static_assert(kVecSpare < kNumVec, "work-vector slots exceed the workspace");
 
 // device scalar slots of Plan::scal
 enum : int {
-    kScalCompD = 0,
+    kScalCompD = 0,  // completion coefficients of the transposed operators
     kScalCompS = 1,
     kScalMean = 2,
     kScalNorm = 3,
     kScalDrag = 4,   // 3 slots
     kScalStage = 16, // staging: finite flag (16), bounding box (18..23), weight sum (24), near-pair counts (26, 27), list counts (28 .. 31)
-    kScalGmres = 32, // inner and outer Hessenberg columns / coefficients
+    kScalGmres = 32, // inner and outer Hessenberg columns / coefficients, 6 (m + 2), then the rotations of
+                     // the deflation space (2 kFuseCols)
 };
 
 struct GmresWS {

@@ -37,15 +37,13 @@ int debug_level() {
 // small helpers
 // ------------------------------------------------------------------------------
 double Ctx::norm(const double* a, int64_t len) {
-    dev_dot(P, a, a, len, P.scal + kScalNorm, s);
-    const double v = host_read_scalar(P.scal + kScalNorm, s);
+    const double v = dev_dot_host(P, a, a, len, s);
     if (!std::isfinite(v)) throw Error(SDBIE_ERR_NONFINITE, "non-finite iterate");
     return std::sqrt(v);
 }
 
 double Ctx::dot(const double* a, const double* b, int64_t len) {
-    dev_dot(P, a, b, len, P.scal + kScalNorm, s);
-    return host_read_scalar(P.scal + kScalNorm, s);
+    return dev_dot_host(P, a, b, len, s);
 }
 
 void Ctx::copy(const double* a, double* b, int64_t len) {
@@ -56,13 +54,13 @@ void Ctx::copy(const double* a, double* b, int64_t len) {
 // operators
 // ------------------------------------------------------------------------------
 void Ctx::op_darcy(const double* p, double* out, bool mixed) {
-    dev_dot(P, P.w, p, P.n, P.scal + kScalCompD, s);
     PassDesc d;
+    d.comp_a = P.w;
+    d.comp_b = p;
     d.dl = true;
     d.sub = true;
     d.c_dl = 1.0 / (4.0 * kPi);
     d.dl_dens = p;
-    d.comp = P.scal + kScalCompD;
     d.comp_scale = 1.0 / P.area;
     d.out = out;
     d.mixed = mixed;
@@ -70,8 +68,9 @@ void Ctx::op_darcy(const double* p, double* out, bool mixed) {
 }
 
 void Ctx::op_stokes(const double* u, double* out, double mu, double beta, bool mixed) {
-    dev_dot(P, P.wn, u, 3 * P.n, P.scal + kScalCompS, s);
     PassDesc d;
+    d.comp_a = P.wn;
+    d.comp_b = u;
     d.dl = true;
     d.sub = true;
     d.c_dl = -3.0 / (4.0 * kPi);
@@ -84,7 +83,6 @@ void Ctx::op_stokes(const double* u, double* out, double mu, double beta, bool m
         d.slip_beta = beta;
         d.sl_dens = nullptr;
     }
-    d.comp = P.scal + kScalCompS;
     d.comp_scale = 1.0 / P.area;
     d.out = out;
     d.mixed = mixed;
@@ -155,10 +153,18 @@ GmresOut Ctx::gmres(const GmresWS& ws, const GmresOp& op, const double* b, doubl
     Recycle* rc_fill = rc_cur && rc_cur->k == 0 ? rc_cur : nullptr;
     const int kr = rc_use ? rc_use->k : 0;
     std::vector<double> rh(kr + 1), rz(kr), Ecol((size_t)kr * m), G(kr + 1), SG(kr);
+    // the Krylov steps run the fused kernels up to kFuseCols columns
+    const bool fuse_rc = kr + 1 <= kFuseCols;
+    const double* host = P.host_pinned;
     // device coefficients of the two corrections (distinct regions of a work vector;
-    // every reuse is preceded by a stream synchronisation)
+    // every reuse is preceded by a stream synchronisation) and the space's rotations
     double* dG = P.vec(kVecRecycle);
     double* dSG = dG + kr + 1;
+    double* drot = P.scal + kScalGmres + 6 * (P.max_restart + 2);
+    if (rc_use && fuse_rc) {
+        SDBIE_HIP(hipMemcpyAsync(drot, rc_use->cs.data(), kr * sizeof(double), hipMemcpyHostToDevice, s));
+        SDBIE_HIP(hipMemcpyAsync(drot + kr, rc_use->sn.data(), kr * sizeof(double), hipMemcpyHostToDevice, s));
+    }
     // e = C^T w = Q^T V^T w (kr values in rh); then w -= C e = V (Q e)
     auto project_off = [&](double* wv) {
         dev_multidot(P, rc_use->V, L, kr + 1, wv, L, ws.dcol, s);
@@ -195,7 +201,8 @@ GmresOut Ctx::gmres(const GmresWS& ws, const GmresOp& op, const double* b, doubl
         add_U(rh.data(), 1.0, x);
     };
     if (rc_use) deflate_residual();
-    double beta = norm(r, L);
+    // r is b itself without an initial guess
+    double beta = x_nonzero || resfn || rc_use ? norm(r, L) : bnorm;
     res.relres = beta / bnorm;
     const double rel0 = res.relres;
     int n64 = 0;  // products with double pairs (diagnostics)
@@ -219,26 +226,36 @@ GmresOut Ctx::gmres(const GmresWS& ws, const GmresOp& op, const double* b, doubl
             op(vk, w, m32, res.relres);
             krylov_index = -1;
             res.iters++;
-            if (rc_use) {
-                project_off(w);
-                std::copy(rh.begin(), rh.begin() + kr, Ecol.begin() + (size_t)k * kr);
+            if (k + 1 <= kFuseCols && fuse_rc) {
+                dev_cgs2(P, rc_use ? rc_use->V : nullptr, kr, drot, ws.V, k + 1, w, ws.V + (int64_t)(k + 1) * L, L, s);
+                SDBIE_HIP(hipStreamSynchronize(s));
+                if (rc_use) std::copy(host + kHostE, host + kHostE + kr, Ecol.begin() + (size_t)k * kr);
+                std::copy(host + kHostH1, host + kHostH1 + k + 1, col.begin());
+                std::copy(host + kHostH2, host + kHostH2 + k + 1, col.begin() + k + 1);
+                col[2 * (k + 1)] = host[kHostNorm];
+            } else {
+                if (rc_use) {
+                    project_off(w);
+                    std::copy(rh.begin(), rh.begin() + kr, Ecol.begin() + (size_t)k * kr);
+                }
+                double* h1 = ws.dcol;
+                double* h2 = ws.dcol + (k + 1);
+                double* hn = ws.dcol + 2 * (k + 1);
+                dev_multidot(P, ws.V, L, k + 1, w, L, h1, s);
+                dev_multi_axpy_sub(ws.V, L, k + 1, h1, w, L, s);
+                dev_multidot(P, ws.V, L, k + 1, w, L, h2, s);
+                dev_multi_axpy_sub(ws.V, L, k + 1, h2, w, L, s);
+                dev_dot(P, w, w, L, hn, s);
+                SDBIE_HIP(hipMemcpyAsync(col.data(), ws.dcol, (2 * (k + 1) + 1) * sizeof(double),
+                                         hipMemcpyDeviceToHost, s));
+                SDBIE_HIP(hipStreamSynchronize(s));
+                const double nw = std::sqrt(col[2 * (k + 1)]);
+                if (nw > 0.0 && std::isfinite(nw)) dev_scale(1.0 / nw, w, ws.V + (int64_t)(k + 1) * L, L, s);
             }
-            double* h1 = ws.dcol;
-            double* h2 = ws.dcol + (k + 1);
-            double* hn = ws.dcol + 2 * (k + 1);
-            dev_multidot(P, ws.V, L, k + 1, w, L, h1, s);
-            dev_multi_axpy_sub(ws.V, L, k + 1, h1, w, L, s);
-            dev_multidot(P, ws.V, L, k + 1, w, L, h2, s);
-            dev_multi_axpy_sub(ws.V, L, k + 1, h2, w, L, s);
-            dev_dot(P, w, w, L, hn, s);
-            SDBIE_HIP(hipMemcpyAsync(col.data(), ws.dcol, (2 * (k + 1) + 1) * sizeof(double),
-                                     hipMemcpyDeviceToHost, s));
-            SDBIE_HIP(hipStreamSynchronize(s));
             for (int j = 0; j <= k; ++j) Hat(j, k) = col[j] + col[k + 1 + j];
             const double hk1 = std::sqrt(col[2 * (k + 1)]);
             if (!std::isfinite(hk1)) throw Error(SDBIE_ERR_NONFINITE, "non-finite Krylov vector");
             Hat(k + 1, k) = hk1;
-            if (hk1 > 0.0 && k + 1 < m + 1) dev_scale(1.0 / hk1, w, ws.V + (int64_t)(k + 1) * L, L, s);
             for (int j = 0; j < k; ++j) {
                 const double t = cs[j] * Hat(j, k) + sn[j] * Hat(j + 1, k);
                 Hat(j + 1, k) = -sn[j] * Hat(j, k) + cs[j] * Hat(j + 1, k);
@@ -423,8 +440,9 @@ void Ctx::darcy(const sdbie_params& prm, const double* v, double* p, bool p_nonz
     if (!v_zero && fused_residuals_ok(p_nonzero, extra_rhs, bnorm)) {
         // r = (mu/K) S_L[v] - Abar_D x: the single and subtracted double layer in one pass
         const ResidualFn res = [&](const double* xv, double* r) {
-            dev_dot(P, P.w, xv, n, P.scal + kScalCompD, s);
             PassDesc d;
+            d.comp_a = P.w;
+            d.comp_b = xv;
             d.dl = true;
             d.sub = true;
             d.c_dl = -1.0 / (4.0 * kPi);
@@ -432,7 +450,6 @@ void Ctx::darcy(const sdbie_params& prm, const double* v, double* p, bool p_nonz
             d.sl = true;
             d.c_sl = -(prm.mu / prm.K) / (4.0 * kPi);
             d.sl_dens = v;
-            d.comp = P.scal + kScalCompD;
             d.comp_scale = -1.0 / P.area;
             d.out = r;
             launch_laplace_pass(P, d, s);
@@ -463,8 +480,9 @@ void Ctx::stokes(const sdbie_params& prm, const double U[3], const double* p, co
         // and the subtracted stresslet in one pass
         const ResidualFn res = [&](const double* xv, double* r) {
             dev_traction(P, p, xv, beta, fx, f, s);
-            dev_dot(P, P.wn, xv, 3 * n, P.scal + kScalCompS, s);
             PassDesc d;
+            d.comp_a = P.wn;
+            d.comp_b = xv;
             d.dl = true;
             d.sub = true;
             d.c_dl = 3.0 / (4.0 * kPi);
@@ -474,7 +492,6 @@ void Ctx::stokes(const sdbie_params& prm, const double U[3], const double* p, co
             d.sl = true;
             d.c_sl = -1.0 / (8.0 * kPi * prm.mu);
             d.sl_dens = f;
-            d.comp = P.scal + kScalCompS;
             d.comp_scale = -1.0 / P.area;
             d.add_const = U;
             d.out = r;
@@ -738,8 +755,9 @@ void Ctx::coupled_residual(const sdbie_params& prm, const double U[3], const dou
     const double beta = prm.alpha * prm.mu / std::sqrt(prm.K);
     double* vn = P.vec(kVecCoupledV);
     dev_normal_component(P, u, vn, s);
-    dev_dot(P, P.w, pt, n, P.scal + kScalCompD, s);
     PassDesc d;
+    d.comp_a = P.w;
+    d.comp_b = pt;
     d.dl = true;
     d.sub = true;
     d.c_dl = -1.0 / (4.0 * kPi);
@@ -747,7 +765,6 @@ void Ctx::coupled_residual(const sdbie_params& prm, const double U[3], const dou
     d.sl = true;
     d.c_sl = -(prm.mu / prm.K) / (4.0 * kPi);
     d.sl_dens = vn;
-    d.comp = P.scal + kScalCompD;
     d.comp_scale = -1.0 / P.area;
     d.out = r1;
     launch_laplace_pass(P, d, s);
@@ -755,8 +772,9 @@ void Ctx::coupled_residual(const sdbie_params& prm, const double U[3], const dou
     double* f = P.vec(kVecTraction);
     project_mean(pt, vn);
     dev_traction(P, vn, u, beta, fx, f, s);
-    dev_dot(P, P.wn, u, 3 * n, P.scal + kScalCompS, s);
     PassDesc e;
+    e.comp_a = P.wn;
+    e.comp_b = u;
     e.dl = true;
     e.sub = true;
     e.c_dl = 3.0 / (4.0 * kPi);
@@ -766,7 +784,6 @@ void Ctx::coupled_residual(const sdbie_params& prm, const double U[3], const dou
     e.sl = true;
     e.c_sl = -1.0 / (8.0 * kPi * prm.mu);
     e.sl_dens = f;
-    e.comp = P.scal + kScalCompS;
     e.comp_scale = -1.0 / P.area;
     e.add_const = U;
     e.out = r2;
@@ -1112,6 +1129,9 @@ Ctx::Ctx(Plan& plan, hipStream_t st, const sdbie_opts& opts) : P(plan), s(st), o
     outer.dy = P.scal + kScalGmres + 3 * (m + 2) + 2 * (m + 1) + 1;
     P.applies_fp64 = P.applies_mixed = 0;
     P.pairs = 0.0;
+    if (!P.host_pinned)
+        SDBIE_HIP(hipHostMalloc(reinterpret_cast<void**>(&P.host_pinned), kHostDoubles * sizeof(double),
+                                hipHostMallocDefault));
 }
 
 void Ctx::finish() {
