@@ -287,14 +287,6 @@ __global__ void k_scatter(int64_t n, int comps, const int32_t* __restrict__ perm
     for (int c = 0; c < comps; ++c) dst[c * n + o] = src[c * n + i];
 }
 
-// flag[0] = 1 if some entry is not finite, flag[1] = 1 if some finite entry exceeds bound in magnitude
-__global__ void k_check_finite(const double* __restrict__ a, int64_t len, double bound, int* __restrict__ flag) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= len) return;
-    if (!isfinite(a[i])) flag[0] = 1;
-    else if (fabs(a[i]) > bound) flag[1] = 1;
-}
-
 // ---- adjoint helpers ------------------------------------------------------
 // out = tn + lam * dl1 + w * (*sum) / area      (transposed completed Darcy operator)
 __global__ void k_adj_darcy(int64_t n, const double* __restrict__ tn, const double* __restrict__ lam,
@@ -471,11 +463,6 @@ void dev_gather(const Plan& P, const double* src, double* dst, int comps, hipStr
 
 void dev_scatter(const Plan& P, const double* src, double* dst, int comps, hipStream_t s) {
     hipLaunchKernelGGL(k_scatter, dim3(nblk(P.n)), dim3(256), 0, s, P.n, comps, (const int32_t*)P.perm, src, dst);
-    SDBIE_LAUNCHED();
-}
-
-void dev_check_finite(const double* a, int64_t len, double bound, int* flag, hipStream_t s) {
-    hipLaunchKernelGGL(k_check_finite, dim3(nblk(len)), dim3(256), 0, s, a, len, bound, flag);
     SDBIE_LAUNCHED();
 }
 

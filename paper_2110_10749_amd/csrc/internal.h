@@ -290,9 +290,6 @@ void dev_traction(const Plan& P, const double* p, const double* u, double beta, 
 // sorted <-> caller order
 void dev_gather(const Plan& P, const double* src, double* dst, int comps, hipStream_t s);
 void dev_scatter(const Plan& P, const double* src, double* dst, int comps, hipStream_t s);
-// non-finite check: *flag (device int) set to 1 if any element is not finite
-void dev_check_finite(const double* a, int64_t len, double bound, int* flag, hipStream_t s);
-
 // adjoint helpers (see blas.hip)
 void dev_adj_darcy(const Plan& P, const double* tn, const double* lam, const double* dl1, const double* sum,
                    double* out, hipStream_t s);

@@ -7,8 +7,8 @@
 // hipGetSymbolAddress (with that device current) and kept, and only that
 // address is handed to kernels.  Every call on one device reuses its array:
 // staging rewrites all node data, masks and boxes, the pass kernels write
-// every partial slot they later read, and the flags and counters are cleared
-// by fill kernels.  Calls that overlap in time on one device race on it.
+// every partial slot they later read, and kernels write the flags and
+// counters.  Calls that overlap in time on one device race on it.
 #include <cmath>
 #include <mutex>
 #include <string>

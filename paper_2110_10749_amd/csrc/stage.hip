@@ -5,45 +5,60 @@
 // so the near-field branch (rho < rho_cut) is taken by few waves per source
 // and the rest run the plain far-field kernel.
 //
-// Steps (all on the device): bounding box (min/max reduction), 30-bit Morton
-// key per node (10 bits per axis), key<<32 | index sorted by a bitonic network
-// over the next power of two (padding keys = UINT64_MAX; keys are unique, so
-// the order is deterministic), then gather of x, n, w into sorted double
-// arrays and the weighted normals w n; copies padded to whole tiles of kTile
-// nodes for the pair kernels; per-tile bounding boxes; a float copy of the
-// coordinates in the frame of each node's tile; and the near-field masks of
-// tile pairs (box distance below rho_cut delta, one mask for the double cutoff
-// and one for the float cutoff).
-
+// Steps (all on the device, one synchronisation at the end): finite check and
+// bounding box; 30-bit Morton key per node (10 bits per axis), key<<32 | index
+// sorted by a bitonic network over the next power of two (padding keys =
+// UINT64_MAX; keys are unique, so the order is deterministic); gather of x, n,
+// w into sorted double arrays and the weighted normals w n, copies padded to
+// whole tiles of kTile nodes for the pair kernels, tile and unit bounding
+// boxes and a float copy of the coordinates in the frame of each node's tile;
+// the near-field masks of tile pairs (box distance below rho_cut delta, one
+// mask for the double cutoff and one for the float cutoff); and the work lists
+// of the symmetric passes.
+//
+// Staging is launches more than work: with one launch per step of the sorting
+// network (153 at n = 68166), one per array and three synchronisations it took
+// 0.8 ms there and 0.45 ms at n = 9582; now about 20 launches and 0.2 ms.
 #include "smoothing_coeffs.h"
 #include "solver.h"
 
 namespace sdbie {
 namespace {
 
-__global__ __launch_bounds__(256) void k_bbox(int64_t n, const double* __restrict__ x, double* __restrict__ out) {
-    // one block per axis: out[2c] = min, out[2c+1] = max
-    __shared__ double smin[256], smax[256];
-    const int c = blockIdx.x;
-    double lo = INFINITY, hi = -INFINITY;
-    for (int64_t i = threadIdx.x; i < n; i += 256) {
-        const double v = x[c * n + i];
-        lo = fmin(lo, v);
-        hi = fmax(hi, v);
-    }
-    smin[threadIdx.x] = lo;
-    smax[threadIdx.x] = hi;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            smin[threadIdx.x] = fmin(smin[threadIdx.x], smin[threadIdx.x + s]);
-            smax[threadIdx.x] = fmax(smax[threadIdx.x], smax[threadIdx.x + s]);
+constexpr int kScanBlocks = 256;  // blocks of the input scan
+
+// per block: min and max of x per axis, then 1 if some entry of x, n or w is
+// not finite, 1 if some coordinate exceeds kMaxCoord: part[kScanBlocks][8]
+__global__ __launch_bounds__(256) void k_scan_input(int64_t n, const double* __restrict__ x,
+                                                    const double* __restrict__ nrm, const double* __restrict__ w,
+                                                    double* __restrict__ part) {
+    __shared__ double sh[4][8];
+    double v[8] = {INFINITY, -INFINITY, INFINITY, -INFINITY, INFINITY, -INFINITY, 0.0, 0.0};
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)kScanBlocks * 256) {
+        for (int c = 0; c < 3; ++c) {
+            const double t = x[c * n + i];
+            v[2 * c] = fmin(v[2 * c], t);
+            v[2 * c + 1] = fmax(v[2 * c + 1], t);
+            if (!isfinite(t) || !isfinite(nrm[c * n + i])) v[6] = 1.0;
+            else if (fabs(t) > kMaxCoord) v[7] = 1.0;
         }
-        __syncthreads();
+        if (!isfinite(w[i])) v[6] = 1.0;
     }
-    if (threadIdx.x == 0) {
-        out[2 * c] = smin[0];
-        out[2 * c + 1] = smax[0];
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const double t = __shfl_xor(v[c], o, 64);
+            v[c] = c < 6 && !(c & 1) ? fmin(v[c], t) : fmax(v[c], t);
+        }
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) sh[threadIdx.x >> 6][c] = v[c];
+    __syncthreads();
+    if (threadIdx.x < 8) {
+        const int c = threadIdx.x;
+        double r = sh[0][c];
+        for (int k = 1; k < 4; ++k) r = c < 6 && !(c & 1) ? fmin(r, sh[k][c]) : fmax(r, sh[k][c]);
+        part[blockIdx.x * 8 + c] = r;
     }
 }
 
@@ -56,9 +71,42 @@ __device__ __forceinline__ uint32_t spread10(uint32_t v) {
     return v;
 }
 
-__global__ void k_morton(int64_t n, int64_t npow2, const double* __restrict__ x, const double* __restrict__ bb,
-                         uint64_t* __restrict__ keys) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Morton keys; every block adds up the block results of the input scan, the
+// first writes them to stage[0..9] (the box 2 .. 7, the two flags as ints in
+// stage[0]) and clears the near-pair counters stage[10], stage[11]
+__global__ __launch_bounds__(256) void k_morton(int64_t n, int64_t npow2, const double* __restrict__ x,
+                                                const double* __restrict__ part, double* __restrict__ stage,
+                                                uint64_t* __restrict__ keys) {
+    __shared__ double sh[4][8], bb[8];
+    static_assert(kScanBlocks == 256, "one block result per thread");
+    double v[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v[c] = part[threadIdx.x * 8 + c];
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const double t = __shfl_xor(v[c], o, 64);
+            v[c] = c < 6 && !(c & 1) ? fmin(v[c], t) : fmax(v[c], t);
+        }
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) sh[threadIdx.x >> 6][c] = v[c];
+    __syncthreads();
+    if (threadIdx.x < 8) {
+        const int c = threadIdx.x;
+        double r = sh[0][c];
+        for (int k = 1; k < 4; ++k) r = c < 6 && !(c & 1) ? fmin(r, sh[k][c]) : fmax(r, sh[k][c]);
+        bb[c] = r;
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        int* flag = reinterpret_cast<int*>(stage);
+        flag[0] = bb[6] > 0.0;
+        flag[1] = bb[7] > 0.0;
+        for (int c = 0; c < 6; ++c) stage[2 + c] = bb[c];
+        stage[10] = stage[11] = 0.0;  // two 64-bit counters (all-zero bits)
+    }
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= npow2) return;
     if (i >= n) {
         keys[i] = ~0ull;
@@ -76,130 +124,187 @@ __global__ void k_morton(int64_t n, int64_t npow2, const double* __restrict__ x,
     keys[i] = ((uint64_t)code << 32) | (uint64_t)i;
 }
 
-__global__ void k_bitonic(uint64_t* __restrict__ keys, int64_t npow2, int64_t j, int64_t k) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= npow2) return;
-    const int64_t l = i ^ j;
-    if (l > i) {
-        const uint64_t a = keys[i], b = keys[l];
-        const bool up = (i & k) == 0;
-        if ((a > b) == up) {
-            keys[i] = b;
-            keys[l] = a;
+// ---- sorting network -----------------------------------------------------------
+// Bitonic steps (k, j) compare elements i and i ^ j; the lower one keeps the
+// smaller key where bit k of i is clear.  A block holds kSortBlock consecutive
+// keys, 8 to a thread: steps with j < 8 stay in registers, j < 512 pass keys
+// between the lanes of a wave, the others through LDS.  Steps across blocks run
+// up to three to a launch, 8 keys to a thread.
+constexpr int kSortBlock = 8192, kSortThreads = kSortBlock / 8;
+
+__device__ __forceinline__ uint64_t keep(uint64_t a, uint64_t b, bool smaller) {
+    return (a < b) == smaller ? a : b;
+}
+
+// steps k, j = jmax, jmax / 2 .. 1 on the block's keys (element i0 + 8 tid + e in v[e])
+__device__ __forceinline__ void bitonic_block(uint64_t (&v)[8], int64_t i0, int64_t k, int jmax, uint64_t* sh) {
+    const int tid = threadIdx.x;
+    const int64_t i = i0 + 8 * tid;
+    for (int j = jmax; j >= 8; j >>= 1) {
+        const bool smaller = ((i & k) == 0) == ((i & j) == 0);  // bits above the 8 elements of a thread
+        if (j >= 512) {
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sh[e * kSortThreads + tid] = v[e];
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = keep(v[e], sh[e * kSortThreads + (tid ^ (j >> 3))], smaller);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                v[e] = keep(v[e], (uint64_t)__shfl_xor((unsigned long long)v[e], j >> 3, 64), smaller);
         }
     }
-}
-
-__global__ void k_stage(int64_t n, const uint64_t* __restrict__ keys, const double* __restrict__ x,
-                        const double* __restrict__ nrm, const double* __restrict__ w, int32_t* __restrict__ perm,
-                        double* __restrict__ xs, double* __restrict__ ns, double* __restrict__ wsrt,
-                        double* __restrict__ wn) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const int64_t o = (int64_t)(keys[k] & 0xffffffffull);
-    perm[k] = (int32_t)o;
-    const double wk = w[o];
-    wsrt[k] = wk;
-    for (int c = 0; c < 3; ++c) {
-        const double xv = x[c * n + o], nv = nrm[c * n + o];
-        xs[c * n + k] = xv;
-        ns[c * n + k] = nv;
-        wn[c * n + k] = wk * nv;
+#pragma unroll
+    for (int j = 4; j > 0; j >>= 1) {
+        if (j > jmax) continue;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (!(e & j)) {
+                const bool up = ((i + e) & k) == 0;
+                const uint64_t a = v[e], b = v[e | j];
+                v[e] = keep(a, b, up);
+                v[e | j] = keep(a, b, !up);
+            }
     }
 }
 
-// padded copies for the pair kernels: nodes k >= n sit at a point `far`
-// outside the bounding box (10 extents away) with zero weight and normal.
-__global__ void k_pad(int64_t n, int64_t npad, const double* __restrict__ xs, const double* __restrict__ ns,
-                      const double* __restrict__ ws, const double* __restrict__ bb, double* __restrict__ px,
-                      double* __restrict__ pn, double* __restrict__ pw) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= npad) return;
-    const double ext = fmax(fmax(bb[1] - bb[0], bb[3] - bb[2]), bb[5] - bb[4]);
-    for (int c = 0; c < 3; ++c) {
-        const double xv = k < n ? xs[c * n + k] : bb[2 * c + 1] + 10.0 * ext + 1.0;
-        px[c * npad + k] = xv;
-        pn[c * npad + k] = k < n ? ns[c * n + k] : 0.0;
+// full: every step k = 2 .. min(npow2, kSortBlock); else the steps j < kSortBlock of k
+__global__ __launch_bounds__(kSortThreads) void k_sort_block(uint64_t* __restrict__ keys, int64_t npow2, int64_t k,
+                                                             int full) {
+    __shared__ uint64_t sh[kSortBlock];
+    const int64_t i0 = (int64_t)blockIdx.x * kSortBlock, i = i0 + 8 * threadIdx.x;
+    uint64_t v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = i + e < npow2 ? keys[i + e] : ~0ull;
+    if (full) {
+        const int64_t top = npow2 < kSortBlock ? npow2 : kSortBlock;
+        for (int64_t kk = 2; kk <= top; kk <<= 1) bitonic_block(v, i0, kk, (int)(kk >> 1), sh);
+    } else {
+        bitonic_block(v, i0, k, kSortBlock / 2, sh);
     }
-    pw[k] = k < n ? ws[k] : 0.0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        if (i + e < npow2) keys[i + e] = v[e];
 }
 
-// float coordinates in the frame of their tile: minus the centre of the tile's
-// box (every tile holds at least one real node, so the centre is finite).  The
-// kernels see coordinates only through differences x_i - x_j, formed after
+// steps (k, j), (k, j / 2) .. (k, j >> (S - 1)) across blocks: 2^S keys to a thread, j >> (S - 1) apart
+template <int S>
+__global__ __launch_bounds__(256) void k_sort_global(uint64_t* __restrict__ keys, int64_t npow2, int64_t k, int64_t j) {
+    constexpr int E = 1 << S;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, d = j >> (S - 1);
+    if (t >= npow2 / E) return;
+    const int64_t i = (t / d) * (d * E) + t % d;  // the S bits from log2 d on are clear
+    const bool up = (i & k) == 0;                 // k > j: the same for the thread's keys
+    uint64_t v[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = keys[i + e * d];
+#pragma unroll
+    for (int b = E / 2; b > 0; b >>= 1)
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (!(e & b)) {
+                const uint64_t x = v[e], y = v[e | b];
+                v[e] = keep(x, y, up);
+                v[e | b] = keep(x, y, !up);
+            }
+#pragma unroll
+    for (int e = 0; e < E; ++e) keys[i + e * d] = v[e];
+}
+
+void sort_keys(uint64_t* keys, int64_t npow2, hipStream_t st) {
+    const unsigned nb = (unsigned)((npow2 + kSortBlock - 1) / kSortBlock);
+    // one wave at least; below kSortBlock only the threads that hold keys
+    const unsigned th = npow2 >= kSortBlock ? kSortThreads : (unsigned)(npow2 / 8 < 64 ? 64 : npow2 / 8);
+    hipLaunchKernelGGL(k_sort_block, dim3(nb), dim3(th), 0, st, keys, npow2, (int64_t)0, 1);
+    SDBIE_LAUNCHED();
+    for (int64_t k = 2 * kSortBlock; k <= npow2; k <<= 1) {
+        int64_t j = k >> 1;
+        while (j >= kSortBlock) {
+            const int64_t left = j / kSortBlock;  // steps left across blocks: log2(left) + 1
+            const int s = left >= 4 ? 3 : left >= 2 ? 2 : 1;
+            const dim3 g((unsigned)(((npow2 >> s) + 255) / 256));
+            if (s == 3) hipLaunchKernelGGL((k_sort_global<3>), g, dim3(256), 0, st, keys, npow2, k, j);
+            else if (s == 2) hipLaunchKernelGGL((k_sort_global<2>), g, dim3(256), 0, st, keys, npow2, k, j);
+            else hipLaunchKernelGGL((k_sort_global<1>), g, dim3(256), 0, st, keys, npow2, k, j);
+            SDBIE_LAUNCHED();
+            j >>= s;
+        }
+        hipLaunchKernelGGL(k_sort_block, dim3(nb), dim3(kSortThreads), 0, st, keys, npow2, k, 0);
+        SDBIE_LAUNCHED();
+    }
+}
+
+// Sorted and padded copies, one block per tile.  Padding nodes k >= n sit at a
+// point outside the bounding box (10 extents away) with zero weight and normal.
+// Boxes of the tile and of its units hold the real nodes (empty: +inf / -inf).
+// The float coordinates are in the frame of their tile: minus the centre of the
+// tile's box (every tile holds at least one real node, so the centre is finite).
+// The kernels see coordinates only through differences x_i - x_j, formed after
 // moving the targets into the source tile's frame, so the rounding of a float
 // coordinate is set by the tile's extent, not by the body's or by the
 // distance from the origin.
-__global__ void k_frame32(int64_t npad, const double* __restrict__ px, const double* __restrict__ boxes,
-                          float* __restrict__ px32) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= npad) return;
-    const double* b = boxes + (k / kTile) * 6;
-    for (int c = 0; c < 3; ++c) px32[c * npad + k] = (float)(px[c * npad + k] - 0.5 * (b[2 * c] + b[2 * c + 1]));
-}
+struct StageArgs {
+    int64_t n, npad;
+    const uint64_t* keys;
+    const double *x, *nrm, *w, *bb;  // bb: bounding box
+    int32_t* perm;
+    double *xs, *ns, *ws, *wn, *px, *pn, *pw;
+    float* px32;
+    double *boxes, *uboxes;
+};
 
-// bounding box of each group of W consecutive (sorted) real nodes (empty:
-// +inf / -inf for a group of padding only); one block of W threads per group
-template <int W>
-__global__ __launch_bounds__(W) void k_boxes(int64_t n, const double* __restrict__ xs, double* __restrict__ boxes) {
-    __shared__ double sh[6][W];
-    const int64_t k = (int64_t)blockIdx.x * W + threadIdx.x;
+__global__ __launch_bounds__(kTile) void k_stage(StageArgs a) {
+    __shared__ double ub[kTile / 64][6];
+    static_assert(kNearUnit == 64, "a wave stages a unit");
+    const int64_t k = (int64_t)blockIdx.x * kTile + threadIdx.x, n = a.n, npad = a.npad;
+    const bool real = k < n;
+    const int64_t o = real ? (int64_t)(a.keys[k] & 0xffffffffull) : 0;
+    const double ext = fmax(fmax(a.bb[1] - a.bb[0], a.bb[3] - a.bb[2]), a.bb[5] - a.bb[4]);
+    const double wk = real ? a.w[o] : 0.0;
+    double xv[3], lo[3], hi[3];
     for (int c = 0; c < 3; ++c) {
-        const double v = k < n ? xs[c * n + k] : NAN;
-        sh[2 * c][threadIdx.x] = k < n ? v : INFINITY;
-        sh[2 * c + 1][threadIdx.x] = k < n ? v : -INFINITY;
-    }
-    __syncthreads();
-    for (int s = W / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s)
-            for (int c = 0; c < 3; ++c) {
-                sh[2 * c][threadIdx.x] = fmin(sh[2 * c][threadIdx.x], sh[2 * c][threadIdx.x + s]);
-                sh[2 * c + 1][threadIdx.x] = fmax(sh[2 * c + 1][threadIdx.x], sh[2 * c + 1][threadIdx.x + s]);
-            }
-        __syncthreads();
-    }
-    if (threadIdx.x < 6) boxes[(int64_t)blockIdx.x * 6 + threadIdx.x] = sh[threadIdx.x][0];
-}
-
-// mask[b][t] = 1 when the boxes of tiles b and t are closer than the cutoff.
-// cnt[0], cnt[1] += the (target, source) pairs of real nodes in the near tile
-// pairs of each precision (integer sums: exact in any order).
-__global__ void k_near_masks(int nt, int64_t n, const double* __restrict__ boxes, double rc64, double rc32,
-                             uint8_t* __restrict__ m64, uint8_t* __restrict__ m32,
-                             unsigned long long* __restrict__ cnt) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    unsigned long long c64 = 0, c32 = 0;
-    if (idx < (int64_t)nt * nt) {
-        const int64_t b = idx / nt, t = idx % nt;
-        const double* A = boxes + b * 6;
-        const double* B = boxes + t * 6;
-        double d2 = 0.0;
-        for (int c = 0; c < 3; ++c) {
-            const double gap = fmax(0.0, fmax(A[2 * c] - B[2 * c + 1], B[2 * c] - A[2 * c + 1]));
-            d2 += gap * gap;
+        xv[c] = real ? a.x[c * n + o] : a.bb[2 * c + 1] + 10.0 * ext + 1.0;
+        const double nv = real ? a.nrm[c * n + o] : 0.0;
+        if (real) {
+            a.xs[c * n + k] = xv[c];
+            a.ns[c * n + k] = nv;
+            a.wn[c * n + k] = wk * nv;
         }
-        const bool n64 = d2 < rc64 * rc64, n32 = d2 < rc32 * rc32;
-        m64[idx] = n64 ? 1 : 0;
-        m32[idx] = n32 ? 1 : 0;
-        const int64_t rb = n - b * kTile < kTile ? n - b * kTile : kTile;
-        const int64_t rt = n - t * kTile < kTile ? n - t * kTile : kTile;
-        const unsigned long long pr = (unsigned long long)(rb * rt);
-        c64 = n64 ? pr : 0;
-        c32 = n32 ? pr : 0;
+        a.px[c * npad + k] = xv[c];
+        a.pn[c * npad + k] = nv;
+        lo[c] = real ? xv[c] : INFINITY;
+        hi[c] = real ? xv[c] : -INFINITY;
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        c64 += __shfl_down(c64, off);
-        c32 += __shfl_down(c32, off);
+    if (real) {
+        a.perm[k] = (int32_t)o;
+        a.ws[k] = wk;
     }
-    if ((threadIdx.x & 63) == 0) {
-        if (c64) atomicAdd(cnt, c64);
-        if (c32) atomicAdd(cnt + 1, c32);
+    a.pw[k] = wk;
+    for (int off = 32; off > 0; off >>= 1)
+        for (int c = 0; c < 3; ++c) {
+            lo[c] = fmin(lo[c], __shfl_xor(lo[c], off, 64));
+            hi[c] = fmax(hi[c], __shfl_xor(hi[c], off, 64));
+        }
+    const int u = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0)
+        for (int c = 0; c < 3; ++c) {
+            ub[u][2 * c] = lo[c];
+            ub[u][2 * c + 1] = hi[c];
+        }
+    __syncthreads();
+    for (int c = 0; c < 3; ++c) {
+        lo[c] = fmin(fmin(ub[0][2 * c], ub[1][2 * c]), fmin(ub[2][2 * c], ub[3][2 * c]));
+        hi[c] = fmax(fmax(ub[0][2 * c + 1], ub[1][2 * c + 1]), fmax(ub[2][2 * c + 1], ub[3][2 * c + 1]));
+        a.px32[c * npad + k] = (float)(xv[c] - 0.5 * (lo[c] + hi[c]));
     }
+    if (threadIdx.x < 6) a.boxes[(int64_t)blockIdx.x * 6 + threadIdx.x] = threadIdx.x & 1 ? hi[threadIdx.x >> 1] : lo[threadIdx.x >> 1];
+    if (threadIdx.x < 24) a.uboxes[(int64_t)blockIdx.x * 24 + threadIdx.x] = ub[threadIdx.x / 6][threadIdx.x % 6];
 }
 
-// Work lists of the symmetric passes, from the near masks, in three kernels:
-// counts of each mask row, their prefix sums (one block), and the items and
-// blocks of each row.  Blocks hold as many pairs as leave about
+// Near masks, and the work lists of the symmetric passes, in three kernels: the
+// mask rows and their counts, the prefix sums of those (one block), and the
+// items and blocks of each row.  Blocks hold as many pairs as leave about
 // SDBIE_SYM_TARGET of them for each kind of pair (at most kSymChunk while the
 // forward slots have room): with 8 pairs to a block the 2200 pairs of n = 17070
 // made 343 blocks for 256 CUs.
@@ -233,32 +338,90 @@ enum : int {
 };
 static_assert(kRowFarBlk + 3 <= kSymRowInts, "ints of a row");
 
-__global__ __launch_bounds__(256) void k_list_rows(int T, const uint8_t* __restrict__ m64,
-                                                   const uint8_t* __restrict__ m32, int32_t* __restrict__ rows,
-                                                   int32_t* __restrict__ colrank) {
+// mask[a][b] = 1 when the boxes of tiles a and b are closer than the cutoff (one
+// block per row a; the masks are symmetric).  cnt[0], cnt[1] += the (target,
+// source) pairs of real nodes in the near tile pairs of each precision (integer
+// sums: exact in any order).  With rows: the counts of the row's tile pairs, and
+// for the far-only set the rank of each far b < a in column a.  The first
+// kRedBlocks blocks also take the block partials of the weight sum (dev_dot's).
+__global__ __launch_bounds__(256) void k_mask_rows(int T, int64_t n, const double* __restrict__ boxes, double rc64,
+                                                   double rc32, uint8_t* __restrict__ m64, uint8_t* __restrict__ m32,
+                                                   unsigned long long* __restrict__ cnt, int32_t* __restrict__ rows,
+                                                   int32_t* __restrict__ colrank, const double* __restrict__ w,
+                                                   double* __restrict__ part) {
     __shared__ int sh[4];
+    __shared__ double shd[4];
     const int a = blockIdx.x;
-    int cnt[5] = {0, 0, 0, 0, 0};
+    if (a < kRedBlocks) {
+        double s = 0.0;
+        for (int64_t i = (int64_t)a * 256 + threadIdx.x; i < n; i += (int64_t)kRedBlocks * 256) s += w[i];
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if ((threadIdx.x & 63) == 0) shd[threadIdx.x >> 6] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) part[a] = (shd[0] + shd[1]) + (shd[2] + shd[3]);
+    }
+    if (a >= T) return;
+    const double* A = boxes + (int64_t)a * 6;
+    int c[5] = {0, 0, 0, 0, 0};
+    unsigned long long c64 = 0, c32 = 0;
     for (int b0 = 0; b0 < T; b0 += 256) {
         const int b = b0 + threadIdx.x;
         const bool in = b < T;
-        const bool n64 = in && m64[(int64_t)a * T + b], n32 = in && m32[(int64_t)a * T + b];
+        bool n64 = false, n32 = false;
+        if (in) {
+            const double* B = boxes + (int64_t)b * 6;
+            double d2 = 0.0;
+            for (int k = 0; k < 3; ++k) {
+                const double gap = fmax(0.0, fmax(A[2 * k] - B[2 * k + 1], B[2 * k] - A[2 * k + 1]));
+                d2 += gap * gap;
+            }
+            n64 = d2 < rc64 * rc64;
+            n32 = d2 < rc32 * rc32;
+            m64[(int64_t)a * T + b] = n64 ? 1 : 0;
+            m32[(int64_t)a * T + b] = n32 ? 1 : 0;
+            const int64_t ra = n - (int64_t)a * kTile < kTile ? n - (int64_t)a * kTile : kTile;
+            const int64_t rb = n - (int64_t)b * kTile < kTile ? n - (int64_t)b * kTile : kTile;
+            if (n64) c64 += (unsigned long long)(ra * rb);
+            if (n32) c32 += (unsigned long long)(ra * rb);
+        }
+        if (!rows) continue;
         int t;
         block_rank(in && b > a && n64, sh, t);
-        cnt[kRowNear64] += t;
+        c[kRowNear64] += t;
         block_rank(in && b > a && !n64, sh, t);
-        cnt[kRowFar64] += t;
-        // the masks are symmetric: row a, b < a, is the far-only column of source tile a
+        c[kRowFar64] += t;
         const bool cf = in && b < a && !n64;
         const int r = block_rank(cf, sh, t);
-        if (cf) colrank[(int64_t)a * T + b] = cnt[kRowColFar64] + r;
-        cnt[kRowColFar64] += t;
+        if (cf) colrank[(int64_t)a * T + b] = c[kRowColFar64] + r;
+        c[kRowColFar64] += t;
         block_rank(in && b != a && n32, sh, t);
-        cnt[kRowNear32] += t;
+        c[kRowNear32] += t;
         block_rank(in && b > a && !n32, sh, t);
-        cnt[kRowFar32] += t;
+        c[kRowFar32] += t;
     }
-    if (threadIdx.x < 5) rows[(int64_t)a * kSymRowInts + threadIdx.x] = cnt[threadIdx.x];
+    if (rows && threadIdx.x == 0)
+        for (int k = 0; k < 5; ++k) rows[(int64_t)a * kSymRowInts + k] = c[k];
+    for (int off = 32; off > 0; off >>= 1) {
+        c64 += __shfl_down(c64, off);
+        c32 += __shfl_down(c32, off);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        if (c64) atomicAdd(cnt, c64);
+        if (c32) atomicAdd(cnt + 1, c32);
+    }
+}
+
+// the weight sum from its block partials (k_reduce_cols' order)
+__device__ __forceinline__ void reduce_area(const double* __restrict__ part, double* __restrict__ out) {
+    __shared__ double sh[4];
+    double s = part[threadIdx.x] + part[threadIdx.x + 256];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) out[0] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+__global__ __launch_bounds__(256) void k_area(const double* __restrict__ part, double* __restrict__ out) {
+    reduce_area(part, out);
 }
 
 struct ListArgs {
@@ -270,6 +433,8 @@ struct ListArgs {
     int32_t* rows;
     int32_t *items[3], *blocks[3], *fwd_start[3], *rev_start[3];
     int32_t* out;  // number of blocks of the three sets, near and far chunk of double and float
+    const double* area_part;
+    double* area;
 };
 
 constexpr int kScanRows = 8;  // rows per thread of the scan (2048 tiles)
@@ -283,15 +448,19 @@ __device__ __forceinline__ int block_scan(int (&v)[kScanRows], int* sh) {
         v[i] = s;
         s += t;
     }
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-        const int t = (int)threadIdx.x >= o ? sh[threadIdx.x - o] : 0;
-        __syncthreads();
-        sh[threadIdx.x] += t;
-        __syncthreads();
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int inc = s;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += t;
     }
-    const int base = threadIdx.x ? sh[threadIdx.x - 1] : 0, total = sh[255];
+    if (lane == 63) sh[w] = inc;
+    __syncthreads();
+    int base = inc - s, total = 0;
+    for (int k = 0; k < 4; ++k) {
+        if (k < w) base += sh[k];
+        total += sh[k];
+    }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kScanRows; ++i) v[i] += base;
@@ -299,7 +468,8 @@ __device__ __forceinline__ int block_scan(int (&v)[kScanRows], int* sh) {
 }
 
 __global__ __launch_bounds__(256) void k_list_scan(ListArgs A) {
-    __shared__ int sh[256];
+    __shared__ int sh[4];
+    reduce_area(A.area_part, A.area);
     const int r0 = threadIdx.x * kScanRows;
     auto row = [&](int i, int what) { return r0 + i < A.T ? A.rows[(int64_t)(r0 + i) * kSymRowInts + what] : 0; };
     auto put = [&](int i, int what, int v) {
@@ -445,7 +615,7 @@ __global__ __launch_bounds__(256) void k_list_fill(ListArgs A) {
     }
 }
 
-// Enqueues the list kernels; the block counts arrive in out[0..2] (device).
+// Enqueues the list kernels after k_mask_rows; the block counts arrive in out[0..2] (device).
 // Forward and reverse slots of several parts to a pair share the partial
 // buffer of the one-direction passes; of one part the reverse slots have their
 // own region, and the forward ones take the larger of the buffer and sym_fwd.
@@ -460,6 +630,8 @@ void build_symmetric_lists(Plan& P, int32_t* out, hipStream_t st) {
     A.rows = P.sym_rows;
     A.colrank = static_cast<const int32_t*>(P.rec);  // T^2 ints; no pass runs yet
     A.out = out;
+    A.area_part = P.red;
+    A.area = P.scal + kScalStage + 8;
     const bool in_partial = P.partial_bytes > P.sym_fwd_bytes;
     for (int k = 0; k < 2; ++k) {
         SymSet& S = P.sym[k];
@@ -487,9 +659,6 @@ void build_symmetric_lists(Plan& P, int32_t* out, hipStream_t st) {
         A.fwd_start[k] = P.sym[k].fwd_start;
         A.rev_start[k] = P.sym[k].rev_start;
     }
-    hipLaunchKernelGGL(k_list_rows, dim3((unsigned)T), dim3(256), 0, st, T, (const uint8_t*)P.mask64,
-                       (const uint8_t*)P.mask32, P.sym_rows, static_cast<int32_t*>(P.rec));
-    SDBIE_LAUNCHED();
     hipLaunchKernelGGL(k_list_scan, dim3(1), dim3(256), 0, st, A);
     SDBIE_LAUNCHED();
     hipLaunchKernelGGL(k_list_fill, dim3((unsigned)T), dim3(256), 0, st, A);
@@ -500,72 +669,70 @@ void build_symmetric_lists(Plan& P, int32_t* out, hipStream_t st) {
 
 void stage_surface(Plan& P, const sdbie_surface* s, hipStream_t st) {
     const int64_t n = P.n;
-    // finite check of the node data first (Morton keys of NaN are meaningless)
-    // flags and counters are cleared by a fill kernel, not a memset node (the
-    // staging of the allocation-free entry point may sit in a captured stream)
-    int* flag = reinterpret_cast<int*>(P.scal + kScalStage);
-    dev_fill(0.0, P.scal + kScalStage, 1, st);  // two ints
-    dev_check_finite(s->x, 3 * n, kMaxCoord, flag, st);
-    dev_check_finite(s->nrm, 3 * n, HUGE_VAL, flag, st);
-    dev_check_finite(s->w, n, HUGE_VAL, flag, st);
-    int hflag[2] = {0, 0};
-    SDBIE_HIP(hipMemcpyAsync(hflag, flag, sizeof(hflag), hipMemcpyDeviceToHost, st));
-    SDBIE_HIP(hipStreamSynchronize(st));
-    if (hflag[0]) throw Error(SDBIE_ERR_NONFINITE, "non-finite node coordinates, normals or weights");
-    if (hflag[1]) throw Error(SDBIE_ERR_ARG, "node coordinates must not exceed 1e15 in magnitude");
-
-    double* bb = P.scal + kScalStage + 2;
-    hipLaunchKernelGGL(k_bbox, dim3(3), dim3(256), 0, st, n, s->x, bb);
+    // Flags and counters are written by kernels, not memset nodes (the staging of
+    // the allocation-free entry point may sit in a captured stream).  Non-finite
+    // input is found at the end: no step reads or writes out of range for it.
+    double* stage = P.scal + kScalStage;
+    hipLaunchKernelGGL(k_scan_input, dim3(kScanBlocks), dim3(256), 0, st, n, s->x, s->nrm, s->w,
+                       static_cast<double*>(P.rec));  // no pass runs yet
     SDBIE_LAUNCHED();
-    const unsigned nb = (unsigned)((P.npow2 + 255) / 256);
-    hipLaunchKernelGGL(k_morton, dim3(nb), dim3(256), 0, st, n, P.npow2, s->x, (const double*)bb, P.keys);
+    static_assert(kScanBlocks * 8 * sizeof(double) <= kTile * kRecBytes, "the block results fit one tile's records");
+    hipLaunchKernelGGL(k_morton, dim3((unsigned)((P.npow2 + 255) / 256)), dim3(256), 0, st, n, P.npow2, s->x,
+                       static_cast<const double*>(P.rec), stage, P.keys);
     SDBIE_LAUNCHED();
-    for (int64_t k = 2; k <= P.npow2; k <<= 1)
-        for (int64_t j = k >> 1; j > 0; j >>= 1) {
-            hipLaunchKernelGGL(k_bitonic, dim3(nb), dim3(256), 0, st, P.keys, P.npow2, j, k);
-            SDBIE_LAUNCHED();
-        }
-    hipLaunchKernelGGL(k_stage, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, (const uint64_t*)P.keys,
-                       s->x, s->nrm, s->w, P.perm, P.x, P.nrm, P.w, P.wn);
-    SDBIE_LAUNCHED();
-    hipLaunchKernelGGL(k_pad, dim3((unsigned)((P.npad + 255) / 256)), dim3(256), 0, st, n, P.npad,
-                       (const double*)P.x, (const double*)P.nrm, (const double*)P.w, (const double*)bb, P.px, P.pn,
-                       P.pw);
-    SDBIE_LAUNCHED();
-    hipLaunchKernelGGL((k_boxes<kTile>), dim3((unsigned)P.ntiles), dim3(kTile), 0, st, n, (const double*)P.x,
-                       P.boxes);
-    SDBIE_LAUNCHED();
-    hipLaunchKernelGGL(k_frame32, dim3((unsigned)((P.npad + 255) / 256)), dim3(256), 0, st, P.npad,
-                       (const double*)P.px, (const double*)P.boxes, P.px32);
-    SDBIE_LAUNCHED();
-    hipLaunchKernelGGL((k_boxes<kNearUnit>), dim3((unsigned)(P.npad / kNearUnit)), dim3(kNearUnit), 0, st, n,
-                       (const double*)P.x, P.uboxes);
+    sort_keys(P.keys, P.npow2, st);
+    StageArgs a;
+    a.n = n;
+    a.npad = P.npad;
+    a.keys = P.keys;
+    a.x = s->x;
+    a.nrm = s->nrm;
+    a.w = s->w;
+    a.bb = stage + 2;
+    a.perm = P.perm;
+    a.xs = P.x;
+    a.ns = P.nrm;
+    a.ws = P.w;
+    a.wn = P.wn;
+    a.px = P.px;
+    a.pn = P.pn;
+    a.pw = P.pw;
+    a.px32 = P.px32;
+    a.boxes = P.boxes;
+    a.uboxes = P.uboxes;
+    hipLaunchKernelGGL(k_stage, dim3((unsigned)P.ntiles), dim3(kTile), 0, st, a);
     SDBIE_LAUNCHED();
     // cutoffs with a relative margin of 1e-6 (the far kernels assume rho >= rho_cut)
     const double rc64 = SDBIE_RHO_CUT_STOKES_F64 * P.delta * (1.0 + 1e-6);
     const double rc32 = SDBIE_RHO_CUT_STOKES_F32 * P.delta * (1.0 + 1e-6);
-    const int64_t nt2 = (int64_t)P.ntiles * P.ntiles;
-    unsigned long long* cnt = reinterpret_cast<unsigned long long*>(P.scal + kScalStage + 10);
-    dev_fill(0.0, P.scal + kScalStage + 10, 2, st);  // two 64-bit counters (all-zero bits)
-    hipLaunchKernelGGL(k_near_masks, dim3((unsigned)((nt2 + 255) / 256)), dim3(256), 0, st, P.ntiles, n,
-                       (const double*)P.boxes, rc64, rc32, P.mask64, P.mask32, cnt);
-    SDBIE_LAUNCHED();
     const bool lists = P.sym[0].items != nullptr;
-    if (lists) build_symmetric_lists(P, reinterpret_cast<int32_t*>(P.scal + kScalStage + 12), st);
-    dev_dot(P, P.w, nullptr, n, P.scal + kScalStage + 8, st);
+    hipLaunchKernelGGL(k_mask_rows, dim3((unsigned)(P.ntiles > kRedBlocks ? P.ntiles : kRedBlocks)), dim3(256), 0, st,
+                       P.ntiles, n, (const double*)P.boxes, rc64, rc32, P.mask64, P.mask32,
+                       reinterpret_cast<unsigned long long*>(stage + 10), lists ? P.sym_rows : nullptr,
+                       static_cast<int32_t*>(P.rec), (const double*)P.w, P.red);
+    SDBIE_LAUNCHED();
+    if (lists) {
+        build_symmetric_lists(P, reinterpret_cast<int32_t*>(stage + 12), st);
+    } else {
+        hipLaunchKernelGGL(k_area, dim3(1), dim3(256), 0, st, (const double*)P.red, stage + 8);
+        SDBIE_LAUNCHED();
+    }
     struct {
-        double area, pad;
+        int32_t flag[2];
+        double pad[7], area, pad9;
         unsigned long long near[2];
         int32_t blocks[8];
     } h;
-    static_assert(sizeof(h) == 8 * sizeof(double), "area (8), near-pair counts (10, 11), list counts (12 ..)");
-    SDBIE_HIP(hipMemcpyAsync(&h, P.scal + kScalStage + 8, sizeof(h), hipMemcpyDeviceToHost, st));
+    static_assert(sizeof(h) == 16 * sizeof(double), "the staging scalars (solver.h)");
+    SDBIE_HIP(hipMemcpyAsync(&h, stage, sizeof(h), hipMemcpyDeviceToHost, st));
     SDBIE_HIP(hipStreamSynchronize(st));
+    if (h.flag[0]) throw Error(SDBIE_ERR_NONFINITE, "non-finite node coordinates, normals or weights");
+    if (h.flag[1]) throw Error(SDBIE_ERR_ARG, "node coordinates must not exceed 1e15 in magnitude");
+    if (!(h.area > 0.0)) throw Error(SDBIE_ERR_ARG, "the quadrature weights sum to zero");
     P.near_pairs64 = (double)h.near[0];
     P.near_pairs32 = (double)h.near[1];
     P.area = h.area;
     for (int k = 0; lists && k < 3; ++k) P.sym[k].nblocks = h.blocks[k];
-    if (!(P.area > 0.0)) throw Error(SDBIE_ERR_ARG, "the quadrature weights sum to zero");
 }
 
 }  // namespace sdbie
