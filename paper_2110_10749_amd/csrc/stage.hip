@@ -127,10 +127,11 @@ __global__ __launch_bounds__(256) void k_morton(int64_t n, int64_t npow2, const 
 // ---- sorting network -----------------------------------------------------------
 // Bitonic steps (k, j) compare elements i and i ^ j; the lower one keeps the
 // smaller key where bit k of i is clear.  A block holds kSortBlock consecutive
-// keys, 8 to a thread: steps with j < 8 stay in registers, j < 512 pass keys
+// keys, 8 to a thread (with 8192 the passes of one block, bound by the LDS pipe,
+// took 21 to 32 us each: 132 us of sorting at n = 68166): steps with j < 8 stay in registers, j < 512 pass keys
 // between the lanes of a wave, the others through LDS.  Steps across blocks run
 // up to three to a launch, 8 keys to a thread.
-constexpr int kSortBlock = 8192, kSortThreads = kSortBlock / 8;
+constexpr int kSortBlock = 2048, kSortThreads = kSortBlock / 8;
 
 __device__ __forceinline__ uint64_t keep(uint64_t a, uint64_t b, bool smaller) {
     return (a < b) == smaller ? a : b;
@@ -298,7 +299,12 @@ __global__ __launch_bounds__(kTile) void k_stage(StageArgs a) {
         hi[c] = fmax(fmax(ub[0][2 * c + 1], ub[1][2 * c + 1]), fmax(ub[2][2 * c + 1], ub[3][2 * c + 1]));
         a.px32[c * npad + k] = (float)(xv[c] - 0.5 * (lo[c] + hi[c]));
     }
-    if (threadIdx.x < 6) a.boxes[(int64_t)blockIdx.x * 6 + threadIdx.x] = threadIdx.x & 1 ? hi[threadIdx.x >> 1] : lo[threadIdx.x >> 1];
+    if (threadIdx.x < 6) {
+        const int c = threadIdx.x;
+        double r = ub[0][c];
+        for (int k = 1; k < 4; ++k) r = c & 1 ? fmax(r, ub[k][c]) : fmin(r, ub[k][c]);
+        a.boxes[(int64_t)blockIdx.x * 6 + c] = r;
+    }
     if (threadIdx.x < 24) a.uboxes[(int64_t)blockIdx.x * 24 + threadIdx.x] = ub[threadIdx.x / 6][threadIdx.x % 6];
 }
 
@@ -361,11 +367,14 @@ __global__ __launch_bounds__(256) void k_mask_rows(int T, int64_t n, const doubl
         if (threadIdx.x == 0) part[a] = (shd[0] + shd[1]) + (shd[2] + shd[3]);
     }
     if (a >= T) return;
+    // wave v takes the 64-tile groups g = v, v + 4, ..; the counts stay in its scalars
+    __shared__ int cnt5[4][5], before[2048 / 64 + 1];
     const double* A = boxes + (int64_t)a * 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, groups = (T + 63) / 64;
     int c[5] = {0, 0, 0, 0, 0};
     unsigned long long c64 = 0, c32 = 0;
-    for (int b0 = 0; b0 < T; b0 += 256) {
-        const int b = b0 + threadIdx.x;
+    for (int g = wave; g < groups; g += 4) {
+        const int b = 64 * g + lane;
         const bool in = b < T;
         bool n64 = false, n32 = false;
         if (in) {
@@ -385,22 +394,33 @@ __global__ __launch_bounds__(256) void k_mask_rows(int T, int64_t n, const doubl
             if (n32) c32 += (unsigned long long)(ra * rb);
         }
         if (!rows) continue;
-        int t;
-        block_rank(in && b > a && n64, sh, t);
-        c[kRowNear64] += t;
-        block_rank(in && b > a && !n64, sh, t);
-        c[kRowFar64] += t;
-        const bool cf = in && b < a && !n64;
-        const int r = block_rank(cf, sh, t);
-        if (cf) colrank[(int64_t)a * T + b] = c[kRowColFar64] + r;
-        c[kRowColFar64] += t;
-        block_rank(in && b != a && n32, sh, t);
-        c[kRowNear32] += t;
-        block_rank(in && b > a && !n32, sh, t);
-        c[kRowFar32] += t;
+        const uint64_t cf = __ballot(in && b < a && !n64);
+        c[kRowNear64] += __popcll(__ballot(in && b > a && n64));
+        c[kRowFar64] += __popcll(__ballot(in && b > a && !n64));
+        c[kRowColFar64] += __popcll(cf);
+        c[kRowNear32] += __popcll(__ballot(in && b != a && n32));
+        c[kRowFar32] += __popcll(__ballot(in && b > a && !n32));
+        if (lane == 0) before[g + 1] = __popcll(cf);
     }
-    if (rows && threadIdx.x == 0)
-        for (int k = 0; k < 5; ++k) rows[(int64_t)a * kSymRowInts + k] = c[k];
+    if (rows) {
+        if (lane == 0)
+            for (int k = 0; k < 5; ++k) cnt5[wave][k] = c[k];
+        __syncthreads();
+        if (threadIdx.x < 5)
+            rows[(int64_t)a * kSymRowInts + threadIdx.x] =
+                cnt5[0][threadIdx.x] + cnt5[1][threadIdx.x] + cnt5[2][threadIdx.x] + cnt5[3][threadIdx.x];
+        if (threadIdx.x == 0) {
+            before[0] = 0;
+            for (int g = 0; g < groups; ++g) before[g + 1] += before[g];
+        }
+        __syncthreads();
+        for (int g = wave; g < groups && 64 * g < a; g += 4) {
+            const int b = 64 * g + lane;
+            const bool f = b < a && !m64[(int64_t)a * T + (b < T ? b : 0)];  // this wave's own writes
+            const uint64_t cf = __ballot(f);
+            if (f) colrank[(int64_t)a * T + b] = before[g] + __popcll(cf & ((1ull << lane) - 1));
+        }
+    }
     for (int off = 32; off > 0; off >>= 1) {
         c64 += __shfl_down(c64, off);
         c32 += __shfl_down(c32, off);
