@@ -11,11 +11,6 @@
 namespace sdbie {
 namespace {
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 // block of 256 lanes -> sum in lane 0 (fixed order)
 __device__ __forceinline__ double block_sum(double v, double* sh) {
@@ -29,14 +24,25 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
     return r;
 }
 
+// The reductions over kRedBlocks blocks launch only those that hold elements
+// (len / 256 of them, red_blocks); the first clears the others' partials.
+__device__ __forceinline__ void clear_partials(double* __restrict__ part) {
+    if (blockIdx.x == 0)
+        for (int b = gridDim.x + threadIdx.x; b < kRedBlocks; b += 256) part[b] = 0.0;
+}
+inline unsigned red_blocks(int64_t len) {
+    return len < (int64_t)kRedBlocks * 256 ? (unsigned)((len + 255) / 256) : (unsigned)kRedBlocks;
+}
+
 __global__ __launch_bounds__(256) void k_dot_partial(const double* __restrict__ a, const double* __restrict__ b,
                                                      int64_t len, double* __restrict__ part) {
     __shared__ double sh[4];
     double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < len; i += (int64_t)gridDim.x * 256)
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < len; i += (int64_t)kRedBlocks * 256)
         s += b ? a[i] * b[i] : a[i];
     const double r = block_sum(s, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = r;
+    clear_partials(part);
 }
 
 // part: [k][nb] -> out[j] = sum_b part[j][b], one block per j
@@ -74,6 +80,23 @@ __global__ __launch_bounds__(256) void k_multidot_partial(const double* __restri
     for (int c = 0; c < nc; ++c) {
         const double r = block_sum(acc[c], sh);
         if (threadIdx.x == 0) part[(int64_t)(j0 + c) * gridDim.x + blockIdx.x] = r;
+    }
+}
+
+// the same for chunks of at most 64 elements: a wave per chunk (the block's other
+// waves would add zeros), 128 blocks instead of 512
+__global__ __launch_bounds__(256) void k_multidot_small(const double* __restrict__ V, int64_t ld, int k,
+                                                        const double* __restrict__ w, int64_t len,
+                                                        double* __restrict__ part) {
+    const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t chunk = (len + kRedBlocks - 1) / kRedBlocks, i = b * chunk + lane;
+    const bool in = lane < chunk && i < len;
+    const double wi = in ? w[i] : 0.0;
+    const int j0 = blockIdx.y * kDotCols;
+    const int nc = k - j0 < kDotCols ? k - j0 : kDotCols;
+    for (int c = 0; c < nc; ++c) {
+        const double r = wave_sum(in ? V[(int64_t)(j0 + c) * ld + i] * wi : 0.0);
+        if (lane == 0) part[(int64_t)(j0 + c) * kRedBlocks + b] = r;
     }
 }
 
@@ -119,6 +142,9 @@ __device__ __forceinline__ double two_products(double a, double b, double c, dou
 // is turned into e = Q^T h and the subtracted vector is V (Q e): what the host
 // did between two copies, unfused multiplies and adds as there.
 // Block 0 writes h (with rot: e) to hout, host memory.
+// SMALL: chunks of at most 64 elements, a wave per chunk (as k_multidot_small):
+// the columns are then reduced by 128 blocks, not 512.
+template <bool SMALL>
 __global__ __launch_bounds__(256) void k_cgs_step(const double* __restrict__ Vs, int64_t lds, int ks,
                                                   const double* __restrict__ part_in, const double* __restrict__ rot,
                                                   double* __restrict__ hout, const double* __restrict__ Vd,
@@ -133,25 +159,48 @@ __global__ __launch_bounds__(256) void k_cgs_step(const double* __restrict__ Vs,
         const int kr = ks - 1;
         if (tid == 0) {
             const double *c = sc, *sn = sc + kr;
+            double cur = h[0];
+#pragma unroll 4
             for (int j = 0; j < kr; ++j) {
-                const double t = two_products(c[j], h[j], sn[j], h[j + 1]);
-                h[j + 1] = two_products(-sn[j], h[j], c[j], h[j + 1]);
-                h[j] = t;
+                const double nxt = h[j + 1];
+                h[j] = two_products(c[j], cur, sn[j], nxt);
+                cur = two_products(-sn[j], cur, c[j], nxt);
             }
             if (blockIdx.x == 0)
                 for (int j = 0; j < kr; ++j) hout[j] = h[j];
-            h[kr] = 0.0;
+            cur = 0.0;
+#pragma unroll 4
             for (int j = kr - 1; j >= 0; --j) {
-                const double t = two_products(c[j], h[j], -sn[j], h[j + 1]);
-                h[j + 1] = two_products(sn[j], h[j], c[j], h[j + 1]);
-                h[j] = t;
+                const double g = h[j];
+                h[j + 1] = two_products(sn[j], g, c[j], cur);
+                cur = two_products(c[j], g, -sn[j], cur);
             }
+            h[0] = cur;
         }
         __syncthreads();
     } else if (blockIdx.x == 0 && tid < ks) {
         hout[tid] = h[tid];
     }
-    const int64_t chunk = (len + gridDim.x - 1) / gridDim.x;
+    const int64_t chunk = (len + kRedBlocks - 1) / kRedBlocks;
+    if constexpr (SMALL) {
+        const int b = blockIdx.x * 4 + (tid >> 6), lane = tid & 63;
+        const int64_t i = b * chunk + lane;
+        const bool in = lane < chunk && i < len;
+        double wi = 0.0;
+        if (in) {
+            double s = 0.0;
+#pragma unroll 4
+            for (int j = 0; j < ks; ++j) s = fma(h[j], Vs[(int64_t)j * lds + i], s);
+            wi = w[i] - s;
+            w[i] = wi;
+        }
+#pragma unroll 4
+        for (int j = 0; j < kd; ++j) {
+            const double r = wave_sum(in ? Vd[(int64_t)j * ldd + i] * wi : 0.0);
+            if (lane == 0) part_out[(int64_t)j * kRedBlocks + b] = r;
+        }
+        return;
+    }
     const int64_t lo = (int64_t)blockIdx.x * chunk;
     const int64_t hi = lo + chunk < len ? lo + chunk : len;
     for (int64_t i = lo + tid; i < hi; i += 256) {
@@ -177,7 +226,8 @@ __global__ __launch_bounds__(256) void k_cgs_step(const double* __restrict__ Vs,
         }
         __syncthreads();
         if (tid < nc)
-            part_out[(int64_t)(j0 + tid) * gridDim.x + blockIdx.x] = (sh[tid][0] + sh[tid][1]) + (sh[tid][2] + sh[tid][3]);
+            part_out[(int64_t)(j0 + tid) * kRedBlocks + blockIdx.x] =
+                (sh[tid][0] + sh[tid][1]) + (sh[tid][2] + sh[tid][3]);
         __syncthreads();
     }
 }
@@ -190,8 +240,9 @@ __global__ __launch_bounds__(256) void k_cgs_last(const double* __restrict__ V, 
     reduce_columns(part_in, k, h);
     if (blockIdx.x == 0 && (int)threadIdx.x < k) hout[threadIdx.x] = h[threadIdx.x];
     double q = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < len; i += (int64_t)gridDim.x * 256) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < len; i += (int64_t)kRedBlocks * 256) {
         double s = 0.0;
+#pragma unroll 4
         for (int j = 0; j < k; ++j) s = fma(h[j], V[(int64_t)j * ld + i], s);
         const double wi = w[i] - s;
         w[i] = wi;
@@ -199,6 +250,7 @@ __global__ __launch_bounds__(256) void k_cgs_last(const double* __restrict__ V, 
     }
     const double r = block_sum(q, sh);
     if (threadIdx.x == 0) part_out[blockIdx.x] = r;
+    clear_partials(part_out);
 }
 
 // out = w / ||w|| (nothing when w = 0); the squared norm to hout
@@ -353,7 +405,7 @@ inline unsigned nblk(int64_t len) { return (unsigned)((len + 255) / 256); }
 }  // namespace
 
 void dev_dot(const Plan& P, const double* a, const double* b, int64_t len, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_dot_partial, dim3(kRedBlocks), dim3(256), 0, s, a, b, len, P.red);
+    hipLaunchKernelGGL(k_dot_partial, dim3(red_blocks(len)), dim3(256), 0, s, a, b, len, P.red);
     SDBIE_LAUNCHED();
     hipLaunchKernelGGL(k_reduce_cols, dim3(1), dim3(256), 0, s, (const double*)P.red, kRedBlocks, out);
     SDBIE_LAUNCHED();
@@ -374,22 +426,29 @@ void dev_cgs2(const Plan& P, const double* Vr, int kr, const double* rot, const 
     double* pa = P.red;           // two sets of block partials in turn
     double* pb = P.partial;       // free between the pair passes
     static_assert((size_t)(kFuseCols + 1) * kRedBlocks * sizeof(double) <= kMinPartial, "block partials in `partial`");
-    const dim3 grid(kRedBlocks), th(256);
+    const bool small = len <= (int64_t)kRedBlocks * 64;
+    const dim3 grid(small ? kRedBlocks / 4 : kRedBlocks), th(256);
     const int k0 = kr > 0 ? kr + 1 : k;
-    hipLaunchKernelGGL(k_multidot_partial, dim3(kRedBlocks, (unsigned)((k0 + kDotCols - 1) / kDotCols)), th, 0, s,
-                       kr > 0 ? Vr : V, len, k0, (const double*)w, len, pa);
+    const dim3 g0(grid.x, (unsigned)((k0 + kDotCols - 1) / kDotCols));
+    if (small)
+        hipLaunchKernelGGL(k_multidot_small, g0, th, 0, s, kr > 0 ? Vr : V, len, k0, (const double*)w, len, pa);
+    else
+        hipLaunchKernelGGL(k_multidot_partial, g0, th, 0, s, kr > 0 ? Vr : V, len, k0, (const double*)w, len, pa);
     SDBIE_LAUNCHED();
-    if (kr > 0) {
-        hipLaunchKernelGGL(k_cgs_step, grid, th, 0, s, Vr, len, kr + 1, (const double*)pa, rot, host + kHostE, V, len, k,
-                           w, len, pb);
+    auto step = [&](const double* Vs, int ks, const double* r, double* h) {
+        if (small)
+            hipLaunchKernelGGL((k_cgs_step<true>), grid, th, 0, s, Vs, len, ks, (const double*)pa, r, h, V, len, k, w,
+                               len, pb);
+        else
+            hipLaunchKernelGGL((k_cgs_step<false>), grid, th, 0, s, Vs, len, ks, (const double*)pa, r, h, V, len, k, w,
+                               len, pb);
         SDBIE_LAUNCHED();
         std::swap(pa, pb);
-    }
-    hipLaunchKernelGGL(k_cgs_step, grid, th, 0, s, V, len, k, (const double*)pa, (const double*)nullptr, host + kHostH1,
-                       V, len, k, w, len, pb);
-    SDBIE_LAUNCHED();
-    std::swap(pa, pb);
-    hipLaunchKernelGGL(k_cgs_last, grid, th, 0, s, V, len, k, (const double*)pa, host + kHostH2, w, len, pb);
+    };
+    if (kr > 0) step(Vr, kr + 1, rot, host + kHostE);
+    step(V, k, nullptr, host + kHostH1);
+    hipLaunchKernelGGL(k_cgs_last, dim3(red_blocks(len)), th, 0, s, V, len, k, (const double*)pa, host + kHostH2, w, len,
+                       pb);
     SDBIE_LAUNCHED();
     const unsigned sb = nblk(len) < kRedBlocks ? nblk(len) : kRedBlocks;
     hipLaunchKernelGGL(k_cgs_scale, dim3(sb), th, 0, s, (const double*)pb, host + kHostNorm, (const double*)w, next, len);
@@ -398,7 +457,7 @@ void dev_cgs2(const Plan& P, const double* Vr, int kr, const double* rot, const 
 
 double dev_dot_host(const Plan& P, const double* a, const double* b, int64_t len, hipStream_t s) {
     double* part = P.host_pinned + kHostDot;
-    hipLaunchKernelGGL(k_dot_partial, dim3(kRedBlocks), dim3(256), 0, s, a, b, len, part);
+    hipLaunchKernelGGL(k_dot_partial, dim3(red_blocks(len)), dim3(256), 0, s, a, b, len, part);
     SDBIE_LAUNCHED();
     SDBIE_HIP(hipStreamSynchronize(s));
     // k_reduce_cols' order

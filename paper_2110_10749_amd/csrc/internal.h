@@ -12,6 +12,25 @@
 
 namespace sdbie {
 
+// Sum over a wave, every lane the same: lanes 32, 16, 8, 4, 2 and 1 apart.  The last
+// four steps are DPP moves; after the step of 8, lane l +- 4 of a row hold the same
+// value, so the direction of the rotation by 4 does not matter.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+    return v + __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    v += __shfl_xor(v, 32, 64);
+    v += __shfl_xor(v, 16, 64);
+    v = dpp_add<0x128>(v);        // row_ror:8
+    v = dpp_add<0x124>(v);        // row_ror:4
+    v = dpp_add<0x4e>(v);         // quad_perm [2, 3, 0, 1]
+    return dpp_add<0xb1>(v);      // quad_perm [1, 0, 3, 2]
+}
+
 // Error carried inside the library; converted to a status code at the C ABI.
 struct Error : std::runtime_error {
     int code;

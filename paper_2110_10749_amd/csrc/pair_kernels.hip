@@ -178,6 +178,101 @@ __device__ __forceinline__ void near_factors(T r2, T inv_r, T id, T id2, T& k1, 
     }
 }
 
+// near_factors for N pairs of a lane at once (double): k1 .. k4 hold the plain
+// factors on entry and are replaced where r2 < rc2.  One pair after the other,
+// each polynomial waits for its scalar coefficient loads and then runs one
+// dependent chain of fmas; N pairs share the loads and run N chains.  The closed
+// forms are evaluated for every lane once one lane needs them (lanes outside
+// their range keep other values), the series when one lane is that close; each
+// value is formed by the operations of near_factors.
+template <int N, int M>
+__device__ __forceinline__ void horner_n(const double (&tab)[M], const double (&x)[N], double (&a)[N]) {
+    cdouble* c = (cdouble*)tab;
+    asm volatile("" : "+s"(c));
+#pragma unroll
+    for (int u = 0; u < N; ++u) a[u] = c[M - 1];
+#pragma unroll
+    for (int i = M - 2; i >= 0; --i)
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            double r;
+            asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a[u]), "v"(x[u]), "s"(c[i]));
+            a[u] = r;
+        }
+}
+
+template <int N, bool K1, bool K2, bool K3, bool K4>
+__device__ __forceinline__ void near_factors_n(const double (&r2)[N], const double (&inv_r)[N], double id, double id2,
+                                               double rc2, double (&k1)[N], double (&k2)[N], double (&k3)[N],
+                                               double (&k4)[N]) {
+    double x[N];
+    bool in[N], ser[N], any_in = false, any_ser = false;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        x[u] = r2[u] * id2;
+        in[u] = r2[u] < rc2;
+        ser[u] = in[u] && x[u] < Consts<double>::rho_s2;
+        any_in = any_in || in[u];
+        any_ser = any_ser || ser[u];
+    }
+    if (!__any(any_in)) return;
+    {
+        constexpr double kLog2e = 1.44269504088896340736;
+        constexpr double kLn2Hi = 0.693147180559945309417, kLn2Lo = 2.319046813846299558e-17;
+        double n[N], mr[N], E[N], t[N], ec[N], rho[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            rho[u] = r2[u] * inv_r[u] * id;
+            n[u] = rint(x[u] * kLog2e);
+            double r = fma(-n[u], kLn2Hi, x[u]);
+            r = fma(-n[u], kLn2Lo, r);
+            mr[u] = -r;
+            t[u] = rcp_t(fma(SDBIE_ERFCX_P, rho[u], 1.0));
+        }
+        horner_n<N>(kExpTaylor, mr, E);
+        horner_n<N>(kERFCX_F64, t, ec);
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const double e = ldexp(E[u], -(int)n[u]);
+            const double ef = fma(-e, ec[u], 1.0);
+            const double cE = kTwoOverSqrtPi * rho[u] * e;
+            const double ir2 = inv_r[u] * inv_r[u];
+            const double third = 1.0 / 3.0;
+            const bool c = in[u] && !ser[u];
+            if (K1) k1[u] = c ? (ef - cE * third * (2.0 * x[u] - 5.0)) * inv_r[u] : k1[u];
+            if (K2) k2[u] = c ? (ef + cE * third * (2.0 * x[u] - 3.0)) * inv_r[u] * ir2 : k2[u];
+            if (K3) k3[u] = c ? (ef - cE * third * ((4.0 * x[u] - 14.0) * x[u] + 3.0)) * inv_r[u] * ir2 : k3[u];
+            if (K4)
+                k4[u] = c ? (ef - cE * (1.0 / 9.0) * (((8.0 * x[u] - 36.0) * x[u] + 6.0) * x[u] + 9.0)) * inv_r[u] *
+                                ir2 * ir2
+                          : k4[u];
+        }
+    }
+    if (!__any(any_ser)) return;
+    const double id3 = id * id2;
+    double f[N];
+    if (K1) {
+        horner_n<N>(kF1_F64, x, f);
+#pragma unroll
+        for (int u = 0; u < N; ++u) k1[u] = ser[u] ? f[u] * id : k1[u];
+    }
+    if (K2) {
+        horner_n<N>(kF2_F64, x, f);
+#pragma unroll
+        for (int u = 0; u < N; ++u) k2[u] = ser[u] ? f[u] * id3 : k2[u];
+    }
+    if (K3) {
+        horner_n<N>(kF3_F64, x, f);
+#pragma unroll
+        for (int u = 0; u < N; ++u) k3[u] = ser[u] ? f[u] * id3 : k3[u];
+    }
+    if (K4) {
+        horner_n<N>(kF4_F64, x, f);
+#pragma unroll
+        for (int u = 0; u < N; ++u) k4[u] = ser[u] ? f[u] * id3 * id2 : k4[u];
+    }
+}
+
 struct KArgs {
     int64_t n;          // real nodes (targets and sources)
     int64_t npad;       // ntiles * kTile
@@ -207,6 +302,7 @@ struct KArgs {
     double* gather_dst;
     const int32_t* perm;
     int gather_c;
+    int near_waves;  // near_small_body: waves per 64 targets
     const double* dl_tgt;  // target density of the subtracted double layer (nullable: dl_dens)
     // position-gradient pass
     const double *g_p, *g_v, *g_u, *g_f, *g_l1, *g_l2;
@@ -320,8 +416,18 @@ struct LaplaceOp {
         const T dx = xi - r[0], dy = yi - r[1], dz = zi - r[2];
         const T r2 = fma(dx, dx, fma(dy, dy, dz * dz));
         const T inv_r = rsq_pair<NEAR>(r2);
-        T k1 = inv_r, k2 = inv_r * inv_r * inv_r, k3, k4;
+        T k1 = inv_r, k2 = inv_r * inv_r * inv_r, k3 = T(0), k4 = T(0);
         if (NEAR && r2 < rc2) near_factors<T, SL, DL, false, false>(r2, inv_r, id, id2, k1, k2, k3, k4);
+        terms(r, dx, dy, dz, k1, k2, k3, k4);
+    }
+    // smoothed factors the pairs use, and the plain ones
+    static constexpr bool K1 = SL, K2 = DL, K3 = false, K4 = false;
+    __device__ __forceinline__ static void plain(T inv_r, T& k1, T& k2, T&, T&) {
+        k1 = inv_r;
+        k2 = inv_r * inv_r * inv_r;
+    }
+    template <class P>
+    __device__ __forceinline__ void terms(P r, T dx, T dy, T dz, T k1, T k2, T, T) {
         if (DL) {
             const T dn = fma(dx, r[NX], fma(dy, r[NY], dz * r[NZ]));
             tacc = fma((r[Q] - qi) * dn, k2, tacc);
@@ -332,6 +438,12 @@ struct LaplaceOp {
         acc += (double)tacc;
         tacc = T(0);
     }
+    // the double sums out (and cleared), and back in
+    __device__ __forceinline__ void take(double (&v)[C]) {
+        v[0] = acc;
+        acc = 0.0;
+    }
+    __device__ __forceinline__ void give(const double (&v)[C]) { acc = v[0]; }
     __device__ __forceinline__ void store(const KArgs& a, int slot, int64_t i) const {
         a.partial[(int64_t)slot * a.n + i] = acc;
     }
@@ -434,8 +546,19 @@ struct StokesOp {
             tz = fma(fma(c, dz, fz), inv_r, tz);
             return;
         }
-        T k1 = inv_r, k2, k3 = inv_r * ir2, k4 = k3 * ir2;
+        T k1 = inv_r, k2 = T(0), k3 = inv_r * ir2, k4 = k3 * ir2;
         if (NEAR && r2 < rc2) near_factors<T, SL, false, SL, DL>(r2, inv_r, id, id2, k1, k2, k3, k4);
+        terms(r, dx, dy, dz, k1, k2, k3, k4);
+    }
+    static constexpr bool K1 = SL, K2 = false, K3 = SL, K4 = DL;
+    __device__ __forceinline__ static void plain(T inv_r, T& k1, T&, T& k3, T& k4) {
+        const T ir2 = inv_r * inv_r;
+        k1 = inv_r;
+        k3 = inv_r * ir2;
+        k4 = k3 * ir2;
+    }
+    template <class P>
+    __device__ __forceinline__ void terms(P r, T dx, T dy, T dz, T k1, T, T k3, T k4) {
         T cd = T(0);
         if (DL) {
             const T ux = r[UX] - uix, uy = r[UY] - uiy, uz = r[UZ] - uiz;
@@ -459,6 +582,17 @@ struct StokesOp {
         ay += (double)ty;
         az += (double)tz;
         tx = ty = tz = T(0);
+    }
+    __device__ __forceinline__ void take(double (&v)[C]) {
+        v[0] = ax;
+        v[1] = ay;
+        v[2] = az;
+        ax = ay = az = 0.0;
+    }
+    __device__ __forceinline__ void give(const double (&v)[C]) {
+        ax = v[0];
+        ay = v[1];
+        az = v[2];
     }
     __device__ __forceinline__ void store(const KArgs& a, int slot, int64_t i) const {
         double* o = a.partial + (int64_t)slot * 3 * a.n;
@@ -501,8 +635,14 @@ struct LaplaceTNOp {
         const T dx = xi - r[0], dy = yi - r[1], dz = zi - r[2];
         const T r2 = fma(dx, dx, fma(dy, dy, dz * dz));
         const T inv_r = rsq_pair<NEAR>(r2);
-        T k1, k2 = inv_r * inv_r * inv_r, k3, k4;
+        T k1 = T(0), k2 = inv_r * inv_r * inv_r, k3 = T(0), k4 = T(0);
         if (NEAR && r2 < rc2) near_factors<T, false, true, false, false>(r2, inv_r, id, id2, k1, k2, k3, k4);
+        terms(r, dx, dy, dz, k1, k2, k3, k4);
+    }
+    static constexpr bool K1 = false, K2 = true, K3 = false, K4 = false;
+    __device__ __forceinline__ static void plain(T inv_r, T&, T& k2, T&, T&) { k2 = inv_r * inv_r * inv_r; }
+    template <class P>
+    __device__ __forceinline__ void terms(P r, T dx, T dy, T dz, T, T k2, T, T) {
         const T dn = fma(dx, nxi, fma(dy, nyi, dz * nzi));
         tacc = fma(r[3] * dn, k2, tacc);
     }
@@ -510,6 +650,12 @@ struct LaplaceTNOp {
         acc += (double)tacc;
         tacc = T(0);
     }
+    // the double sums out (and cleared), and back in
+    __device__ __forceinline__ void take(double (&v)[C]) {
+        v[0] = acc;
+        acc = 0.0;
+    }
+    __device__ __forceinline__ void give(const double (&v)[C]) { acc = v[0]; }
     __device__ __forceinline__ void store(const KArgs& a, int slot, int64_t i) const {
         a.partial[(int64_t)slot * a.n + i] = acc;
     }
@@ -547,8 +693,17 @@ struct StokesTNOp {
         const T r2 = fma(dx, dx, fma(dy, dy, dz * dz));
         const T inv_r = rsq_pair<NEAR>(r2);
         const T ir2 = inv_r * inv_r;
-        T k1, k2, k3, k4 = inv_r * ir2 * ir2;
+        T k1 = T(0), k2 = T(0), k3 = T(0), k4 = inv_r * ir2 * ir2;
         if (NEAR && r2 < rc2) near_factors<T, false, false, false, true>(r2, inv_r, id, id2, k1, k2, k3, k4);
+        terms(r, dx, dy, dz, k1, k2, k3, k4);
+    }
+    static constexpr bool K1 = false, K2 = false, K3 = false, K4 = true;
+    __device__ __forceinline__ static void plain(T inv_r, T&, T&, T&, T& k4) {
+        const T ir2 = inv_r * inv_r;
+        k4 = inv_r * ir2 * ir2;
+    }
+    template <class P>
+    __device__ __forceinline__ void terms(P r, T dx, T dy, T dz, T, T, T, T k4) {
         const T dq = fma(dx, r[3], fma(dy, r[4], dz * r[5]));
         const T c = dq * fma(dx, nxi, fma(dy, nyi, dz * nzi)) * k4;
         tx = fma(c, dx, tx);
@@ -560,6 +715,17 @@ struct StokesTNOp {
         ay += (double)ty;
         az += (double)tz;
         tx = ty = tz = T(0);
+    }
+    __device__ __forceinline__ void take(double (&v)[C]) {
+        v[0] = ax;
+        v[1] = ay;
+        v[2] = az;
+        ax = ay = az = 0.0;
+    }
+    __device__ __forceinline__ void give(const double (&v)[C]) {
+        ax = v[0];
+        ay = v[1];
+        az = v[2];
     }
     __device__ __forceinline__ void store(const KArgs& a, int slot, int64_t i) const {
         double* o = a.partial + (int64_t)slot * 3 * a.n;
@@ -598,8 +764,19 @@ struct StokesTNSLOp {
         const T r2 = fma(dx, dx, fma(dy, dy, dz * dz));
         const T inv_r = rsq_pair<NEAR>(r2);
         const T ir2 = inv_r * inv_r;
-        T k1 = inv_r, k2, k3 = inv_r * ir2, k4 = k3 * ir2;
+        T k1 = inv_r, k2 = T(0), k3 = inv_r * ir2, k4 = k3 * ir2;
         if (NEAR && r2 < rc2) near_factors<T, true, false, true, true>(r2, inv_r, id, id2, k1, k2, k3, k4);
+        terms(r, dx, dy, dz, k1, k2, k3, k4);
+    }
+    static constexpr bool K1 = true, K2 = false, K3 = true, K4 = true;
+    __device__ __forceinline__ static void plain(T inv_r, T& k1, T&, T& k3, T& k4) {
+        const T ir2 = inv_r * inv_r;
+        k1 = inv_r;
+        k3 = inv_r * ir2;
+        k4 = k3 * ir2;
+    }
+    template <class P>
+    __device__ __forceinline__ void terms(P r, T dx, T dy, T dz, T k1, T, T k3, T k4) {
         const T dq = fma(dx, r[3], fma(dy, r[4], dz * r[5]));
         const T c = dq * fma(dx, nxi, fma(dy, nyi, dz * nzi)) * k4;
         tx = fma(c, dx, tx);
@@ -618,6 +795,23 @@ struct StokesTNSLOp {
         by += (double)sy;
         bz += (double)sz;
         tx = ty = tz = sx = sy = sz = T(0);
+    }
+    __device__ __forceinline__ void take(double (&v)[C]) {
+        v[0] = ax;
+        v[1] = ay;
+        v[2] = az;
+        v[3] = bx;
+        v[4] = by;
+        v[5] = bz;
+        ax = ay = az = bx = by = bz = 0.0;
+    }
+    __device__ __forceinline__ void give(const double (&v)[C]) {
+        ax = v[0];
+        ay = v[1];
+        az = v[2];
+        bx = v[3];
+        by = v[4];
+        bz = v[5];
     }
     __device__ __forceinline__ void store(const KArgs& a, int slot, int64_t i) const {
         double* o = a.partial + (int64_t)slot * 6 * a.n;
@@ -787,12 +981,6 @@ struct GradOp {
 
 static_assert(GradOp<false>::R * sizeof(double) <= kRecBytes, "record larger than its workspace slot");
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 // sum of a 256-thread block (all lanes), the waves' sums added as (0 + 1) + (2 + 3)
 __device__ __forceinline__ double block_sum(double v) {
     __shared__ double sh[4];
@@ -815,6 +1003,9 @@ __global__ __launch_bounds__(256) void pack_sources(KArgs a) {
         for (int64_t i = j; i < a.comp_len; i += (int64_t)kRedBlocks * 256) s += a.comp_a[i] * a.comp_b[i];
         s = block_sum(s);
         if (threadIdx.x == 0) a.comp_part[blockIdx.x] = s;
+        // blocks past the launch hold no elements
+        if (blockIdx.x == 0)
+            for (int b = gridDim.x + threadIdx.x; b < kRedBlocks; b += 256) a.comp_part[b] = 0.0;
     }
     if (j >= a.npad) return;
     if (a.gather_src && j < a.n) {
@@ -1033,6 +1224,134 @@ __device__ __forceinline__ void near_body(const KArgs& a, int blk) {
     if (i < a.n) op.store(a, a.nsplit + split, i);
 }
 
+#ifndef SDBIE_NEAR_GROUP
+#define SDBIE_NEAR_GROUP 2
+#endif
+constexpr int kNearGroup = SDBIE_NEAR_GROUP;
+// N near pairs of a lane at once (double), added in the records' order
+template <class Op, int N>
+__device__ __forceinline__ void near_group(Op& op, src_ptr<double> r, double id, double id2, double rc2) {
+    double dx[N], dy[N], dz[N], r2[N], ir[N], k1[N], k2[N], k3[N], k4[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const src_ptr<double> q = r + u * Op::R;
+        dx[u] = op.xi - q[0];
+        dy[u] = op.yi - q[1];
+        dz[u] = op.zi - q[2];
+        r2[u] = fma(dx[u], dx[u], fma(dy[u], dy[u], dz[u] * dz[u]));
+        ir[u] = rsq(r2[u]);
+        k1[u] = k2[u] = k3[u] = k4[u] = 0.0;
+        Op::plain(ir[u], k1[u], k2[u], k3[u], k4[u]);
+    }
+    near_factors_n<N, Op::K1, Op::K2, Op::K3, Op::K4>(r2, ir, id, id2, rc2, k1, k2, k3, k4);
+#pragma unroll
+    for (int u = 0; u < N; ++u) op.terms(r + u * Op::R, dx[u], dy[u], dz[u], k1[u], k2[u], k3[u], k4[u]);
+}
+
+// Near-field pass of small surfaces: the same sums in the same order, with W = 2
+// or 4 waves on that many of the split's units at a time instead of one unit
+// after the other.  Each group of W waves owns 64 targets of one split; its waves
+// leave each unit's sums (in float: each 16-term block's) in LDS and the first of
+// them adds them in unit order.  With fewer near-field waves than the chip holds a pass takes as
+// long as one wave's chain of units (n = 2650: two units of 64 smoothed pairs,
+// 91 us for a double Stokes double layer; n = 9582 with 8 splits: a dozen units,
+// 530 us for a double single layer); the double steps also run two pairs at a
+// time, since registers are no limit there.
+template <class Op, typename T>
+__device__ __forceinline__ void near_small_body(const KArgs& a, int blk) {
+    constexpr int C = Op::C;
+    constexpr int NU = sizeof(T) == 8 ? kNearGroup : Op::U, FU = Op::U > 1 ? Op::U / 2 : 1;
+    constexpr int B = block_terms<T>() < kNearUnit ? block_terms<T>() : kNearUnit, NB = kNearUnit / B;
+    static_assert(B % NU == 0 && B % FU == 0, "blocks of whole unrolled steps");
+    constexpr int kWaves = kTPB / 64, kUnits = kTile / kNearUnit;
+    static_assert(kWaves == kUnits, "the groups of a block own units of one tile");
+    __shared__ double sh[kWaves][NB][C][64];
+    const int lane = threadIdx.x & 63, bwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int W = a.near_waves, group = bwave / W, wave = bwave % W;
+    const int split = blk % a.nsplit, tu = blk / a.nsplit * (kWaves / W) + group;  // target unit
+    const int b = tu / kUnits;
+    const int64_t w0 = (int64_t)tu * 64, i = w0 + lane;  // < npad
+    Op op;
+    op.init(a, i);
+    T x0[3] = {};
+    own_frame<T>(op, x0);
+    const T id = T(a.inv_delta), id2 = id * id, rc2 = T(a.rc2);
+    const bool wave_full = w0 + 64 <= a.n;
+    const src_ptr<double> wb = (src_ptr<double>)a.uboxes + (int64_t)tu * 6;
+    const uint8_t* row = a.mask + (int64_t)b * a.ntiles;
+    const src_ptr<T> rec = (src_ptr<T>)a.rec;
+    double sum[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) sum[c] = 0.0;
+    // the first m units of the round, in order
+    auto add_round = [&](int m) {
+        __syncthreads();
+        if (wave == 0)
+            for (int u = 0; u < m; ++u)
+#pragma unroll
+                for (int k = 0; k < NB; ++k)
+#pragma unroll
+                    for (int c = 0; c < C; ++c) sum[c] += sh[bwave + u][k][c][lane];
+        __syncthreads();
+    };
+    int rank = 0, m = 0;  // near tiles seen; units of this split in the round
+    for (int c0 = 0; c0 < a.ntiles; c0 += 64) {
+        const bool f = (c0 + lane < a.ntiles) && row[c0 + lane];
+        uint64_t bal = __ballot(f);  // uniform
+        while (bal) {
+            const int t = c0 + __ffsll((long long)bal) - 1;
+            bal &= bal - 1;
+            for (int q = 0; q < kUnits; ++q) {
+                if ((rank * kUnits + q) % a.nsplit != split) continue;
+                if (m == wave) {
+                    targets_to_frame<T>(op, a, x0, b, t);
+                    const int64_t u0 = (int64_t)t * kTile + q * kNearUnit;
+                    const src_ptr<T> ru = rec + u0 * Op::R;
+                    bool far_unit = wave_full && u0 + kNearUnit <= a.n;
+                    if (far_unit) {
+                        const src_ptr<double> ub = (src_ptr<double>)a.uboxes + (u0 / kNearUnit) * 6;
+                        double d2 = 0.0;
+                        for (int c = 0; c < 3; ++c) {
+                            const double gap = fmax(0.0, fmax(wb[2 * c] - ub[2 * c + 1], ub[2 * c] - wb[2 * c + 1]));
+                            d2 += gap * gap;
+                        }
+                        far_unit = d2 >= a.rcu2;
+                    }
+#pragma unroll 1
+                    for (int k = 0; k < NB; ++k) {
+                        if (far_unit) {
+#pragma unroll 1
+                            for (int jj = k * B; jj < (k + 1) * B; jj += FU)
+                                pair_group<Op, T, false, FU>(op, ru + jj * Op::R, id, id2, rc2);
+                        } else {
+#pragma unroll 1
+                            for (int jj = k * B; jj < (k + 1) * B; jj += NU) {
+                                if constexpr (sizeof(T) == 8) near_group<Op, NU>(op, ru + jj * Op::R, id, id2, rc2);
+                                else pair_group<Op, T, true, NU>(op, ru + jj * Op::R, id, id2, rc2);
+                            }
+                        }
+                        op.flush();
+                        double v[C];
+                        op.take(v);
+#pragma unroll
+                        for (int c = 0; c < C; ++c) sh[bwave][k][c][lane] = v[c];
+                    }
+                }
+                if (++m == W) {
+                    add_round(W);
+                    m = 0;
+                }
+            }
+            ++rank;
+        }
+    }
+    add_round(m);
+    if (wave == 0 && i < a.n) {
+        op.give(sum);
+        op.store(a, a.nsplit + split, i);
+    }
+}
+
 template <class Op, typename T>
 __global__ __launch_bounds__(kTPB) void near_pairs(KArgs a) {
     near_body<Op, T>(a, blockIdx.x);
@@ -1062,6 +1381,18 @@ __global__ __launch_bounds__(kTPB) __attribute__((amdgpu_waves_per_eu(8))) void 
     const int nfar = a.ntiles * a.nsplit;
     if ((int)blockIdx.x < nfar) far_body<Op, T>(a, blockIdx.x);
     else near_body<Op, T>(a, (int)blockIdx.x - nfar);
+}
+
+// Both with the near-field blocks of small surfaces (near_waves times as many).
+template <class Op, typename T>
+__global__ __launch_bounds__(kTPB) void pass_pairs_small(KArgs a) {
+    const int nfar = a.ntiles * a.nsplit;
+    if ((int)blockIdx.x < nfar) {
+        if constexpr (sizeof(T) == 4 && SDBIE_FAR_LDS) far_lds_body<Op>(a, blockIdx.x);
+        else far_body<Op, T>(a, blockIdx.x);
+    } else {
+        near_small_body<Op, T>(a, (int)blockIdx.x - nfar);
+    }
 }
 
 // The same without the wave target (position-gradient passes).
@@ -1604,6 +1935,11 @@ __global__ __launch_bounds__(kTPB) void sym_far_near_pairs(KArgs a, SymArgs sa) 
     if ((int)blockIdx.x < sa.nblocks) sym_body<Sym, double, false>(a, sa, blockIdx.x);
     else near_body<Op, double>(a, (int)blockIdx.x - sa.nblocks);
 }
+template <class Op, class Sym>
+__global__ __launch_bounds__(kTPB) void sym_far_near_small(KArgs a, SymArgs sa) {
+    if ((int)blockIdx.x < sa.nblocks) sym_body<Sym, double, false>(a, sa, blockIdx.x);
+    else near_small_body<Op, double>(a, (int)blockIdx.x - sa.nblocks);
+}
 
 // Sum of the symmetric pass per target, in a fixed order, then the terms of
 // epilogue(): the forward slots of its tile's blocks, the reverse slots of the
@@ -1643,6 +1979,8 @@ __global__ __launch_bounds__(kEpiThreads) void sym_epilogue(
     if (g == 0 && i < n) epi_finish<C>(n, i, v, tw, base, base_scale, comp != nullptr, cs, nrm, add0, add1, add2, out, perm);
 }
 
+int near_waves(const Plan& P, bool mixed);
+
 KArgs make_args(const Plan& P, const PassDesc& d, int nsplit, double cut, int comps) {
     KArgs a;
     a.n = P.n;
@@ -1677,6 +2015,7 @@ KArgs make_args(const Plan& P, const PassDesc& d, int nsplit, double cut, int co
     a.gather_dst = d.gather_dst;
     a.perm = P.perm;
     a.gather_c = comps;
+    a.near_waves = near_waves(P, d.mixed);
     a.g_p = a.g_v = a.g_u = a.g_f = a.g_l1 = a.g_l2 = nullptr;
     a.g_mu = a.g_K = 1.0;
     return a;
@@ -1686,6 +2025,19 @@ template <class Op>
 struct family_is_gradient { static constexpr bool value = false; };
 template <bool SWAP>
 struct family_is_gradient<GradOp<SWAP>> { static constexpr bool value = true; };
+
+// Waves on one target unit's near units: more than one when the near blocks of a
+// pass (four waves each) leave wave slots of the chip empty (256 CUs, 32 waves
+// each) and a split holds more than one near unit on average, so that there is a
+// chain to cut; as many as there are units, since a wave without one only holds
+// registers.  Double, coupled solve at n = 2650 (32 splits, 1.3 units each): 77 ms
+// with one wave, 58 with two, 64 with four; drag gradient at n = 4302 (64
+// splits, 1.06 units each): 210, -, 237 ms.
+int near_waves(const Plan& P, bool mixed) {
+    if ((int64_t)P.ntiles * P.nsplit * 4 >= 256 * 32) return 1;
+    const double units = (mixed ? P.near_pairs32 : P.near_pairs64) / ((double)P.n * kNearUnit) / P.nsplit;
+    return units > 2.2 ? 4 : units > 1.15 ? 2 : 1;
+}
 
 const SymSet& sym_set(const Plan& P, bool mixed) {
     return P.sym[mixed ? kSymF32 : P.far_only64 ? kSymFar64 : kSymF64];
@@ -1704,9 +2056,11 @@ bool launch_pair_kernels(const Plan& P, const KArgs& a, hipStream_t st, int fami
     const double near = mixed ? P.near_pairs32 : P.near_pairs64;
     {
         ProfScope prof(prof_variant(family, mixed, code, 2), 0.0, st);
-        const int64_t pb = a.npad / 256;
-        hipLaunchKernelGGL((pack_sources<Op, T>), dim3((unsigned)(a.comp_a && pb < kRedBlocks ? kRedBlocks : pb)),
-                           dim3(256), 0, st, a);
+        // as many blocks as hold sources or elements of the completion's dot product
+        int64_t pb = a.npad / 256, cb = a.comp_a ? (a.comp_len + 255) / 256 : 0;
+        if (cb > kRedBlocks) cb = kRedBlocks;
+        if (cb > pb) pb = cb;
+        hipLaunchKernelGGL((pack_sources<Op, T>), dim3((unsigned)pb), dim3(256), 0, st, a);
         SDBIE_LAUNCHED();
     }
     using Sym = typename SymOf<Op>::type;
@@ -1723,8 +2077,14 @@ bool launch_pair_kernels(const Plan& P, const KArgs& a, hipStream_t st, int fami
             ProfScope prof(prof_variant(family, mixed, code, 4), all, st);
             if constexpr (sizeof(T) == 8) {
                 if (P.far_only64) {
-                    hipLaunchKernelGGL((sym_far_near_pairs<Op, Sym>),
-                                       dim3((unsigned)(sa.nblocks + a.ntiles * a.nsplit)), dim3(kTPB), 0, st, a, sa);
+                    if (a.near_waves > 1)
+                        hipLaunchKernelGGL((sym_far_near_small<Op, Sym>),
+                                           dim3((unsigned)(sa.nblocks + a.near_waves * a.ntiles * a.nsplit)), dim3(kTPB), 0, st,
+                                           a, sa);
+                    else
+                        hipLaunchKernelGGL((sym_far_near_pairs<Op, Sym>),
+                                           dim3((unsigned)(sa.nblocks + a.ntiles * a.nsplit)), dim3(kTPB), 0, st, a,
+                                           sa);
                     SDBIE_LAUNCHED();
                     return true;
                 }
@@ -1738,10 +2098,12 @@ bool launch_pair_kernels(const Plan& P, const KArgs& a, hipStream_t st, int fami
     if constexpr (SDBIE_ONE_LAUNCH) {
         // far and near blocks in one launch (timed as one kernel, all N^2 pairs)
         ProfScope prof(prof_variant(family, mixed, code, 3), all, st);
-        if constexpr (sizeof(T) == 4 && SDBIE_FAR_LDS)
-            hipLaunchKernelGGL((pass_pairs_lds<Op>), dim3(2 * grid.x), dim3(kTPB), 0, st, a);
-        else if constexpr (family_is_gradient<Op>::value)
+        if constexpr (family_is_gradient<Op>::value)
             hipLaunchKernelGGL((pass_pairs_wide<Op, T>), dim3(2 * grid.x), dim3(kTPB), 0, st, a);
+        else if (a.near_waves > 1)
+            hipLaunchKernelGGL((pass_pairs_small<Op, T>), dim3((1 + a.near_waves) * grid.x), dim3(kTPB), 0, st, a);
+        else if constexpr (sizeof(T) == 4 && SDBIE_FAR_LDS)
+            hipLaunchKernelGGL((pass_pairs_lds<Op>), dim3(2 * grid.x), dim3(kTPB), 0, st, a);
         else
             hipLaunchKernelGGL((pass_pairs<Op, T>), dim3(2 * grid.x), dim3(kTPB), 0, st, a);
         SDBIE_LAUNCHED();
