@@ -130,6 +130,52 @@ def erfcx_fit(lo, hi, p, deg, ctype):
     return coef, worst
 
 
+def erfcx_weighted_fit(lo, hi, p, deg):
+    """Coefficients (low to high) of g(t), t = 1/(1 + p rho), with exp(-rho^2) g
+    ~ erfc(rho) on [lo, hi]: least squares of that absolute error at Chebyshev
+    points of the t interval in 60-digit arithmetic.  erf = 1 - exp(-rho^2) g
+    only sees the error times exp(-rho^2), so three degrees less than the fit of
+    g itself keep erf at the rounding of double.  Returns (coefficients, max
+    absolute error of exp(-rho^2) g)."""
+    with mp.workdps(60):
+        tlo, thi = 1 / (1 + p * mp.mpf(hi)), 1 / (1 + p * mp.mpf(lo))
+        tm, th = (tlo + thi) / 2, (thi - tlo) / 2
+        m = 12 * (deg + 1)
+        rows = []
+        for k in range(m):
+            t = tm + th * mp.cos(mp.pi * (k + mp.mpf(1) / 2) / m)
+            rho = (1 / t - 1) / p
+            rows.append((t, mp.exp(-rho * rho), mp.erfc(rho)))
+        N, r = mp.zeros(deg + 1, deg + 1), mp.zeros(deg + 1, 1)
+        for t, w, f in rows:
+            b = [w * t ** j for j in range(deg + 1)]
+            for i in range(deg + 1):
+                r[i] += b[i] * f
+                for j in range(i + 1):
+                    N[i, j] += b[i] * b[j]
+        for i in range(deg + 1):
+            for j in range(i):
+                N[j, i] = N[i, j]
+        c = mp.lu_solve(N, r)
+        coef = [c[j] for j in range(deg + 1)]
+        worst = max(abs(w * sum(coef[j] * t ** j for j in range(deg + 1)) - f) for t, w, f in rows)
+    return coef, float(worst)
+
+
+def exp_fit(deg):
+    """Coefficients of a polynomial ~ e^y on |y| <= ln(2)/2 (interpolation at
+    the Chebyshev points), and its max relative error on a grid."""
+    with mp.workdps(60):
+        h = mp.log(2) / 2
+        nodes = [h * mp.cos(mp.pi * (k + mp.mpf(1) / 2) / (deg + 1)) for k in range(deg + 1)]
+        A = mp.matrix([[y ** j for j in range(deg + 1)] for y in nodes])
+        c = mp.lu_solve(A, mp.matrix([mp.exp(y) for y in nodes]))
+        coef = [c[j] for j in range(deg + 1)]
+        worst = max(abs(sum(coef[j] * y ** j for j in range(deg + 1)) / mp.exp(y) - 1)
+                    for y in [h * (mp.mpf(k) / 200 - 1) for k in range(401)])
+    return coef, float(worst)
+
+
 def emit_plain(name, vals, ctype, suffix):
     body = ",\n    ".join(mp.nstr(v, 25, min_fixed=-1, max_fixed=-1) + suffix for v in vals)
     return f"static constexpr int {name}_N = {len(vals)};\n" \
@@ -164,6 +210,10 @@ def main():
     g64, e64 = erfcx_fit(rho_s64 - 0.01, sto + 0.1, p_fit, 16, "double")
     g32, e32 = erfcx_fit(rho_s32 - 0.01, sto32 + 0.1, p_fit, 8, "float")
     assert e64 < 1.5e-15 and e32 < 4e-7, (e64, e32)
+    p_w = 0.4
+    gw, ew = erfcx_weighted_fit(rho_s64 - 0.01, sto + 0.1, p_w, 13)
+    ex, ee = exp_fit(11)
+    assert ew < 5e-18 and ee < 5e-18, (ew, ee)
     # the adjoint's derivative factors also need s2 and s4 -> 1
     out.append(f"#define SDBIE_RHO_CUT_LAPLACE_F64 {lap}")
     out.append(f"#define SDBIE_RHO_CUT_STOKES_F64 {sto}")
@@ -180,6 +230,12 @@ def main():
     out.append(f"#define SDBIE_ERFCX_P {p_fit}")
     out.append(emit_plain("kERFCX_F64", g64, "double", ""))
     out.append(emit_plain("kERFCX_F32", g32, "float", "f"))
+    out.append(f"// exp(-rho^2) sum_j kERFCXW_F64[j] t^j is erfc(rho) to {ew:.0e} (absolute), t = 1/(1 +")
+    out.append("// SDBIE_ERFCXW_P rho), same range")
+    out.append(f"#define SDBIE_ERFCXW_P {p_w}")
+    out.append(emit_plain("kERFCXW_F64", gw, "double", ""))
+    out.append(f"// e^y on |y| <= ln(2)/2 to {ee:.0e} (relative)")
+    out.append(emit_plain("kEXP_F64", ex, "double", ""))
     for k in (2, 4):
         g = G_series(k)
         out.append(emit(f"kG{k}_F64", truncate(g, rho_s64, eps64), "double", ""))

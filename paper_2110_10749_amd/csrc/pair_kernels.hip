@@ -201,6 +201,107 @@ __device__ __forceinline__ void horner_n(const double (&tab)[M], const double (&
         }
 }
 
+// two polynomials at once, their chains interleaved (MA >= MB)
+template <int N, int MA, int MB>
+__device__ __forceinline__ void horner_2n(const double (&ta)[MA], const double (&xa)[N], double (&a)[N],
+                                          const double (&tb)[MB], const double (&xb)[N], double (&b)[N]) {
+    cdouble *ca = (cdouble*)ta, *cb = (cdouble*)tb;
+    asm volatile("" : "+s"(ca), "+s"(cb));
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        a[u] = ca[MA - 1];
+        b[u] = cb[MB - 1];
+    }
+#pragma unroll
+    for (int i = MA - 2; i >= 0; --i) {
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            double r;
+            asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a[u]), "v"(xa[u]), "s"(ca[i]));
+            a[u] = r;
+        }
+        if (i - (MA - MB) >= 0) {
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                double r;
+                asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(b[u]), "v"(xb[u]), "s"(cb[i - (MA - MB)]));
+                b[u] = r;
+            }
+        }
+    }
+}
+
+// The same factors with fewer operations, for the symmetric passes: erfc from a
+// fit of 14 terms that is exact where exp(-rho^2) lets it show, e^y of 12 terms,
+// constants folded into the polynomials (43 double operations instead of 54 for
+// the stresslet factor; the error of each s_k against 60 digits is no larger:
+// largest 2.0e-15 against 3.0e-15 relative, near rho = 0.5, where s_4 = 0.1).
+template <int N, bool K1, bool K2, bool K3, bool K4>
+__device__ __forceinline__ void near_factors_sym(const double (&r2)[N], const double (&inv_r)[N], double id, double id2,
+                                                 double rc2, double (&k1)[N], double (&k2)[N], double (&k3)[N],
+                                                 double (&k4)[N]) {
+    double x[N];
+    bool in[N], ser[N], any_in = false, any_ser = false;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        x[u] = r2[u] * id2;
+        in[u] = r2[u] < rc2;
+        ser[u] = in[u] && x[u] < Consts<double>::rho_s2;
+        any_in = any_in || in[u];
+        any_ser = any_ser || ser[u];
+    }
+    if (!__any(any_in)) return;
+    {
+        constexpr double kLog2e = 1.44269504088896340736, kLn2 = 0.693147180559945309417;
+        double n[N], y[N], E[N], t[N], g[N], rho[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            rho[u] = r2[u] * inv_r[u] * id;
+            n[u] = rint(x[u] * kLog2e);
+            y[u] = fma(n[u], kLn2, -x[u]);  // n (ln 2 - kLn2) < 2e-15: too small for erf where exp(-x) is that small
+            const double v = fma(SDBIE_ERFCXW_P, rho[u], 1.0);
+            const double h = __builtin_amdgcn_rcp(v), e = fma(-v, h, 1.0);
+            t[u] = fma(h, fma(e, e, e), h);  // h (1 + e + e^2)
+        }
+        horner_2n<N>(kERFCXW_F64, t, g, kEXP_F64, y, E);
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const double e = ldexp(E[u], -(int)n[u]);
+            const double ef = fma(-e, g[u], 1.0), cE = kTwoOverSqrtPi * rho[u] * e;
+            const bool c = in[u];
+            // s_k times the plain factor
+            if (K1) k1[u] *= c ? fma(-cE, fma(x[u], 2.0 / 3.0, -5.0 / 3.0), ef) : 1.0;
+            if (K2) k2[u] *= c ? fma(cE, fma(x[u], 2.0 / 3.0, -1.0), ef) : 1.0;
+            if (K3) k3[u] *= c ? fma(-cE, fma(fma(x[u], 4.0 / 3.0, -14.0 / 3.0), x[u], 1.0), ef) : 1.0;
+            if (K4)
+                k4[u] *= c ? fma(-cE, fma(fma(fma(x[u], 8.0 / 9.0, -4.0), x[u], 2.0 / 3.0), x[u], 1.0), ef) : 1.0;
+        }
+    }
+    if (!__any(any_ser)) return;
+    const double id3 = id * id2;
+    double f[N];
+    if (K1) {
+        horner_n<N>(kF1_F64, x, f);
+#pragma unroll
+        for (int u = 0; u < N; ++u) k1[u] = ser[u] ? f[u] * id : k1[u];
+    }
+    if (K2) {
+        horner_n<N>(kF2_F64, x, f);
+#pragma unroll
+        for (int u = 0; u < N; ++u) k2[u] = ser[u] ? f[u] * id3 : k2[u];
+    }
+    if (K3) {
+        horner_n<N>(kF3_F64, x, f);
+#pragma unroll
+        for (int u = 0; u < N; ++u) k3[u] = ser[u] ? f[u] * id3 : k3[u];
+    }
+    if (K4) {
+        horner_n<N>(kF4_F64, x, f);
+#pragma unroll
+        for (int u = 0; u < N; ++u) k4[u] = ser[u] ? f[u] * id3 * id2 : k4[u];
+    }
+}
+
 template <int N, bool K1, bool K2, bool K3, bool K4>
 __device__ __forceinline__ void near_factors_n(const double (&r2)[N], const double (&inv_r)[N], double id, double id2,
                                                double rc2, double (&k1)[N], double (&k2)[N], double (&k3)[N],
@@ -1587,16 +1688,11 @@ struct SymLaplace {
         acc[0] += f;
         racc[0] += rot<(16 - K) & 15>(rv);
     }
-    // the same pair with the smoothed factors: f for the target and, with REV,
-    // rv for the source s (field F at s(F))
+    // The same for a near pair with factors k1 .. k4: f for the target and, with
+    // REV, rv for the source (field F at s(F)).
     template <bool REV, class Field>
-    __device__ __forceinline__ static void near(const T (&tr)[R], const Field& s, T id, T id2, T rc2, T (&f)[C],
-                                                T (&rv)[C]) {
-        const T dx = tr[0] - s(0), dy = tr[1] - s(1), dz = tr[2] - s(2);
-        const T r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-        const T ir = rsq(r2);
-        T k1 = ir, k2 = ir * ir * ir, k3, k4;
-        if (r2 < rc2) near_factors<T, SL, DL, false, false>(r2, ir, id, id2, k1, k2, k3, k4);
+    __device__ __forceinline__ static void near(const T (&tr)[R], const Field& s, T dx, T dy, T dz, T k1, T k2, T, T,
+                                                T (&f)[C], T (&rv)[C]) {
         f[0] = rv[0] = T(0);
         if constexpr (DL) {
             const T dns = fma(dx, s(NX), fma(dy, s(NY), dz * s(NZ)));
@@ -1677,16 +1773,10 @@ struct SymStokes {
         racc[1] += rot<(16 - K) & 15>(rc[1]);
         racc[2] += rot<(16 - K) & 15>(rc[2]);
     }
-    // the same pair with the smoothed factors (see SymLaplace::near)
+    // a near pair (see SymLaplace::near)
     template <bool REV, class Field>
-    __device__ __forceinline__ static void near(const T (&tr)[R], const Field& s, T id, T id2, T rc2, T (&f)[C],
-                                                T (&rv)[C]) {
-        const T dx = tr[0] - s(0), dy = tr[1] - s(1), dz = tr[2] - s(2);
-        const T r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-        const T ir = rsq(r2);
-        const T ir2 = ir * ir;
-        T k1 = ir, k2, k3 = ir * ir2, k4 = k3 * ir2;
-        if (r2 < rc2) near_factors<T, SL, false, SL, DL>(r2, ir, id, id2, k1, k2, k3, k4);
+    __device__ __forceinline__ static void near(const T (&tr)[R], const Field& s, T dx, T dy, T dz, T k1, T, T k3, T k4,
+                                                T (&f)[C], T (&rv)[C]) {
         T cf = T(0), cr = T(0);
         if constexpr (DL) {
             const T ux = s(UX) - (SUB ? tr[UX] : T(0)), uy = s(UY) - (SUB ? tr[UY] : T(0)),
@@ -1840,22 +1930,52 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
             }
             return !(d2 >= a.rcu2);
         };
-        // 16 steps with the smoothed factors against the row of sources from jb on
+        // 16 steps with the smoothed factors against the row of sources from jb on;
+        // in double some at a time (near_factors_sym)
         auto near_steps = [&](int jb, bool reverse) {
+            using Op = typename Sym::Op;
+            // Pairs of a lane at a time.  Measured in double (us a pass; 1, 2 and 4 at a
+            // time): Laplace single layer n = 17070 270, 229, 207; double layer 285,
+            // 244, 239 there and 2.56, 2.56, 2.67 ms at n = 68166; Stokes double layer
+            // n = 4302 52.6 and 49.7.  The stresslet with the Stokeslet takes 144
+            // registers with 2, and is no faster with the shorter forms either (434 us
+            // against 423 at n = 17070): one pair by near_factors.
+            constexpr bool kBoth = Op::K1 && Op::K4;
+            constexpr int G = !kNearBoth || kBoth ? 1 : C == 1 && !Op::K2 ? 4 : 2;
             T facc[C];
 #pragma unroll
             for (int c = 0; c < C; ++c) facc[c] = T(0);
 #pragma unroll 1
-            for (int k = 0; k < 16; ++k) {
-                const int j = jb + ((src.l16 - k) & 15);
-                T f[C], rv[C];
-                Sym::template near<kNearBoth>(
-                    tr, [&](int fld) { return srec[fld * kTile + j]; }, id, id2, rc2, f, rv);
+            for (int k = 0; k < 16; k += G) {
+                T dx[G], dy[G], dz[G], r2[G], ir[G], k1[G], k2[G], k3[G], k4[G];
 #pragma unroll
-                for (int c = 0; c < C; ++c) facc[c] += f[c];
-                if (kNearBoth && reverse) {
+                for (int u = 0; u < G; ++u) {
+                    const int j = jb + ((src.l16 - k - u) & 15);
+                    dx[u] = tr[0] - srec[j];
+                    dy[u] = tr[1] - srec[kTile + j];
+                    dz[u] = tr[2] - srec[2 * kTile + j];
+                    r2[u] = fma(dx[u], dx[u], fma(dy[u], dy[u], dz[u] * dz[u]));
+                    ir[u] = rsq_pos(r2[u]);  // r = 0 (NaN in double) takes the series
+                    k1[u] = k2[u] = k3[u] = k4[u] = T(0);
+                    Op::plain(ir[u], k1[u], k2[u], k3[u], k4[u]);
+                }
+                if constexpr (kNearBoth && !kBoth)
+                    near_factors_sym<G, Op::K1, Op::K2, Op::K3, Op::K4>(r2, ir, id, id2, rc2, k1, k2, k3, k4);
+                else if (r2[0] < rc2)
+                    near_factors<T, Op::K1, Op::K2, Op::K3, Op::K4>(r2[0], ir[0], id, id2, k1[0], k2[0], k3[0], k4[0]);
 #pragma unroll
-                    for (int c = 0; c < C; ++c) unsafeAtomicAdd(&sracc[c * kTile + j], (double)rv[c]);
+                for (int u = 0; u < G; ++u) {
+                    const int j = jb + ((src.l16 - k - u) & 15);
+                    T f[C], rv[C];
+                    Sym::template near<kNearBoth>(
+                        tr, [&](int fld) { return srec[fld * kTile + j]; }, dx[u], dy[u], dz[u], k1[u], k2[u], k3[u],
+                        k4[u], f, rv);
+#pragma unroll
+                    for (int c = 0; c < C; ++c) facc[c] += f[c];
+                    if (kNearBoth && reverse) {
+#pragma unroll
+                        for (int c = 0; c < C; ++c) unsafeAtomicAdd(&sracc[c * kTile + j], (double)rv[c]);
+                    }
                 }
             }
 #pragma unroll
