@@ -425,7 +425,7 @@ void dev_cgs2(const Plan& P, const double* Vr, int kr, const double* rot, const 
     double* host = P.host_pinned;
     double* pa = P.red;           // two sets of block partials in turn
     double* pb = P.partial;       // free between the pair passes
-    static_assert((size_t)(kFuseCols + 1) * kRedBlocks * sizeof(double) <= kMinPartial, "block partials in `partial`");
+    static_assert((size_t)(kFuseCols + 1) * kRedBlocks * sizeof(double) <= (size_t)1 << 20, "block partials in `partial`");
     const bool small = len <= (int64_t)kRedBlocks * 64;
     const dim3 grid(small ? kRedBlocks / 4 : kRedBlocks), th(256);
     const int k0 = kr > 0 ? kr + 1 : k;

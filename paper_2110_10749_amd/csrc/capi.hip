@@ -44,6 +44,15 @@ int64_t sym_max_items(int64_t nt, int k) {
 }
 int64_t sym_max_slots(int64_t nt) { return (sym_max_pairs(nt) + nt) / kSymChunk + 2 * nt; }
 
+// partial slots of a plan at least: the forward and reverse slots of the parts of
+// every tile pair (float: near pairs in both orders) up to kMinPartial, and the
+// block partials of the Krylov steps
+size_t min_partial(int64_t n) {
+    const int64_t nt = (n + kTile - 1) / kTile;
+    const size_t slots = (size_t)(nt * nt + nt * (nt - 1) / 2) * sym_parts(nt) * kSymSlotBytes;
+    return std::max((size_t)1 << 20, std::min(slots, kMinPartial));
+}
+
 // the node data, staging and pair-pass scratch every plan holds: nsplit
 // source splits with up to `comps` components per partial slot, m the
 // longest GMRES restart the reduction buffer serves, min_partial the least
@@ -81,7 +90,7 @@ Layout layout(int64_t n, int m) {
         return o;
     };
     const size_t d = sizeof(double);
-    layout_common(L, take, n, m, choose_splits(n), 6, kMinPartial);  // up to six components per pass (adjoint)
+    layout_common(L, take, n, m, choose_splits(n), 6, min_partial(n));  // up to six components per pass (adjoint)
     L.vecs = take((size_t)kNumVec * 3 * n * d);
     L.basis_in = take((size_t)(m + 1) * 3 * n * d);
     L.basis_out = take((size_t)(m + 1) * n * d);

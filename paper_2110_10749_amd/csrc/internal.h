@@ -96,8 +96,8 @@ enum : int {
     kHostE = 0, kHostH1 = kFuseCols, kHostH2 = 2 * kFuseCols, kHostNorm = 3 * kFuseCols,
     kHostDot = 3 * kFuseCols + 8, kHostDoubles = kHostDot + kRedBlocks,
 };
-// partial slots of a plan at least: the forward and reverse slots of 16 parts
-// to a tile pair up to 11 tiles (n = 2816)
+// most bytes of partial slots beyond the one-direction passes' that a plan of few
+// tiles takes for the slots of its symmetric passes
 constexpr size_t kMinPartial = (size_t)12 << 20;
 
 // Pair-sum passes --------------------------------------------------------------

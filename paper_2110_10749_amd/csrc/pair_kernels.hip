@@ -402,6 +402,7 @@ struct KArgs {
     const double* gather_src;  // density in the caller's order, gathered into gather_dst ([gather_c][n])
     double* gather_dst;
     const int32_t* perm;
+    const int32_t* dperm;  // densities are in the caller's order (nullable; packing in the pass, see sym_body)
     int gather_c;
     int near_waves;  // near_small_body: waves per 64 targets
     const double* dl_tgt;  // target density of the subtracted double layer (nullable: dl_dens)
@@ -441,8 +442,10 @@ __device__ __forceinline__ void targets_to_frame(Op& op, const KArgs& a, const T
     }
 }
 
-__device__ __forceinline__ double dens_at(const double* d, int64_t n, int c, int64_t j) {
-    return j < n ? d[c * n + j] : 0.0;
+// component c of density d at staged node j (0 on padding); d is in the caller's
+// order when dperm is set
+__device__ __forceinline__ double dens_at(const KArgs& a, const double* d, int c, int64_t j) {
+    return j < a.n ? d[c * a.n + (a.dperm ? (int64_t)a.dperm[j] : j)] : 0.0;
 }
 
 __device__ __forceinline__ double src_weight(const KArgs& a, int64_t j) {
@@ -502,15 +505,15 @@ struct LaplaceOp {
             r[NX] = T(c * a.nrm[j]);
             r[NY] = T(c * a.nrm[a.npad + j]);
             r[NZ] = T(c * a.nrm[2 * a.npad + j]);
-            r[Q] = T(dens_at(a.dl_dens, a.n, 0, j));
+            r[Q] = T(dens_at(a, a.dl_dens, 0, j));
         }
-        r[G] = SL ? T(a.c_sl * wj * dens_at(a.sl_dens, a.n, 0, j)) : T(0);
+        r[G] = SL ? T(a.c_sl * wj * dens_at(a, a.sl_dens, 0, j)) : T(0);
     }
     __device__ __forceinline__ void init(const KArgs& a, int64_t i) {
         xi = load_x<T>(a, 0, i);
         yi = load_x<T>(a, 1, i);
         zi = load_x<T>(a, 2, i);
-        qi = (DL && SUB) ? T(dens_at(a.dl_dens, a.n, 0, i)) : T(0);
+        qi = (DL && SUB) ? T(dens_at(a, a.dl_dens, 0, i)) : T(0);
     }
     template <bool NEAR, class P>
     __device__ __forceinline__ void pair(P r, T id, T id2, T rc2) {
@@ -577,9 +580,9 @@ struct StokesOp {
         const double nx = a.nrm[j], ny = a.nrm[np + j], nz = a.nrm[2 * np + j];
         double ux = 0.0, uy = 0.0, uz = 0.0;
         if (DL || SLIP) {
-            ux = dens_at(a.dl_dens, a.n, 0, j);
-            uy = dens_at(a.dl_dens, a.n, 1, j);
-            uz = dens_at(a.dl_dens, a.n, 2, j);
+            ux = dens_at(a, a.dl_dens, 0, j);
+            uy = dens_at(a, a.dl_dens, 1, j);
+            uz = dens_at(a, a.dl_dens, 2, j);
         }
         if (DL) {
             const double c = a.c_dl * wj;
@@ -600,9 +603,9 @@ struct StokesOp {
                 fy = a.slip_beta * (uy - un * ny);
                 fz = a.slip_beta * (uz - un * nz);
             } else {
-                fx = dens_at(a.sl_dens, a.n, 0, j);
-                fy = dens_at(a.sl_dens, a.n, 1, j);
-                fz = dens_at(a.sl_dens, a.n, 2, j);
+                fx = dens_at(a, a.sl_dens, 0, j);
+                fy = dens_at(a, a.sl_dens, 1, j);
+                fz = dens_at(a, a.sl_dens, 2, j);
             }
             const double c = a.c_sl * wj;
             r[FX] = T(c * fx);
@@ -618,9 +621,9 @@ struct StokesOp {
         zi = load_x<T>(a, 2, i);
         if (DL && SUB) {
             const double* tg = a.dl_tgt ? a.dl_tgt : a.dl_dens;
-            uix = T(dens_at(tg, a.n, 0, i));
-            uiy = T(dens_at(tg, a.n, 1, i));
-            uiz = T(dens_at(tg, a.n, 2, i));
+            uix = T(dens_at(a, tg, 0, i));
+            uiy = T(dens_at(a, tg, 1, i));
+            uiz = T(dens_at(a, tg, 2, i));
         }
     }
     template <bool NEAR, class P>
@@ -721,7 +724,7 @@ struct LaplaceTNOp {
         r[0] = load_x<T>(a, 0, j);
         r[1] = load_x<T>(a, 1, j);
         r[2] = load_x<T>(a, 2, j);
-        r[3] = T(a.c_dl * src_weight(a, j) * dens_at(a.dl_dens, a.n, 0, j));
+        r[3] = T(a.c_dl * src_weight(a, j) * dens_at(a, a.dl_dens, 0, j));
     }
     __device__ __forceinline__ void init(const KArgs& a, int64_t i) {
         xi = load_x<T>(a, 0, i);
@@ -775,9 +778,9 @@ struct StokesTNOp {
         r[1] = load_x<T>(a, 1, j);
         r[2] = load_x<T>(a, 2, j);
         const double c = a.c_dl * src_weight(a, j);
-        r[3] = T(c * dens_at(a.dl_dens, a.n, 0, j));
-        r[4] = T(c * dens_at(a.dl_dens, a.n, 1, j));
-        r[5] = T(c * dens_at(a.dl_dens, a.n, 2, j));
+        r[3] = T(c * dens_at(a, a.dl_dens, 0, j));
+        r[4] = T(c * dens_at(a, a.dl_dens, 1, j));
+        r[5] = T(c * dens_at(a, a.dl_dens, 2, j));
         r[6] = r[7] = T(0);
     }
     __device__ __forceinline__ void init(const KArgs& a, int64_t i) {
@@ -957,14 +960,14 @@ __device__ __forceinline__ GTgt load_gtgt(const KArgs& a, int64_t i) {
     t.x = a.x[i];
     t.y = a.x[a.npad + i];
     t.z = a.x[2 * a.npad + i];
-    t.p = dens_at(a.g_p, a.n, 0, i);
-    t.ux = dens_at(a.g_u, a.n, 0, i);
-    t.uy = dens_at(a.g_u, a.n, 1, i);
-    t.uz = dens_at(a.g_u, a.n, 2, i);
-    t.l1 = dens_at(a.g_l1, a.n, 0, i);
-    t.lx = dens_at(a.g_l2, a.n, 0, i);
-    t.ly = dens_at(a.g_l2, a.n, 1, i);
-    t.lz = dens_at(a.g_l2, a.n, 2, i);
+    t.p = dens_at(a, a.g_p, 0, i);
+    t.ux = dens_at(a, a.g_u, 0, i);
+    t.uy = dens_at(a, a.g_u, 1, i);
+    t.uz = dens_at(a, a.g_u, 2, i);
+    t.l1 = dens_at(a, a.g_l1, 0, i);
+    t.lx = dens_at(a, a.g_l2, 0, i);
+    t.ly = dens_at(a, a.g_l2, 1, i);
+    t.lz = dens_at(a, a.g_l2, 2, i);
     return t;
 }
 
@@ -977,14 +980,14 @@ __device__ __forceinline__ GSrc load_gsrc(const KArgs& a, int64_t j) {
     s.ny = a.nrm[a.npad + j];
     s.nz = a.nrm[2 * a.npad + j];
     s.w = a.w[j];
-    s.p = dens_at(a.g_p, a.n, 0, j);
-    s.v = dens_at(a.g_v, a.n, 0, j);
-    s.ux = dens_at(a.g_u, a.n, 0, j);
-    s.uy = dens_at(a.g_u, a.n, 1, j);
-    s.uz = dens_at(a.g_u, a.n, 2, j);
-    s.fx = dens_at(a.g_f, a.n, 0, j);
-    s.fy = dens_at(a.g_f, a.n, 1, j);
-    s.fz = dens_at(a.g_f, a.n, 2, j);
+    s.p = dens_at(a, a.g_p, 0, j);
+    s.v = dens_at(a, a.g_v, 0, j);
+    s.ux = dens_at(a, a.g_u, 0, j);
+    s.uy = dens_at(a, a.g_u, 1, j);
+    s.uz = dens_at(a, a.g_u, 2, j);
+    s.fx = dens_at(a, a.g_f, 0, j);
+    s.fy = dens_at(a, a.g_f, 1, j);
+    s.fz = dens_at(a, a.g_f, 2, j);
     return s;
 }
 
@@ -1091,23 +1094,28 @@ __device__ __forceinline__ double block_sum(double v) {
     return (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
+// block partials of the completion's dot product, in dev_dot's order: the first
+// kRedBlocks blocks of the launch (all that hold elements)
+__device__ __forceinline__ void completion_partials(const KArgs& a) {
+    if (!a.comp_a || blockIdx.x >= kRedBlocks) return;
+    double s = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.comp_len; i += (int64_t)kRedBlocks * 256)
+        s += a.comp_a[i] * a.comp_b[i];
+    s = block_sum(s);
+    if (threadIdx.x == 0) a.comp_part[blockIdx.x] = s;
+    // blocks past the launch hold no elements
+    if (blockIdx.x == 0)
+        for (int b = gridDim.x + threadIdx.x; b < kRedBlocks; b += 256) a.comp_part[b] = 0.0;
+}
+
 // One thread per source (padding included): write the pass's source records.
 // The same launch gathers a density given in the caller's order and takes the
-// block partials of the completion's dot product (the first kRedBlocks blocks,
-// dev_dot's order), which the epilogue adds up: three launches less per product,
-// 12 us of the 36 us that a Stokes double layer takes at n = 2650.
+// block partials of the completion's dot product, which the epilogue adds up:
+// three launches less per product.
 template <class Op, typename T>
 __global__ __launch_bounds__(256) void pack_sources(KArgs a) {
     const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (a.comp_a && blockIdx.x < kRedBlocks) {
-        double s = 0.0;
-        for (int64_t i = j; i < a.comp_len; i += (int64_t)kRedBlocks * 256) s += a.comp_a[i] * a.comp_b[i];
-        s = block_sum(s);
-        if (threadIdx.x == 0) a.comp_part[blockIdx.x] = s;
-        // blocks past the launch hold no elements
-        if (blockIdx.x == 0)
-            for (int b = gridDim.x + threadIdx.x; b < kRedBlocks; b += 256) a.comp_part[b] = 0.0;
-    }
+    completion_partials(a);
     if (j >= a.npad) return;
     if (a.gather_src && j < a.n) {
         const int64_t o = a.perm[j];
@@ -1544,15 +1552,15 @@ __device__ __forceinline__ double epi_completion(const double* __restrict__ comp
 // completion, constant) and the store in the caller's node order
 template <int C>
 __device__ __forceinline__ void epi_finish(int64_t n, int64_t i, const double (&v)[C],
-                                           const double* __restrict__ tw, const double* base, double base_scale,
-                                           bool comp, double cs, const double* __restrict__ nrm, double add0,
+                                           const double* __restrict__ tw, const double* base,
+                                           const int32_t* __restrict__ bperm, double base_scale, bool comp, double cs, const double* __restrict__ nrm, double add0,
                                            double add1, double add2, double* out, const int32_t* __restrict__ perm) {
-    const int64_t o = perm ? (int64_t)perm[i] : i;
+    const int64_t o = perm ? (int64_t)perm[i] : i, b = bperm ? (int64_t)bperm[i] : i;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         double s = v[c];
         if (tw) s *= tw[i];
-        if (base) s += base_scale * base[c * n + i];
+        if (base) s += base_scale * base[c * n + b];
         if (comp) s += cs * (C == 3 ? nrm[c * n + i] : 1.0);
         s += (c == 0 ? add0 : (c == 1 ? add1 : add2));
         out[c * n + o] = s;
@@ -1577,7 +1585,7 @@ __global__ __launch_bounds__(kEpiThreads) void epilogue(int64_t n, int nslots, c
 #pragma unroll
             for (int c = 0; c < C; ++c) v[c] += partial[((int64_t)sl * C + c) * n + i];
     epi_combine<C>(v, g, jj);
-    if (g == 0 && i < n) epi_finish<C>(n, i, v, tw, base, base_scale, comp != nullptr, cs, nrm, add0, add1, add2, out, perm);
+    if (g == 0 && i < n) epi_finish<C>(n, i, v, tw, base, nullptr, base_scale, comp != nullptr, cs, nrm, add0, add1, add2, out, perm);
 }
 
 // --------------------------------------------------------------------------
@@ -1878,7 +1886,13 @@ struct SymArgs {
 //   a rough density moves by 1e-6 of its largest value with the frame.  A tile
 //   against itself takes all 16 rotations, one direction.
 // NEAR = false: a set without near pairs.
-template <class Sym, typename T, bool NEAR>
+//
+// PACK: every block forms the records it needs itself, from the staged nodes and
+// the density (in the caller's order for the layer sums), instead of a packing
+// launch before the pass.  Sets of several parts to a pair: a record is then
+// formed by as many blocks as meet the tile, 50 instructions each against the
+// thousands of a part, and a pass of 10 to 60 us is one launch shorter.
+template <class Sym, typename T, bool NEAR, bool PACK>
 __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int blk) {
     constexpr int R = Sym::R, C = Sym::C;
     static_assert(kTile == kTPB && kTile == 256, "one target and one staged source per thread, four waves");
@@ -1891,9 +1905,16 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
     const int first = sa.blocks[3 * blk], cnt = sa.blocks[3 * blk + 1], slot = sa.blocks[3 * blk + 2];
     const int ta = sa.items[4 * first];
     const T* rec = static_cast<const T*>(a.rec);
-    T tr[R];
+    auto load = [&](T (&r)[R], int t) {
+        if constexpr (PACK) {
+            Sym::Op::pack(r, (int64_t)t * kTile + tid, a);
+        } else {
 #pragma unroll
-    for (int f = 0; f < R; ++f) tr[f] = rec[((int64_t)ta * kTile + tid) * R + f];
+            for (int f = 0; f < R; ++f) r[f] = rec[((int64_t)t * kTile + tid) * R + f];
+        }
+    };
+    T tr[R];
+    load(tr, ta);
     const T x0[3] = {tr[0], tr[1], tr[2]};  // the targets in their own tile's frame
     const T id = T(a.inv_delta), id2 = id * id, rc2 = T(a.rc2);
     double acc[C];
@@ -1912,8 +1933,12 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
             for (int c = 0; c < 3; ++c) tr[c] = x0[c] + (float)(tile_centre(a, ta, c) - tile_centre(a, tb, c));
         }
         __syncthreads();  // the previous tile pair is done with the LDS
+        {
+            T r[R];
+            load(r, tb);
 #pragma unroll
-        for (int f = 0; f < R; ++f) srec[f * kTile + tid] = rec[((int64_t)tb * kTile + tid) * R + f];
+            for (int f = 0; f < R; ++f) srec[f * kTile + tid] = r[f];
+        }
 #pragma unroll
         for (int c = 0; c < C; ++c) sracc[c * kTile + tid] = 0.0;
         __syncthreads();
@@ -2043,21 +2068,22 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
 // Left alone, the compiler hoists the LDS reads of a whole row rotation ahead
 // of its 16 steps (up to 134 VGPRs, 3 waves per SIMD for the float Laplace
 // double layer); the float passes are held to 8 waves per SIMD.
-template <class Sym, typename T>
-__global__ __launch_bounds__(kTPB) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 8 : 1)))
+template <class Sym, typename T, bool PACK>
+__global__ __launch_bounds__(kTPB) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (PACK ? 4 : 8) : 1)))
 void sym_pass_pairs(KArgs a, SymArgs sa) {
-    sym_body<Sym, T, true>(a, sa, blockIdx.x);
+    if constexpr (PACK) completion_partials(a);
+    sym_body<Sym, T, true, PACK>(a, sa, blockIdx.x);
 }
 
 // far pairs alone, then the one-direction near-field blocks (double)
 template <class Op, class Sym>
 __global__ __launch_bounds__(kTPB) void sym_far_near_pairs(KArgs a, SymArgs sa) {
-    if ((int)blockIdx.x < sa.nblocks) sym_body<Sym, double, false>(a, sa, blockIdx.x);
+    if ((int)blockIdx.x < sa.nblocks) sym_body<Sym, double, false, false>(a, sa, blockIdx.x);
     else near_body<Op, double>(a, (int)blockIdx.x - sa.nblocks);
 }
 template <class Op, class Sym>
 __global__ __launch_bounds__(kTPB) void sym_far_near_small(KArgs a, SymArgs sa) {
-    if ((int)blockIdx.x < sa.nblocks) sym_body<Sym, double, false>(a, sa, blockIdx.x);
+    if ((int)blockIdx.x < sa.nblocks) sym_body<Sym, double, false, false>(a, sa, blockIdx.x);
     else near_small_body<Op, double>(a, (int)blockIdx.x - sa.nblocks);
 }
 
@@ -2070,8 +2096,8 @@ template <int C, typename RT>
 __global__ __launch_bounds__(kEpiThreads) void sym_epilogue(
     int64_t n, const int32_t* __restrict__ fwd_start, const double* __restrict__ fwd,
     const int32_t* __restrict__ rev_start, const RT* __restrict__ rev, int nsplit,
-    const double* __restrict__ partial, const double* __restrict__ tw, const double* base, double base_scale,
-    const double* __restrict__ comp, double comp_scale, const double* __restrict__ nrm, double add0, double add1,
+    const double* __restrict__ partial, const double* __restrict__ tw, const double* base,
+    const int32_t* __restrict__ bperm, double base_scale, const double* __restrict__ comp, double comp_scale, const double* __restrict__ nrm, double add0, double add1,
     double add2, double* out, const int32_t* __restrict__ perm) {
     static_assert(kTile % kEpiTargets == 0, "a block's targets lie in one tile");
     const int g = threadIdx.x / kEpiTargets, jj = threadIdx.x % kEpiTargets;
@@ -2096,7 +2122,7 @@ __global__ __launch_bounds__(kEpiThreads) void sym_epilogue(
             for (int c = 0; c < C; ++c) v[c] += partial[((int64_t)(nsplit + sl) * C + c) * n + i];
     }
     epi_combine<C>(v, g, jj);
-    if (g == 0 && i < n) epi_finish<C>(n, i, v, tw, base, base_scale, comp != nullptr, cs, nrm, add0, add1, add2, out, perm);
+    if (g == 0 && i < n) epi_finish<C>(n, i, v, tw, base, bperm, base_scale, comp != nullptr, cs, nrm, add0, add1, add2, out, perm);
 }
 
 int near_waves(const Plan& P, bool mixed);
@@ -2134,6 +2160,7 @@ KArgs make_args(const Plan& P, const PassDesc& d, int nsplit, double cut, int co
     a.gather_src = d.gather_src;
     a.gather_dst = d.gather_dst;
     a.perm = P.perm;
+    a.dperm = nullptr;
     a.gather_c = comps;
     a.near_waves = near_waves(P, d.mixed);
     a.g_p = a.g_v = a.g_u = a.g_f = a.g_l1 = a.g_l2 = nullptr;
@@ -2163,6 +2190,10 @@ const SymSet& sym_set(const Plan& P, bool mixed) {
     return P.sym[mixed ? kSymF32 : P.far_only64 ? kSymFar64 : kSymF64];
 }
 
+// whether the blocks of a set's passes form the records (several parts to a tile
+// pair; the completion's partials then come from the pass's first blocks)
+bool sym_packs(const SymSet& S) { return S.parts > 1; }
+
 // pack and pair kernels of one pass, each timed on its own when kernel timing
 // is on (pairs: all N^2 for a pass kernel; with separate far and near
 // launches, the real-node pairs of the far / near tile pairs)
@@ -2174,20 +2205,26 @@ bool launch_pair_kernels(const Plan& P, const KArgs& a, hipStream_t st, int fami
     if (Op::C > P.max_comps) throw Error(SDBIE_ERR_ARG, "this workspace holds no partial slots for that pass");
     const double all = (double)P.n * (double)P.n;
     const double near = mixed ? P.near_pairs32 : P.near_pairs64;
-    {
-        ProfScope prof(prof_variant(family, mixed, code, 2), 0.0, st);
-        // as many blocks as hold sources or elements of the completion's dot product
-        int64_t pb = a.npad / 256, cb = a.comp_a ? (a.comp_len + 255) / 256 : 0;
-        if (cb > kRedBlocks) cb = kRedBlocks;
-        if (cb > pb) pb = cb;
-        hipLaunchKernelGGL((pack_sources<Op, T>), dim3((unsigned)pb), dim3(256), 0, st, a);
-        SDBIE_LAUNCHED();
-    }
     using Sym = typename SymOf<Op>::type;
+    bool sym = false, pack = true;
+    // blocks that hold elements of the completion's dot product
+    int64_t cb = a.comp_a ? (a.comp_len + 255) / 256 : 0;
+    if (cb > kRedBlocks) cb = kRedBlocks;
     if constexpr (!std::is_same<Sym, void>::value) {
         const int kind = mixed ? Sym::kFamilyBit : Sym::kFamilyBit << 2;  // SDBIE_SYM_* of this pass
         const SymSet& S = sym_set(P, mixed);
-        if ((P.symmetric & kind) && S.nblocks > 0 && !a.dl_tgt) {
+        sym = (P.symmetric & kind) && S.nblocks > 0 && !a.dl_tgt;
+        pack = !sym || !sym_packs(S) || cb > S.nblocks;
+    }
+    if (pack) {
+        const int64_t pb = a.npad / 256 > cb ? a.npad / 256 : cb;
+        ProfScope prof(prof_variant(family, mixed, code, 2), 0.0, st);
+        hipLaunchKernelGGL((pack_sources<Op, T>), dim3((unsigned)pb), dim3(256), 0, st, a);
+        SDBIE_LAUNCHED();
+    }
+    if constexpr (!std::is_same<Sym, void>::value) {
+        if (sym) {
+            const SymSet& S = sym_set(P, mixed);
             SymArgs sa;
             sa.nblocks = S.nblocks;
             sa.items = S.items;
@@ -2209,7 +2246,20 @@ bool launch_pair_kernels(const Plan& P, const KArgs& a, hipStream_t st, int fami
                     return true;
                 }
             }
-            hipLaunchKernelGGL((sym_pass_pairs<Sym, T>), dim3((unsigned)sa.nblocks), dim3(kTPB), 0, st, a, sa);
+            if (pack) {
+                hipLaunchKernelGGL((sym_pass_pairs<Sym, T, false>), dim3((unsigned)sa.nblocks), dim3(kTPB), 0, st, a,
+                                   sa);
+            } else {
+                // densities straight from the caller's order
+                KArgs b = a;
+                if (a.gather_src) {
+                    if (b.dl_dens == a.gather_dst) b.dl_dens = a.gather_src;
+                    if (b.sl_dens == a.gather_dst) b.sl_dens = a.gather_src;
+                    b.dperm = a.perm;
+                }
+                hipLaunchKernelGGL((sym_pass_pairs<Sym, T, true>), dim3((unsigned)sa.nblocks), dim3(kTPB), 0, st, b,
+                                   sa);
+            }
             SDBIE_LAUNCHED();
             return true;
         }
@@ -2259,15 +2309,19 @@ void launch_epilogue(const Plan& P, const PassDesc& d, int S, bool sym, hipStrea
     if (sym) {
         const SymSet& Y = sym_set(P, d.mixed);
         const int nsplit = !d.mixed && P.far_only64 ? S : 0;
+        // without a packing launch a density in the caller's order has not been gathered
+        const bool raw = sym_packs(Y) && d.gather_src && d.base == d.gather_dst;
+        const double* base = raw ? d.gather_src : d.base;
+        const int32_t* bperm = raw ? (const int32_t*)P.perm : nullptr;
         if (d.mixed)
             hipLaunchKernelGGL((sym_epilogue<C, float>), dim3(eb), et, 0, st, P.n, (const int32_t*)Y.fwd_start,
                                (const double*)Y.fwd, (const int32_t*)Y.rev_start, (const float*)Y.rev, nsplit,
-                               (const double*)P.partial, tw, d.base, d.base_scale, comp, d.comp_scale,
+                               (const double*)P.partial, tw, base, bperm, d.base_scale, comp, d.comp_scale,
                                (const double*)P.nrm, a0, a1, a2, d.out, perm);
         else
             hipLaunchKernelGGL((sym_epilogue<C, double>), dim3(eb), et, 0, st, P.n, (const int32_t*)Y.fwd_start,
                                (const double*)Y.fwd, (const int32_t*)Y.rev_start, (const double*)Y.rev, nsplit,
-                               (const double*)P.partial, tw, d.base, d.base_scale, comp, d.comp_scale,
+                               (const double*)P.partial, tw, base, bperm, d.base_scale, comp, d.comp_scale,
                                (const double*)P.nrm, a0, a1, a2, d.out, perm);
     } else {
         hipLaunchKernelGGL((epilogue<C>), dim3(eb), et, 0, st, P.n, 2 * S, (const double*)P.partial, tw,
