@@ -312,8 +312,11 @@ __global__ __launch_bounds__(kTile) void k_stage(StageArgs a) {
 // mask rows and their counts, the prefix sums of those (one block), and the
 // items and blocks of each row.  Blocks hold as many pairs as leave about
 // SDBIE_SYM_TARGET of them for each kind of pair (at most kSymChunk while the
-// forward slots have room): with 8 pairs to a block the 2200 pairs of n = 17070
-// made 343 blocks for 256 CUs.
+// forward slots have room).  More pairs to a block save target loads and forward
+// slots, fewer let the last wave of blocks end together: with targets of 2048 and
+// 16384 (4096, 8192 and 65536 lie between or are equal) n = 68166 takes, us a pass,
+// 3895 and 3760 for the double Stokes double layer, 2720 and 2605 for the float
+// slip sum, 1333 and 1255 for the float Laplace double layer.
 
 // position of this thread's flag among the set flags of the block (256 threads), and their number
 __device__ __forceinline__ int block_rank(bool f, int* sh, int& total) {
@@ -656,7 +659,7 @@ void build_symmetric_lists(Plan& P, int32_t* out, hipStream_t st) {
     for (int k = 0; k < 2; ++k) {
         SymSet& S = P.sym[k];
         const int64_t items = k == kSymF32 ? (int64_t)T * T : pairs + T;  // at most, of one part
-        S.parts = sym_parts(T);
+        S.parts = sym_parts(T, k);
         while (S.parts > 1 && (items + pairs) * S.parts * kSymSlotBytes > P.partial_bytes) S.parts /= 2;
         A.parts[k] = S.parts;
         const int width = 16 / S.parts;

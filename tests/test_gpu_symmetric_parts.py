@@ -30,7 +30,7 @@ def sd():
     return sd
 
 
-@pytest.mark.parametrize("N", [256, 257, 1280, 2816, 2817, 5633, 8192, 11521, 16128, 16129])
+@pytest.mark.parametrize("N", [256, 257, 1280, 2816, 2817, 5633, 8192, 11521, 16128, 16129, 23040, 23041])
 def test_symmetric_passes_at_the_list_edges(sd, N):
     x = np.random.default_rng(N).normal(size=(3, N))
     x /= np.linalg.norm(x, axis=0)
