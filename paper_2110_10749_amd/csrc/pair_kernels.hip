@@ -1696,6 +1696,28 @@ struct SymLaplace {
         acc[0] += f;
         racc[0] += rot<(16 - K) & 15>(rv);
     }
+    // A far pair of target tr and source s, both in registers: the forward term is
+    // added to acc, the reverse one to rv (ADD) or put there.
+    template <bool ADD>
+    __device__ __forceinline__ static void pair(const T (&tr)[R], const T (&s)[R], T (&acc)[C], T (&rv)[C]) {
+        const T dx = tr[0] - s[0], dy = tr[1] - s[1], dz = tr[2] - s[2];
+        const T r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+        const T ir = rsq_pos(r2);
+        T r = ADD ? rv[0] : T(0);
+        if constexpr (DL) {
+            const T k2 = ir * ir * ir;
+            const T dns = fma(dx, s[NX], fma(dy, s[NY], dz * s[NZ]));
+            const T dnt = fma(dx, tr[NX], fma(dy, tr[NY], dz * tr[NZ]));
+            const T qf = (SUB ? s[Q] - tr[Q] : s[Q]) * k2, qr = SUB ? qf : -tr[Q] * k2;
+            acc[0] = fma(qf, dns, acc[0]);
+            r = fma(qr, dnt, r);
+        }
+        if constexpr (SL) {
+            acc[0] = fma(s[G], ir, acc[0]);
+            r = fma(tr[G], ir, r);
+        }
+        rv[0] = r;
+    }
     // The same for a near pair with factors k1 .. k4: f for the target and, with
     // REV, rv for the source (field F at s(F)).
     template <bool REV, class Field>
@@ -1780,6 +1802,49 @@ struct SymStokes {
         racc[0] += rot<(16 - K) & 15>(rc[0]);
         racc[1] += rot<(16 - K) & 15>(rc[1]);
         racc[2] += rot<(16 - K) & 15>(rc[2]);
+    }
+    // a far pair (see SymLaplace::pair)
+    template <bool ADD>
+    __device__ __forceinline__ static void pair(const T (&tr)[R], const T (&s)[R], T (&acc)[C], T (&rv)[C]) {
+        const T dx = tr[0] - s[0], dy = tr[1] - s[1], dz = tr[2] - s[2];
+        const T r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+        const T ir = rsq_pos(r2);
+        const T ir2 = ir * ir;
+        T ud = T(0), udr = T(0), dns = T(0), dnt = T(0);
+        if constexpr (DL) {
+            const T ux = s[UX] - (SUB ? tr[UX] : T(0)), uy = s[UY] - (SUB ? tr[UY] : T(0)),
+                    uz = s[UZ] - (SUB ? tr[UZ] : T(0));
+            ud = fma(ux, dx, fma(uy, dy, uz * dz));
+            udr = SUB ? ud : -fma(tr[UX], dx, fma(tr[UY], dy, tr[UZ] * dz));
+            dns = fma(dx, s[NX], fma(dy, s[NY], dz * s[NZ]));
+            dnt = fma(dx, tr[NX], fma(dy, tr[NY], dz * tr[NZ]));
+        }
+        T y[3], f;  // the reverse term is y f
+        if constexpr (SL) {
+            const T dfs = fma(dx, s[FX], fma(dy, s[FY], dz * s[FZ]));
+            const T dft = fma(dx, tr[FX], fma(dy, tr[FY], dz * tr[FZ]));
+            const T ef = (DL ? fma(ud * ir2, dns, dfs) : dfs) * ir2;
+            const T er = (DL ? fma(udr * ir2, dnt, dft) : dft) * ir2;
+            acc[0] = fma(fma(ef, dx, s[FX]), ir, acc[0]);
+            acc[1] = fma(fma(ef, dy, s[FY]), ir, acc[1]);
+            acc[2] = fma(fma(ef, dz, s[FZ]), ir, acc[2]);
+            y[0] = fma(er, dx, tr[FX]);
+            y[1] = fma(er, dy, tr[FY]);
+            y[2] = fma(er, dz, tr[FZ]);
+            f = ir;
+        } else {
+            const T k4 = ir * ir2 * ir2, uf = ud * k4, ur = SUB ? uf : udr * k4;
+            const T cf = uf * dns;
+            acc[0] = fma(cf, dx, acc[0]);
+            acc[1] = fma(cf, dy, acc[1]);
+            acc[2] = fma(cf, dz, acc[2]);
+            y[0] = dx;
+            y[1] = dy;
+            y[2] = dz;
+            f = ur * dnt;
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) rv[c] = ADD ? fma(y[c], f, rv[c]) : y[c] * f;
     }
     // a near pair (see SymLaplace::near)
     template <bool REV, class Field>
@@ -1893,14 +1958,14 @@ struct SymArgs {
 // formed by as many blocks as meet the tile, 50 instructions each against the
 // thousands of a part, and a pass of 10 to 60 us is one launch shorter.
 template <class Sym, typename T, bool NEAR, bool PACK>
-__device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int blk) {
+__device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int blk, T* srec, double* sracc) {
     constexpr int R = Sym::R, C = Sym::C;
     static_assert(kTile == kTPB && kTile == 256, "one target and one staged source per thread, four waves");
     static_assert(kNearUnit == 64, "a wave's targets and a quarter of the sources are units");
     static_assert(block_terms<T>() >= 16, "a row rotation of 16 steps sums in T");
     constexpr bool kNearBoth = sizeof(T) == 8;  // near steps serve both directions
-    __shared__ T srec[R * kTile];  // the source tile, field-major: field f of source j at srec[f * kTile + j]
-    __shared__ double sracc[C * kTile];  // reverse sums of the tile pair, one 16-step rotation at a time
+    // srec: R * kTile, the source tile, field-major: field f of source j at srec[f * kTile + j]
+    // sracc: C * kTile, reverse sums of the tile pair, one 16-step rotation at a time
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int first = sa.blocks[3 * blk], cnt = sa.blocks[3 * blk + 1], slot = sa.blocks[3 * blk + 2];
     const int ta = sa.items[4 * first];
@@ -2065,25 +2130,163 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
     for (int c = 0; c < C; ++c) sa.fwd[((int64_t)slot * C + c) * kTile + tid] = acc[c];
 }
 
-// Left alone, the compiler hoists the LDS reads of a whole row rotation ahead
-// of its 16 steps (up to 134 VGPRs, 3 waves per SIMD for the float Laplace
-// double layer); the float passes are held to 8 waves per SIMD.
+// Far tile pairs of one part, two targets to a lane: a source read from LDS
+// serves two pairs, and their reverse terms travel home as one sum, so a pair
+// takes half the LDS reads and half the DPP moves and adds of sym_body's steps.
+// The pass is bound by its VALU instructions (and by the clock they leave).  Waves
+// w and w ^ 2 hold the targets of units 2 (w & 1) and 2 (w & 1) + 1 and meet source
+// quarters w and w ^ 1, so the four waves own the four quarters in each of two
+// phases; the forward sums of the two waves meet in LDS at the end.
+// Measured, us a pass, one target and two: n = 68166 double Stokes double layer
+// 3680 and 3340, slip sum 4930 and 4450, Laplace single layer 1940 and 1770; float
+// slip sum 2600 and 2520, Laplace double layer 1277 and 1140, single layer 948 and
+// 853; n = 272718 float Stokes double layer 28270 and 27430, Laplace single layer
+// 10700 and 9030.  Four targets to a lane lose again (Laplace double layer 1193:
+// registers), and so do sets of several parts (n = 9582 double slip sum 177 and 191):
+// they keep one.
+constexpr int kSymTargets = 2;
+
+template <class Sym, typename T, int K, int E>
+__device__ __forceinline__ void sym_multi_steps(const T (&tr)[kSymTargets][Sym::R], const T* lds, int jb, int l16,
+                                                T (&facc)[kSymTargets][Sym::C], T (&racc)[Sym::C]) {
+    const int j = jb + ((l16 - K) & 15);
+    T s[Sym::R], rv[Sym::C];
+#pragma unroll
+    for (int f = 0; f < Sym::R; ++f) s[f] = lds[f * kTile + j];
+    Sym::template pair<false>(tr[0], s, facc[0], rv);
+#pragma unroll
+    for (int t = 1; t < kSymTargets; ++t) Sym::template pair<true>(tr[t], s, facc[t], rv);
+#pragma unroll
+    for (int c = 0; c < Sym::C; ++c) racc[c] += rot<(16 - K) & 15>(rv[c]);
+    if constexpr (K + 1 < E) sym_multi_steps<Sym, T, K + 1, E>(tr, lds, jb, l16, facc, racc);
+}
+// a row rotation: 16 steps, float sums over blocks of 16 terms (8 steps of the reverse sums)
+template <class Sym, typename T, int K>
+__device__ __forceinline__ void sym_multi_row(const T (&tr)[kSymTargets][Sym::R], const T* lds, int jb, int l16,
+                                              T (&facc)[kSymTargets][Sym::C], double (&rd)[Sym::C]) {
+    constexpr int E = sizeof(T) == 4 ? K + 16 / kSymTargets : 16;
+    T racc[Sym::C];
+#pragma unroll
+    for (int c = 0; c < Sym::C; ++c) racc[c] = T(0);
+    sym_multi_steps<Sym, T, K, E>(tr, lds, jb, l16, facc, racc);
+#pragma unroll
+    for (int c = 0; c < Sym::C; ++c) rd[c] += (double)racc[c];
+    if constexpr (E < 16) sym_multi_row<Sym, T, E>(tr, lds, jb, l16, facc, rd);
+}
+
+template <class Sym, typename T>
+__device__ __forceinline__ void sym_multi_body(const KArgs& a, const SymArgs& sa, int blk, T* srec, double* sracc) {
+    constexpr int R = Sym::R, C = Sym::C, NT = kSymTargets, G = 4 / NT;
+    static_assert(kTile == 256 && kTPB == 256 && NT == 2, "four units and quarters, four waves");
+    static_assert(block_terms<T>() >= 16, "a row rotation of 16 steps sums in T");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int first = sa.blocks[3 * blk], cnt = sa.blocks[3 * blk + 1], slot = sa.blocks[3 * blk + 2];
+    const int ta = sa.items[4 * first];
+    const T* rec = static_cast<const T*>(a.rec);
+    const int l16 = lane & 15, row = lane >> 4;
+    const int i0 = 64 * NT * (wave % G) + lane;  // target t of the lane is node i0 + 64 t of the tile
+    T tr[NT][R], x0[NT][3];
+    double acc[NT][C];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+#pragma unroll
+        for (int f = 0; f < R; ++f) tr[t][f] = rec[((int64_t)ta * kTile + i0 + 64 * t) * R + f];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) x0[t][c] = tr[t][c];  // in their own tile's frame
+#pragma unroll
+        for (int c = 0; c < C; ++c) acc[t][c] = 0.0;
+    }
+    T* rev = static_cast<T*>(sa.rev);
+    for (int it = first; it < first + cnt; ++it) {
+        const int tb = sa.items[4 * it + 1], p = sa.items[4 * it + 2];
+        if constexpr (sizeof(T) == 4) {  // the targets in the source tile's frame
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const T d = (float)(tile_centre(a, ta, c) - tile_centre(a, tb, c));
+#pragma unroll
+                for (int t = 0; t < NT; ++t) tr[t][c] = x0[t][c] + d;
+            }
+        }
+        __syncthreads();  // the previous tile pair is done with the LDS
+#pragma unroll
+        for (int f = 0; f < R; ++f) srec[f * kTile + tid] = rec[((int64_t)tb * kTile + tid) * R + f];
+#pragma unroll
+        for (int c = 0; c < C; ++c) sracc[c * kTile + tid] = 0.0;
+        __syncthreads();
+#pragma unroll 1
+        for (int ph = 0; ph < G; ++ph) {
+            const int q = wave ^ ph;
+#pragma unroll 1
+            for (int rr = 0; rr < 4; ++rr) {
+                const int jb = 64 * q + (((row + rr) & 3) << 4), j = jb + l16;
+                T facc[NT][C];
+                double rd[C];
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    rd[c] = 0.0;
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) facc[t][c] = T(0);
+                }
+                sym_multi_row<Sym, T, 0>(tr, srec, jb, l16, facc, rd);
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    sracc[c * kTile + j] += rd[c];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) acc[t][c] += (double)facc[t][c];
+                }
+            }
+            __syncthreads();  // each quarter's reverse sums go to the wave that takes it next
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) rev[((int64_t)p * C + c) * kTile + tid] = T(sracc[c * kTile + tid]);
+    }
+    __syncthreads();  // the reverse sums are read
+    if (wave >= G)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int c = 0; c < C; ++c) sracc[c * kTile + i0 + 64 * t] = acc[t][c];
+    __syncthreads();
+    if (wave < G)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                sa.fwd[((int64_t)slot * C + c) * kTile + i0 + 64 * t] = acc[t][c] + sracc[c * kTile + i0 + 64 * t];
+}
+
+// Left alone, the compiler hoists the LDS reads of a whole row rotation ahead of
+// its 16 steps (up to 134 VGPRs with one target to a lane, 3 waves per SIMD).  The
+// float passes are held to 7 waves per SIMD (one component) and 5 (three): n =
+// 272718 with 5, 6 and 7 Laplace double layer 16.2, 15.9, 15.8 ms; with 4, 5 and 6
+// Stokes double layer 27.5, 27.5, 27.9 ms, slip sum 36.9, 36.6, 37.2 ms.
+constexpr int sym_waves(int tsize, int c, bool pack) { return tsize == 8 ? 1 : pack ? 4 : c == 1 ? 7 : 5; }
 template <class Sym, typename T, bool PACK>
-__global__ __launch_bounds__(kTPB) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (PACK ? 4 : 8) : 1)))
+__global__ __launch_bounds__(kTPB) __attribute__((amdgpu_waves_per_eu(sym_waves(sizeof(T), Sym::C, PACK))))
 void sym_pass_pairs(KArgs a, SymArgs sa) {
-    if constexpr (PACK) completion_partials(a);
-    sym_body<Sym, T, true, PACK>(a, sa, blockIdx.x);
+    __shared__ T srec[Sym::R * kTile];
+    __shared__ double sracc[Sym::C * kTile];
+    if constexpr (PACK) {
+        completion_partials(a);
+    } else if (sa.items[4 * sa.blocks[3 * blockIdx.x] + 3] == kSymAll) {
+        // far pairs of one part (near and far items share no block)
+        sym_multi_body<Sym, T>(a, sa, blockIdx.x, srec, sracc);
+        return;
+    }
+    sym_body<Sym, T, true, PACK>(a, sa, blockIdx.x, srec, sracc);
 }
 
 // far pairs alone, then the one-direction near-field blocks (double)
 template <class Op, class Sym>
 __global__ __launch_bounds__(kTPB) void sym_far_near_pairs(KArgs a, SymArgs sa) {
-    if ((int)blockIdx.x < sa.nblocks) sym_body<Sym, double, false, false>(a, sa, blockIdx.x);
+    __shared__ double srec[Sym::R * kTile], sracc[Sym::C * kTile];
+    if ((int)blockIdx.x < sa.nblocks) sym_body<Sym, double, false, false>(a, sa, blockIdx.x, srec, sracc);
     else near_body<Op, double>(a, (int)blockIdx.x - sa.nblocks);
 }
 template <class Op, class Sym>
 __global__ __launch_bounds__(kTPB) void sym_far_near_small(KArgs a, SymArgs sa) {
-    if ((int)blockIdx.x < sa.nblocks) sym_body<Sym, double, false, false>(a, sa, blockIdx.x);
+    __shared__ double srec[Sym::R * kTile], sracc[Sym::C * kTile];
+    if ((int)blockIdx.x < sa.nblocks) sym_body<Sym, double, false, false>(a, sa, blockIdx.x, srec, sracc);
     else near_small_body<Op, double>(a, (int)blockIdx.x - sa.nblocks);
 }
 
