@@ -404,7 +404,7 @@ struct KArgs {
     const int32_t* perm;
     const int32_t* dperm;  // densities are in the caller's order (nullable; packing in the pass, see sym_body)
     int gather_c;
-    int near_waves;  // near_small_body: waves per 64 targets
+    int near_mode;  // 0: near_body, 1 and 2: near_split_body (2: by units)
     const double* dl_tgt;  // target density of the subtracted double layer (nullable: dl_dens)
     // position-gradient pass
     const double *g_p, *g_v, *g_u, *g_f, *g_l1, *g_l2;
@@ -538,16 +538,29 @@ struct LaplaceOp {
         }
         if (SL) tacc = fma(r[G], k1, tacc);
     }
+    // The terms of a pair cut in two (near_split_body): the values that cost the work,
+    // and the links of each component's chain of sums, operation for operation as in
+    // pair<NEAR> and terms.  axis: the coordinate of component c.
+    static constexpr int NV = 2 * DL + SL;
+    template <bool NEAR, class P>
+    __device__ __forceinline__ void values(P r, T dx, T dy, T dz, T k1, T k2, T, T, T (&v)[NV]) const {
+        if constexpr (DL) {
+            const T dn = fma(dx, r[NX], fma(dy, r[NY], dz * r[NZ]));
+            v[0] = (r[Q] - qi) * dn;
+            v[1] = k2;
+        }
+        if constexpr (SL) v[NV - 1] = k1;
+    }
+    template <bool NEAR, class P>
+    __device__ __forceinline__ void chain(P r, int, int, T, const T (&v)[NV], T& t) const {
+        if constexpr (DL) t = fma(v[0], v[1], t);
+        if constexpr (SL) t = fma(r[G], v[NV - 1], t);
+    }
+    __device__ __forceinline__ double scale(int) const { return 1.0; }
     __device__ __forceinline__ void flush() {
         acc += (double)tacc;
         tacc = T(0);
     }
-    // the double sums out (and cleared), and back in
-    __device__ __forceinline__ void take(double (&v)[C]) {
-        v[0] = acc;
-        acc = 0.0;
-    }
-    __device__ __forceinline__ void give(const double (&v)[C]) { acc = v[0]; }
     __device__ __forceinline__ void store(const KArgs& a, int slot, int64_t i) const {
         a.partial[(int64_t)slot * a.n + i] = acc;
     }
@@ -681,22 +694,44 @@ struct StokesOp {
         ty = fma(cd, dy, ty);
         tz = fma(cd, dz, tz);
     }
+    // see LaplaceOp::values
+    static constexpr int NV = SL ? 2 : 1;
+    template <bool NEAR, class P>
+    __device__ __forceinline__ void values(P r, T dx, T dy, T dz, T k1, T, T k3, T k4, T (&v)[NV]) const {
+        T ud = T(0), dn = T(0);
+        if constexpr (DL) {
+            const T ux = r[UX] - uix, uy = r[UY] - uiy, uz = r[UZ] - uiz;
+            ud = fma(ux, dx, fma(uy, dy, uz * dz));
+            dn = fma(dx, r[NX], fma(dy, r[NY], dz * r[NZ]));
+        }
+        if constexpr (SL) {
+            const T df = fma(dx, r[FX], fma(dy, r[FY], dz * r[FZ]));
+            if constexpr (NEAR) {
+                v[0] = fma(df, k3, DL ? ud * dn * k4 : T(0));
+            } else {
+                const T ir2 = k1 * k1;  // k1 = 1/r
+                v[0] = (DL ? fma(ud * dn, ir2, df) : df) * ir2;
+            }
+            v[1] = k1;
+        } else {
+            v[0] = ud * dn * k4;
+        }
+    }
+    template <bool NEAR, class P>
+    __device__ __forceinline__ void chain(P r, int c, int axis, T d, const T (&v)[NV], T& t) const {
+        if constexpr (SL && !NEAR) {
+            t = fma(fma(v[0], d, r[FX + c]), v[1], t);
+        } else {
+            if constexpr (SL) t = fma(r[FX + c], v[1], t);
+            t = fma(v[0], d, t);
+        }
+    }
+    __device__ __forceinline__ double scale(int) const { return 1.0; }
     __device__ __forceinline__ void flush() {
         ax += (double)tx;
         ay += (double)ty;
         az += (double)tz;
         tx = ty = tz = T(0);
-    }
-    __device__ __forceinline__ void take(double (&v)[C]) {
-        v[0] = ax;
-        v[1] = ay;
-        v[2] = az;
-        ax = ay = az = 0.0;
-    }
-    __device__ __forceinline__ void give(const double (&v)[C]) {
-        ax = v[0];
-        ay = v[1];
-        az = v[2];
     }
     __device__ __forceinline__ void store(const KArgs& a, int slot, int64_t i) const {
         double* o = a.partial + (int64_t)slot * 3 * a.n;
@@ -750,16 +785,21 @@ struct LaplaceTNOp {
         const T dn = fma(dx, nxi, fma(dy, nyi, dz * nzi));
         tacc = fma(r[3] * dn, k2, tacc);
     }
+    // see LaplaceOp::values
+    static constexpr int NV = 2;
+    template <bool NEAR, class P>
+    __device__ __forceinline__ void values(P r, T dx, T dy, T dz, T, T k2, T, T, T (&v)[NV]) const {
+        const T dn = fma(dx, nxi, fma(dy, nyi, dz * nzi));
+        v[0] = r[3] * dn;
+        v[1] = k2;
+    }
+    template <bool NEAR, class P>
+    __device__ __forceinline__ void chain(P, int, int, T, const T (&v)[NV], T& t) const { t = fma(v[0], v[1], t); }
+    __device__ __forceinline__ double scale(int) const { return 1.0; }
     __device__ __forceinline__ void flush() {
         acc += (double)tacc;
         tacc = T(0);
     }
-    // the double sums out (and cleared), and back in
-    __device__ __forceinline__ void take(double (&v)[C]) {
-        v[0] = acc;
-        acc = 0.0;
-    }
-    __device__ __forceinline__ void give(const double (&v)[C]) { acc = v[0]; }
     __device__ __forceinline__ void store(const KArgs& a, int slot, int64_t i) const {
         a.partial[(int64_t)slot * a.n + i] = acc;
     }
@@ -814,22 +854,21 @@ struct StokesTNOp {
         ty = fma(c, dy, ty);
         tz = fma(c, dz, tz);
     }
+    // see LaplaceOp::values
+    static constexpr int NV = 1;
+    template <bool NEAR, class P>
+    __device__ __forceinline__ void values(P r, T dx, T dy, T dz, T, T, T, T k4, T (&v)[NV]) const {
+        const T dq = fma(dx, r[3], fma(dy, r[4], dz * r[5]));
+        v[0] = dq * fma(dx, nxi, fma(dy, nyi, dz * nzi)) * k4;
+    }
+    template <bool NEAR, class P>
+    __device__ __forceinline__ void chain(P, int, int, T d, const T (&v)[NV], T& t) const { t = fma(v[0], d, t); }
+    __device__ __forceinline__ double scale(int) const { return 1.0; }
     __device__ __forceinline__ void flush() {
         ax += (double)tx;
         ay += (double)ty;
         az += (double)tz;
         tx = ty = tz = T(0);
-    }
-    __device__ __forceinline__ void take(double (&v)[C]) {
-        v[0] = ax;
-        v[1] = ay;
-        v[2] = az;
-        ax = ay = az = 0.0;
-    }
-    __device__ __forceinline__ void give(const double (&v)[C]) {
-        ax = v[0];
-        ay = v[1];
-        az = v[2];
     }
     __device__ __forceinline__ void store(const KArgs& a, int slot, int64_t i) const {
         double* o = a.partial + (int64_t)slot * 3 * a.n;
@@ -891,6 +930,21 @@ struct StokesTNSLOp {
         sy = fma(r[4], k1, fma(cs, dy, sy));
         sz = fma(r[5], k1, fma(cs, dz, sz));
     }
+    // see LaplaceOp::values
+    static constexpr int NV = 3;
+    template <bool NEAR, class P>
+    __device__ __forceinline__ void values(P r, T dx, T dy, T dz, T k1, T, T k3, T k4, T (&v)[NV]) const {
+        const T dq = fma(dx, r[3], fma(dy, r[4], dz * r[5]));
+        v[0] = dq * fma(dx, nxi, fma(dy, nyi, dz * nzi)) * k4;
+        v[1] = dq * k3;
+        v[2] = k1;
+    }
+    template <bool NEAR, class P>
+    __device__ __forceinline__ void chain(P r, int c, int axis, T d, const T (&v)[NV], T& t) const {
+        if (c < 3) t = fma(v[0], d, t);
+        else t = fma(r[3 + axis], v[2], fma(v[1], d, t));
+    }
+    __device__ __forceinline__ double scale(int c) const { return c < 3 ? 1.0 : sl_scale; }
     __device__ __forceinline__ void flush() {
         ax += (double)tx;
         ay += (double)ty;
@@ -899,23 +953,6 @@ struct StokesTNSLOp {
         by += (double)sy;
         bz += (double)sz;
         tx = ty = tz = sx = sy = sz = T(0);
-    }
-    __device__ __forceinline__ void take(double (&v)[C]) {
-        v[0] = ax;
-        v[1] = ay;
-        v[2] = az;
-        v[3] = bx;
-        v[4] = by;
-        v[5] = bz;
-        ax = ay = az = bx = by = bz = 0.0;
-    }
-    __device__ __forceinline__ void give(const double (&v)[C]) {
-        ax = v[0];
-        ay = v[1];
-        az = v[2];
-        bx = v[3];
-        by = v[4];
-        bz = v[5];
     }
     __device__ __forceinline__ void store(const KArgs& a, int slot, int64_t i) const {
         double* o = a.partial + (int64_t)slot * 6 * a.n;
@@ -1333,52 +1370,58 @@ __device__ __forceinline__ void near_body(const KArgs& a, int blk) {
     if (i < a.n) op.store(a, a.nsplit + split, i);
 }
 
-#ifndef SDBIE_NEAR_GROUP
-#define SDBIE_NEAR_GROUP 2
-#endif
-constexpr int kNearGroup = SDBIE_NEAR_GROUP;
-// N near pairs of a lane at once (double), added in the records' order
-template <class Op, int N>
-__device__ __forceinline__ void near_group(Op& op, src_ptr<double> r, double id, double id2, double rc2) {
-    double dx[N], dy[N], dz[N], r2[N], ir[N], k1[N], k2[N], k3[N], k4[N];
+// the values (Op::values) of N consecutive pairs of a lane
+template <class Op, typename T, bool NEAR, int N>
+__device__ __forceinline__ void pair_values(const Op& op, src_ptr<T> r, T id, T id2, T rc2, T (&v)[N][Op::NV]) {
+    T dx[N], dy[N], dz[N], r2[N], ir[N], k1[N], k2[N], k3[N], k4[N];
 #pragma unroll
     for (int u = 0; u < N; ++u) {
-        const src_ptr<double> q = r + u * Op::R;
+        const src_ptr<T> q = r + u * Op::R;
         dx[u] = op.xi - q[0];
         dy[u] = op.yi - q[1];
         dz[u] = op.zi - q[2];
         r2[u] = fma(dx[u], dx[u], fma(dy[u], dy[u], dz[u] * dz[u]));
-        ir[u] = rsq(r2[u]);
-        k1[u] = k2[u] = k3[u] = k4[u] = 0.0;
+        ir[u] = rsq_pair<NEAR>(r2[u]);
+        k1[u] = k2[u] = k3[u] = k4[u] = T(0);
         Op::plain(ir[u], k1[u], k2[u], k3[u], k4[u]);
     }
-    near_factors_n<N, Op::K1, Op::K2, Op::K3, Op::K4>(r2, ir, id, id2, rc2, k1, k2, k3, k4);
+    if constexpr (NEAR) {
+        if constexpr (sizeof(T) == 8) {
+            near_factors_n<N, Op::K1, Op::K2, Op::K3, Op::K4>(r2, ir, id, id2, rc2, k1, k2, k3, k4);
+        } else {
 #pragma unroll
-    for (int u = 0; u < N; ++u) op.terms(r + u * Op::R, dx[u], dy[u], dz[u], k1[u], k2[u], k3[u], k4[u]);
+            for (int u = 0; u < N; ++u)
+                if (r2[u] < rc2)
+                    near_factors<T, Op::K1, Op::K2, Op::K3, Op::K4>(r2[u], ir[u], id, id2, k1[u], k2[u], k3[u], k4[u]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+        op.template values<NEAR>(r + u * Op::R, dx[u], dy[u], dz[u], k1[u], k2[u], k3[u], k4[u], v[u]);
 }
 
-// Near-field pass of small surfaces: the same sums in the same order, with W = 2
-// or 4 waves on that many of the split's units at a time instead of one unit
-// after the other.  Each group of W waves owns 64 targets of one split; its waves
-// leave each unit's sums (in float: each 16-term block's) in LDS and the first of
-// them adds them in unit order.  With fewer near-field waves than the chip holds a pass takes as
-// long as one wave's chain of units (n = 2650: two units of 64 smoothed pairs,
-// 91 us for a double Stokes double layer; n = 9582 with 8 splits: a dozen units,
-// 530 us for a double single layer); the double steps also run two pairs at a
-// time, since registers are no limit there.
-template <class Op, typename T>
-__device__ __forceinline__ void near_small_body(const KArgs& a, int blk) {
-    constexpr int C = Op::C;
-    constexpr int NU = sizeof(T) == 8 ? kNearGroup : Op::U, FU = Op::U > 1 ? Op::U / 2 : 1;
-    constexpr int B = block_terms<T>() < kNearUnit ? block_terms<T>() : kNearUnit, NB = kNearUnit / B;
-    static_assert(B % NU == 0 && B % FU == 0, "blocks of whole unrolled steps");
-    constexpr int kWaves = kTPB / 64, kUnits = kTile / kNearUnit;
-    static_assert(kWaves == kUnits, "the groups of a block own units of one tile");
-    __shared__ double sh[kWaves][NB][C][64];
-    const int lane = threadIdx.x & 63, bwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int W = a.near_waves, group = bwave / W, wave = bwave % W;
-    const int split = blk % a.nsplit, tu = blk / a.nsplit * (kWaves / W) + group;  // target unit
-    const int b = tu / kUnits;
+// Near-field pass of small surfaces: the same sums in the same order, four waves
+// to a target unit of one split instead of one.  A wave's unit of smoothed pairs is
+// one long chain (64 steps of 260 double instructions, 30 to 40 us), and a pass of
+// n = 582 to 4302 holds only one to three such units for each SIMD of the chip.
+// UNITS = false: the four waves form the values of every fourth group of sources
+// of a unit, leave them in LDS, and wave c adds component c in source order, 3 to 5
+// instructions a source (two LDS buffers, one barrier a round).
+// UNITS = true: they take four units of the split at a time, and wave c adds
+// their sums in unit order.  That saves those instructions, and needs many units.
+// The rule between them and their figures: near_mode.
+template <class Op, typename T, bool UNITS>
+__device__ __forceinline__ void near_split_body(const KArgs& a, int blk) {
+    constexpr int C = Op::C, NV = Op::NV, NC = (C + 3) / 4;
+    constexpr int N = sizeof(T) == 8 ? 2 : 4, kRound = 4 * N;  // pairs of a lane at a time, sources of a round
+    constexpr int B = block_terms<T>() < kNearUnit ? block_terms<T>() : kNearUnit;
+    static_assert(kNearUnit % kRound == 0 && B % kRound == 0, "whole rounds");
+    static_assert(!UNITS || B == kNearUnit, "a unit is one chain of sums");
+    constexpr int kUnits = kTile / kNearUnit;
+    static_assert(kTPB == 256, "four waves");
+    __shared__ T sh[UNITS ? 1 : 2][UNITS ? 4 : kRound][UNITS ? C : NV][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int split = blk % a.nsplit, tu = blk / a.nsplit, b = tu / kUnits;  // tu: target unit
     const int64_t w0 = (int64_t)tu * 64, i = w0 + lane;  // < npad
     Op op;
     op.init(a, i);
@@ -1389,33 +1432,90 @@ __device__ __forceinline__ void near_small_body(const KArgs& a, int blk) {
     const src_ptr<double> wb = (src_ptr<double>)a.uboxes + (int64_t)tu * 6;
     const uint8_t* row = a.mask + (int64_t)b * a.ntiles;
     const src_ptr<T> rec = (src_ptr<T>)a.rec;
-    double sum[C];
+    T t[NC];  // components wave, wave + 4
+    double acc[NC];
 #pragma unroll
-    for (int c = 0; c < C; ++c) sum[c] = 0.0;
-    // the first m units of the round, in order
+    for (int m = 0; m < NC; ++m) {
+        t[m] = T(0);
+        acc[m] = 0.0;
+    }
+    int buf = 0;
+    auto shared_unit = [&](auto near, src_ptr<T> ru) {
+        constexpr bool NEAR = decltype(near)::value;
+#pragma unroll 1
+        for (int j = 0; j < kNearUnit; j += kRound, buf ^= 1) {
+            {
+                T v[N][NV];
+                pair_values<Op, T, NEAR, N>(op, ru + (j + wave * N) * Op::R, id, id2, rc2, v);
+#pragma unroll
+                for (int u = 0; u < N; ++u)
+#pragma unroll
+                    for (int k = 0; k < NV; ++k) sh[buf][wave * N + u][k][lane] = v[u][k];
+            }
+            __syncthreads();  // the round's values are there, and the last round's have been added
+#pragma unroll
+            for (int m = 0; m < NC; ++m) {
+                const int c = wave + 4 * m, axis = c < 3 ? c : c - 3;
+                if (c >= C) break;
+                const T x = axis == 0 ? op.xi : axis == 1 ? op.yi : op.zi;
+#pragma unroll
+                for (int u = 0; u < kRound; ++u) {
+                    const src_ptr<T> r = ru + (j + u) * Op::R;
+                    T v[NV];
+#pragma unroll
+                    for (int k = 0; k < NV; ++k) v[k] = sh[buf][u][k][lane];
+                    op.template chain<NEAR>(r, c, axis, x - r[axis], v, t[m]);
+                }
+                if ((j + kRound) % B == 0) {
+                    acc[m] += (double)t[m];
+                    t[m] = T(0);
+                }
+            }
+        }
+    };
+    auto own_unit = [&](auto near, src_ptr<T> ru) {
+        constexpr bool NEAR = decltype(near)::value;
+        T s[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) s[c] = T(0);
+#pragma unroll 1
+        for (int j = 0; j < kNearUnit; j += N) {
+            T v[N][NV];
+            pair_values<Op, T, NEAR, N>(op, ru + j * Op::R, id, id2, rc2, v);
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    const src_ptr<T> r = ru + (j + u) * Op::R;
+                    const int axis = c < 3 ? c : c - 3;
+                    op.template chain<NEAR>(r, c, axis, (axis == 0 ? op.xi : axis == 1 ? op.yi : op.zi) - r[axis],
+                                            v[u], s[c]);
+                }
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) sh[0][wave][c][lane] = s[c];
+    };
+    // UNITS: the first m units of the round, in order
     auto add_round = [&](int m) {
         __syncthreads();
-        if (wave == 0)
-            for (int u = 0; u < m; ++u)
+        for (int u = 0; u < m; ++u)
 #pragma unroll
-                for (int k = 0; k < NB; ++k)
-#pragma unroll
-                    for (int c = 0; c < C; ++c) sum[c] += sh[bwave + u][k][c][lane];
+            for (int k = 0; k < NC; ++k)
+                if (wave + 4 * k < C) acc[k] += (double)sh[0][u][wave + 4 * k][lane];
         __syncthreads();
     };
     int rank = 0, m = 0;  // near tiles seen; units of this split in the round
     for (int c0 = 0; c0 < a.ntiles; c0 += 64) {
         const bool f = (c0 + lane < a.ntiles) && row[c0 + lane];
-        uint64_t bal = __ballot(f);  // uniform
+        uint64_t bal = __ballot(f);  // the same in the four waves
         while (bal) {
-            const int t = c0 + __ffsll((long long)bal) - 1;
+            const int tile = c0 + __ffsll((long long)bal) - 1;
             bal &= bal - 1;
             for (int q = 0; q < kUnits; ++q) {
                 if ((rank * kUnits + q) % a.nsplit != split) continue;
-                if (m == wave) {
-                    targets_to_frame<T>(op, a, x0, b, t);
-                    const int64_t u0 = (int64_t)t * kTile + q * kNearUnit;
-                    const src_ptr<T> ru = rec + u0 * Op::R;
+                if (!UNITS || m == wave) {
+                    targets_to_frame<T>(op, a, x0, b, tile);
+                    const int64_t u0 = (int64_t)tile * kTile + q * kNearUnit;
                     bool far_unit = wave_full && u0 + kNearUnit <= a.n;
                     if (far_unit) {
                         const src_ptr<double> ub = (src_ptr<double>)a.uboxes + (u0 / kNearUnit) * 6;
@@ -1426,38 +1526,31 @@ __device__ __forceinline__ void near_small_body(const KArgs& a, int blk) {
                         }
                         far_unit = d2 >= a.rcu2;
                     }
-#pragma unroll 1
-                    for (int k = 0; k < NB; ++k) {
-                        if (far_unit) {
-#pragma unroll 1
-                            for (int jj = k * B; jj < (k + 1) * B; jj += FU)
-                                pair_group<Op, T, false, FU>(op, ru + jj * Op::R, id, id2, rc2);
-                        } else {
-#pragma unroll 1
-                            for (int jj = k * B; jj < (k + 1) * B; jj += NU) {
-                                if constexpr (sizeof(T) == 8) near_group<Op, NU>(op, ru + jj * Op::R, id, id2, rc2);
-                                else pair_group<Op, T, true, NU>(op, ru + jj * Op::R, id, id2, rc2);
-                            }
-                        }
-                        op.flush();
-                        double v[C];
-                        op.take(v);
-#pragma unroll
-                        for (int c = 0; c < C; ++c) sh[bwave][k][c][lane] = v[c];
+                    const src_ptr<T> ru = rec + u0 * Op::R;
+                    if constexpr (UNITS) {
+                        if (far_unit) own_unit(std::false_type(), ru);
+                        else own_unit(std::true_type(), ru);
+                    } else {
+                        if (far_unit) shared_unit(std::false_type(), ru);
+                        else shared_unit(std::true_type(), ru);
                     }
                 }
-                if (++m == W) {
-                    add_round(W);
+                if (UNITS && ++m == 4) {
+                    add_round(4);
                     m = 0;
                 }
             }
             ++rank;
         }
     }
-    add_round(m);
-    if (wave == 0 && i < a.n) {
-        op.give(sum);
-        op.store(a, a.nsplit + split, i);
+    if (UNITS) add_round(m);
+    if (i < a.n) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            const int c = wave + 4 * k;
+            if (c < C)
+                a.partial[((int64_t)(a.nsplit + split) * C + c) * a.n + i] = c < 3 ? acc[k] : op.scale(c) * acc[k];
+        }
     }
 }
 
@@ -1492,15 +1585,15 @@ __global__ __launch_bounds__(kTPB) __attribute__((amdgpu_waves_per_eu(8))) void 
     else near_body<Op, T>(a, (int)blockIdx.x - nfar);
 }
 
-// Both with the near-field blocks of small surfaces (near_waves times as many).
-template <class Op, typename T>
+// Both with the near-field blocks of small surfaces (one for each target unit and split).
+template <class Op, typename T, bool UNITS>
 __global__ __launch_bounds__(kTPB) void pass_pairs_small(KArgs a) {
     const int nfar = a.ntiles * a.nsplit;
     if ((int)blockIdx.x < nfar) {
         if constexpr (sizeof(T) == 4 && SDBIE_FAR_LDS) far_lds_body<Op>(a, blockIdx.x);
         else far_body<Op, T>(a, blockIdx.x);
     } else {
-        near_small_body<Op, T>(a, (int)blockIdx.x - nfar);
+        near_split_body<Op, T, UNITS>(a, (int)blockIdx.x - nfar);
     }
 }
 
@@ -2287,7 +2380,7 @@ template <class Op, class Sym>
 __global__ __launch_bounds__(kTPB) void sym_far_near_small(KArgs a, SymArgs sa) {
     __shared__ double srec[Sym::R * kTile], sracc[Sym::C * kTile];
     if ((int)blockIdx.x < sa.nblocks) sym_body<Sym, double, false, false>(a, sa, blockIdx.x, srec, sracc);
-    else near_small_body<Op, double>(a, (int)blockIdx.x - sa.nblocks);
+    else near_split_body<Op, double, false>(a, (int)blockIdx.x - sa.nblocks);
 }
 
 // Sum of the symmetric pass per target, in a fixed order, then the terms of
@@ -2328,7 +2421,7 @@ __global__ __launch_bounds__(kEpiThreads) void sym_epilogue(
     if (g == 0 && i < n) epi_finish<C>(n, i, v, tw, base, bperm, base_scale, comp != nullptr, cs, nrm, add0, add1, add2, out, perm);
 }
 
-int near_waves(const Plan& P, bool mixed);
+int near_mode(const Plan& P, bool mixed);
 
 KArgs make_args(const Plan& P, const PassDesc& d, int nsplit, double cut, int comps) {
     KArgs a;
@@ -2365,7 +2458,7 @@ KArgs make_args(const Plan& P, const PassDesc& d, int nsplit, double cut, int co
     a.perm = P.perm;
     a.dperm = nullptr;
     a.gather_c = comps;
-    a.near_waves = near_waves(P, d.mixed);
+    a.near_mode = near_mode(P, d.mixed);
     a.g_p = a.g_v = a.g_u = a.g_f = a.g_l1 = a.g_l2 = nullptr;
     a.g_mu = a.g_K = 1.0;
     return a;
@@ -2376,17 +2469,21 @@ struct family_is_gradient { static constexpr bool value = false; };
 template <bool SWAP>
 struct family_is_gradient<GradOp<SWAP>> { static constexpr bool value = true; };
 
-// Waves on one target unit's near units: more than one when the near blocks of a
-// pass (four waves each) leave wave slots of the chip empty (256 CUs, 32 waves
-// each) and a split holds more than one near unit on average, so that there is a
-// chain to cut; as many as there are units, since a wave without one only holds
-// registers.  Double, coupled solve at n = 2650 (32 splits, 1.3 units each): 77 ms
-// with one wave, 58 with two, 64 with four; drag gradient at n = 4302 (64
-// splits, 1.06 units each): 210, -, 237 ms.
-int near_waves(const Plan& P, bool mixed) {
-    if ((int64_t)P.ntiles * P.nsplit * 4 >= 256 * 32) return 1;
+// How the near blocks take a target unit of a split: one wave (0), four waves on each
+// of the split's near units (1), or four waves on four units at a time (2).  One wave
+// once the near blocks of four units each fill half the chip's wave slots (256 CUs,
+// 32 waves each) and a split holds at most two units.  Measured, 0 / 1: double
+// coupled solve (3 iterations, ms) n = 582 9.9 / 5.0, n = 1490 22.6 / 10.8, n = 2650
+// 20.3 / 14.0; at n = 4302 (64 splits, 17 waves per CU, one unit to a split) its
+// passes are equal, and the drag gradient, with the longer adjoint sums, takes 193 /
+// 201 ms.  Eight splits (the allocation-free sums), us, 0 / 1 / 2: n = 4302 420 / 221
+// / 241 (8 units to a split), n = 9582 637 / 398 / 384 (12), n = 17070 914 / 757 / 671,
+// n = 28014 1460 / 1326 / 1180; in float 1 is the faster one there too (718, 768).
+int near_mode(const Plan& P, bool mixed) {
+    const int64_t waves = (int64_t)P.ntiles * P.nsplit * 4;
     const double units = (mixed ? P.near_pairs32 : P.near_pairs64) / ((double)P.n * kNearUnit) / P.nsplit;
-    return units > 2.2 ? 4 : units > 1.15 ? 2 : 1;
+    if (waves >= 256 * 32 || (waves >= 256 * 16 && units <= 2.0)) return 0;
+    return !mixed && units > 10.0 ? 2 : 1;
 }
 
 const SymSet& sym_set(const Plan& P, bool mixed) {
@@ -2437,10 +2534,9 @@ bool launch_pair_kernels(const Plan& P, const KArgs& a, hipStream_t st, int fami
             ProfScope prof(prof_variant(family, mixed, code, 4), all, st);
             if constexpr (sizeof(T) == 8) {
                 if (P.far_only64) {
-                    if (a.near_waves > 1)
+                    if (a.near_mode)
                         hipLaunchKernelGGL((sym_far_near_small<Op, Sym>),
-                                           dim3((unsigned)(sa.nblocks + a.near_waves * a.ntiles * a.nsplit)), dim3(kTPB), 0, st,
-                                           a, sa);
+                                           dim3((unsigned)(sa.nblocks + 4 * a.ntiles * a.nsplit)), dim3(kTPB), 0, st, a, sa);
                     else
                         hipLaunchKernelGGL((sym_far_near_pairs<Op, Sym>),
                                            dim3((unsigned)(sa.nblocks + a.ntiles * a.nsplit)), dim3(kTPB), 0, st, a,
@@ -2473,8 +2569,10 @@ bool launch_pair_kernels(const Plan& P, const KArgs& a, hipStream_t st, int fami
         ProfScope prof(prof_variant(family, mixed, code, 3), all, st);
         if constexpr (family_is_gradient<Op>::value)
             hipLaunchKernelGGL((pass_pairs_wide<Op, T>), dim3(2 * grid.x), dim3(kTPB), 0, st, a);
-        else if (a.near_waves > 1)
-            hipLaunchKernelGGL((pass_pairs_small<Op, T>), dim3((1 + a.near_waves) * grid.x), dim3(kTPB), 0, st, a);
+        else if (sizeof(T) == 8 && a.near_mode == 2)
+            hipLaunchKernelGGL((pass_pairs_small<Op, T, sizeof(T) == 8>), dim3(5 * grid.x), dim3(kTPB), 0, st, a);
+        else if (a.near_mode)
+            hipLaunchKernelGGL((pass_pairs_small<Op, T, false>), dim3(5 * grid.x), dim3(kTPB), 0, st, a);
         else if constexpr (sizeof(T) == 4 && SDBIE_FAR_LDS)
             hipLaunchKernelGGL((pass_pairs_lds<Op>), dim3(2 * grid.x), dim3(kTPB), 0, st, a);
         else
