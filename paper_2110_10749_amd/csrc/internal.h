@@ -174,7 +174,7 @@ struct SymSet {
     int32_t* fwd_start = nullptr;  // [ntiles + 1]
     int32_t* rev_start = nullptr;  // [ntiles + 1]
     double* fwd = nullptr;         // [nblocks][C][kTile] forward partials of the target tile, C <= 3
-    void* rev = nullptr;           // [slots][C][kTile] reverse partials of the source tile (pass precision)
+    void* rev = nullptr;           // [slots][C][kTile doubles] reverse partials of the source tile (rev_slot)
 };
 constexpr int kSymRowInts = 16;
 

@@ -1758,6 +1758,8 @@ struct SymLaplace {
     using Op = LaplaceOp<T, DL, SL, SUB>;
     static constexpr int C = 1, R = Op::R;
     static constexpr int kFamilyBit = SDBIE_SYM_LAPLACE;
+    // near steps serve both directions (see sym_body)
+    static constexpr bool kNearBoth = sizeof(T) == 8 || !DL || SUB;
     static constexpr int Q = Op::Q, NX = Op::NX, NY = Op::NY, NZ = Op::NZ, G = Op::G;
     template <int K, class Src>
     __device__ __forceinline__ static void step(const T (&tr)[R], const Src& sr, T (&acc)[C], T (&racc)[C]) {
@@ -1847,6 +1849,7 @@ struct SymStokes {
     using Op = StokesOp<T, DL, SL, SUB, SLIP>;
     static constexpr int C = 3, R = Op::R;
     static constexpr int kFamilyBit = SDBIE_SYM_STOKES;
+    static constexpr bool kNearBoth = sizeof(T) == 8 || !DL || (SL && SUB);
     static constexpr int NX = Op::NX, NY = Op::NY, NZ = Op::NZ, UX = Op::UX, UY = Op::UY, UZ = Op::UZ;
     static constexpr int FX = Op::FX, FY = Op::FY, FZ = Op::FZ;
     template <int K, class Src>
@@ -1973,6 +1976,13 @@ struct SymStokes {
     }
 };
 
+// Reverse sums of a tile pair's component, slots of kTile doubles: those of a near
+// pair in double, of a far one in the pass's type.
+template <typename T>
+__device__ __forceinline__ T* rev_slot(void* rev, int64_t s) {
+    return reinterpret_cast<T*>(static_cast<double*>(rev) + s * kTile);
+}
+
 template <class Op> struct SymOf { using type = void; };
 template <typename T, bool DL, bool SL, bool SUB>
 struct SymOf<LaplaceOp<T, DL, SL, SUB>> { using type = SymLaplace<T, DL, SL, SUB>; };
@@ -2030,19 +2040,24 @@ struct SymArgs {
 // Near tile pairs run here too: each (wave, quarter) of a near pair whose unit
 // boxes are at least the cutoff apart takes the far steps, the others a loop of
 // steps with the smoothed factors.
-//   double: those steps serve both directions as well (the smoothing is most of
-//   a near pair's work).  The reverse sums go to the source's sum in LDS with
+//   Sym::kNearBoth: those steps serve both directions as well (the smoothing is most
+//   of a near pair's work).  The reverse sums go to the source's sum in LDS with
 //   one LDS add each; a wave owns its quarter during a phase and its 64 lanes
 //   meet 64 distinct sources, so the order of the additions is fixed.  A tile
 //   against itself (b = a): phase 0 is each wave's unit with itself (one
 //   direction, self pairs included), phase 1 the unit pairs (w, w + 1), phase 2
 //   the pairs (0, 2) and (1, 3), half of whose rotations each of the two waves
-//   takes; the reverse sums are the tile's own.
-//   float: one direction, from items of both orders (b > a with the far steps
+//   takes; the reverse sums are the tile's own.  The reverse sums of a near tile
+//   pair are stored in double in float passes too, as their forward ones are.
+//   Otherwise: one direction, from items of both orders (b > a with the far steps
 //   of the pair, b < a without), so that each direction's close pairs keep
-//   coordinates in the frame of their own source tile: the raw double layer of
-//   a rough density moves by 1e-6 of its largest value with the frame.  A tile
-//   against itself takes all 16 rotations, one direction.
+//   coordinates in the frame of their own source tile.  The float double layers
+//   without a single layer: of a rough density the raw one moves by 1e-6 of its
+//   largest value with the frame, the subtracted Stokes one by up to 3e-7 (neither
+//   is the more accurate).  A tile against itself takes all 16 rotations, one direction.
+//   Measured with both directions at once, us a float pass, before and after: slip sum
+//   n = 9582 135 and 97, n = 17070 238 and 211, n = 28014 529 and 484, n = 68166 2640
+//   and 2500; Laplace single layer n = 17070 115 and 96, n = 68166 865 and 795.
 // NEAR = false: a set without near pairs.
 //
 // PACK: every block forms the records it needs itself, from the staged nodes and
@@ -2056,7 +2071,7 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
     static_assert(kTile == kTPB && kTile == 256, "one target and one staged source per thread, four waves");
     static_assert(kNearUnit == 64, "a wave's targets and a quarter of the sources are units");
     static_assert(block_terms<T>() >= 16, "a row rotation of 16 steps sums in T");
-    constexpr bool kNearBoth = sizeof(T) == 8;  // near steps serve both directions
+    constexpr bool kNearBoth = Sym::kNearBoth;
     // srec: R * kTile, the source tile, field-major: field f of source j at srec[f * kTile + j]
     // sracc: C * kTile, reverse sums of the tile pair, one 16-step rotation at a time
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2078,14 +2093,15 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
     double acc[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) acc[c] = 0.0;
-    T* rev = static_cast<T*>(sa.rev);
     constexpr unsigned DPP = sym_dpp_fields<T>();
     SymSrc<T, R, DPP> src;
     src.lds = srec;
     src.l16 = lane & 15;
     for (int it = first; it < first + cnt; ++it) {
-        const int tb = sa.items[4 * it + 1], p = sa.items[4 * it + 2], steps = sa.items[4 * it + 3];
+        const int tb = sa.items[4 * it + 1], p = sa.items[4 * it + 2];
         const bool self = tb == ta;
+        const int steps = sa.items[4 * it + 3] & (kNearBoth && self ? kSymSelf | kSymNear : ~0);
+        if (kNearBoth && tb < ta) continue;  // float sets: the item of the other order
         if constexpr (sizeof(T) == 4) {  // the targets in the source tile's frame
 #pragma unroll
             for (int c = 0; c < 3; ++c) tr[c] = x0[c] + (float)(tile_centre(a, ta, c) - tile_centre(a, tb, c));
@@ -2124,7 +2140,7 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
             // registers with 2, and is no faster with the shorter forms either (434 us
             // against 423 at n = 17070): one pair by near_factors.
             constexpr bool kBoth = Op::K1 && Op::K4;
-            constexpr int G = !kNearBoth || kBoth ? 1 : C == 1 && !Op::K2 ? 4 : 2;
+            constexpr int G = sizeof(T) == 4 || kBoth ? 1 : C == 1 && !Op::K2 ? 4 : 2;
             T facc[C];
 #pragma unroll
             for (int c = 0; c < C; ++c) facc[c] = T(0);
@@ -2142,7 +2158,7 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
                     k1[u] = k2[u] = k3[u] = k4[u] = T(0);
                     Op::plain(ir[u], k1[u], k2[u], k3[u], k4[u]);
                 }
-                if constexpr (kNearBoth && !kBoth)
+                if constexpr (sizeof(T) == 8 && !kBoth)
                     near_factors_sym<G, Op::K1, Op::K2, Op::K3, Op::K4>(r2, ir, id, id2, rc2, k1, k2, k3, k4);
                 else if (r2[0] < rc2)
                     near_factors<T, Op::K1, Op::K2, Op::K3, Op::K4>(r2[0], ir[0], id, id2, k1[0], k2[0], k3[0], k4[0]);
@@ -2216,7 +2232,11 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
             for (int c = 0; c < C; ++c) acc[c] += sracc[c * kTile + tid];
         } else if (kNearBoth || tb > ta) {
 #pragma unroll
-            for (int c = 0; c < C; ++c) rev[((int64_t)p * C + c) * kTile + tid] = T(sracc[c * kTile + tid]);
+            for (int c = 0; c < C; ++c) {
+                const int64_t s = (int64_t)p * C + c;
+                if (NEAR && (steps & kSymNear)) rev_slot<double>(sa.rev, s)[tid] = sracc[c * kTile + tid];
+                else rev_slot<T>(sa.rev, s)[tid] = T(sracc[c * kTile + tid]);
+            }
         }
     }
 #pragma unroll
@@ -2289,7 +2309,6 @@ __device__ __forceinline__ void sym_multi_body(const KArgs& a, const SymArgs& sa
 #pragma unroll
         for (int c = 0; c < C; ++c) acc[t][c] = 0.0;
     }
-    T* rev = static_cast<T*>(sa.rev);
     for (int it = first; it < first + cnt; ++it) {
         const int tb = sa.items[4 * it + 1], p = sa.items[4 * it + 2];
         if constexpr (sizeof(T) == 4) {  // the targets in the source tile's frame
@@ -2331,7 +2350,7 @@ __device__ __forceinline__ void sym_multi_body(const KArgs& a, const SymArgs& sa
             __syncthreads();  // each quarter's reverse sums go to the wave that takes it next
         }
 #pragma unroll
-        for (int c = 0; c < C; ++c) rev[((int64_t)p * C + c) * kTile + tid] = T(sracc[c * kTile + tid]);
+        for (int c = 0; c < C; ++c) rev_slot<T>(sa.rev, (int64_t)p * C + c)[tid] = T(sracc[c * kTile + tid]);
     }
     __syncthreads();  // the reverse sums are read
     if (wave >= G)
@@ -2391,7 +2410,7 @@ __global__ __launch_bounds__(kTPB) void sym_far_near_small(KArgs a, SymArgs sa) 
 template <int C, typename RT>
 __global__ __launch_bounds__(kEpiThreads) void sym_epilogue(
     int64_t n, const int32_t* __restrict__ fwd_start, const double* __restrict__ fwd,
-    const int32_t* __restrict__ rev_start, const RT* __restrict__ rev, int nsplit,
+    const int32_t* __restrict__ rev_start, void* rev, const uint8_t* __restrict__ mask, int ntiles, int parts, int nsplit,
     const double* __restrict__ partial, const double* __restrict__ tw, const double* base,
     const int32_t* __restrict__ bperm, double base_scale, const double* __restrict__ comp, double comp_scale, const double* __restrict__ nrm, double add0, double add1,
     double add2, double* out, const int32_t* __restrict__ perm) {
@@ -2404,15 +2423,20 @@ __global__ __launch_bounds__(kEpiThreads) void sym_epilogue(
     for (int c = 0; c < C; ++c) v[c] = 0.0;
     if (i < n) {
         const int64_t t = i / kTile, j = i % kTile;
-        const int b1 = fwd_start[t + 1], p1 = rev_start[t + 1];
+        const int b1 = fwd_start[t + 1], p0 = rev_start[t], p1 = rev_start[t + 1];
+        const int shift = __ffs(parts) - 1;  // slot p: pair (t, (p - p0) / parts)
 #pragma unroll 4
         for (int b = fwd_start[t] + g; b < b1; b += kEpiGroups)
 #pragma unroll
             for (int c = 0; c < C; ++c) v[c] += fwd[((int64_t)b * C + c) * kTile + j];
 #pragma unroll 4
-        for (int p = rev_start[t] + g; p < p1; p += kEpiGroups)
+        for (int p = p0 + g; p < p1; p += kEpiGroups)
 #pragma unroll
-            for (int c = 0; c < C; ++c) v[c] += (double)rev[((int64_t)p * C + c) * kTile + j];
+            for (int c = 0; c < C; ++c) {
+                const int64_t s = (int64_t)p * C + c;
+                if (sizeof(RT) == 8 || mask[t * ntiles + ((p - p0) >> shift)]) v[c] += rev_slot<double>(rev, s)[j];
+                else v[c] += (double)rev_slot<RT>(rev, s)[j];
+            }
         for (int sl = g; sl < nsplit; sl += kEpiGroups)
 #pragma unroll
             for (int c = 0; c < C; ++c) v[c] += partial[((int64_t)(nsplit + sl) * C + c) * n + i];
@@ -2616,12 +2640,14 @@ void launch_epilogue(const Plan& P, const PassDesc& d, int S, bool sym, hipStrea
         const int32_t* bperm = raw ? (const int32_t*)P.perm : nullptr;
         if (d.mixed)
             hipLaunchKernelGGL((sym_epilogue<C, float>), dim3(eb), et, 0, st, P.n, (const int32_t*)Y.fwd_start,
-                               (const double*)Y.fwd, (const int32_t*)Y.rev_start, (const float*)Y.rev, nsplit,
+                               (const double*)Y.fwd, (const int32_t*)Y.rev_start, Y.rev, (const uint8_t*)P.mask32, P.ntiles,
+                               Y.parts, nsplit,
                                (const double*)P.partial, tw, base, bperm, d.base_scale, comp, d.comp_scale,
                                (const double*)P.nrm, a0, a1, a2, d.out, perm);
         else
             hipLaunchKernelGGL((sym_epilogue<C, double>), dim3(eb), et, 0, st, P.n, (const int32_t*)Y.fwd_start,
-                               (const double*)Y.fwd, (const int32_t*)Y.rev_start, (const double*)Y.rev, nsplit,
+                               (const double*)Y.fwd, (const int32_t*)Y.rev_start, Y.rev, (const uint8_t*)nullptr, P.ntiles,
+                               Y.parts, nsplit,
                                (const double*)P.partial, tw, base, bperm, d.base_scale, comp, d.comp_scale,
                                (const double*)P.nrm, a0, a1, a2, d.out, perm);
     } else {
