@@ -151,8 +151,9 @@ void sdbie_default_opts(sdbie_opts* o);
  * (n/256)^2 * 3471, with S the source splits of a pair pass (a multiple of 8
  * up to 64: 64 at n = 4096, 16 at n = 68166, 8 from n = 131072 on); the
  * quadratic term is the tile masks and the work lists and partial sums of the
- * symmetric far field (sdbie_plan_set_symmetric): 0.84 GB at n = 68166,
- * 9.4 GB at n = 351866 with max_restart = 50.  Above n = 524288 a plan holds
+ * symmetric passes (sdbie_plan_set_symmetric): 0.84 GB at n = 68166,
+ * 9.4 GB at n = 351866 with max_restart = 50.  Small plans hold up to 12 MiB
+ * more, the partial sums of tile pairs cut into parts.  Above n = 524288 a plan holds
  * no symmetric lists (the quadratic term drops to the masks, (n/256)^2 * 2)
  * and runs every pass one direction at a time. */
 size_t sdbie_workspace_bytes(int64_t n, int max_restart);
@@ -169,20 +170,23 @@ int sdbie_plan_create(sdbie_plan* plan, const sdbie_surface* s, int max_restart,
 int sdbie_plan_destroy(sdbie_plan plan);
 int64_t sdbie_plan_n(sdbie_plan plan);
 
-/* Target-source symmetric far field (section "Numerical Results", local
+/* Target-source symmetric passes (section "Numerical Results", local
  * problems: the paper's code evaluates each pair of nodes once for both
  * directions).  `families` is a mask of SDBIE_SYM_LAPLACE and SDBIE_SYM_STOKES
  * (the Laplace or Stokes passes with float pairs) and SDBIE_SYM_LAPLACE_F64
  * and SDBIE_SYM_STOKES_F64 (the same with double pairs): in every later layer
  * sum and solve on the plan (the transposed sums of ddm_adjoint excepted) a
- * pass of a selected kind evaluates each tile pair whose node pairs all lie
- * beyond the smoothing cutoff once, adding its contributions to the targets
- * of both tiles; near tile pairs stay one pass per direction.  Same sums up to
- * rounding.  0: every ordered pair in its own pass.  Plans of more than 524288
- * nodes have no room for the symmetric lists and keep every pass
- * one-directional whatever the mask.  The default, SDBIE_SYM_DEFAULT, selects
- * every kind: each is at least as fast symmetric on gfx950.  ERR_ARG for a
- * null plan or unknown bits. */
+ * pass of a selected kind evaluates each pair of nodes once for both
+ * directions, except close pairs of float double layers without a single layer
+ * (the subtracted Laplace one excepted), which take one evaluation for each.
+ * The double sums of FP64 coupled solves and adjoints evaluate only
+ * the tile pairs whose node pairs all lie beyond the smoothing cutoff that
+ * way: their inexact interface products make the result, within tol_ddm,
+ * depend on the order of every sum, and that order is kept.  Same sums up to rounding.  0: every ordered pair in its own
+ * pass.  Plans of more than 524288 nodes have no room for the symmetric lists
+ * and keep every pass one-directional whatever the mask.  The default,
+ * SDBIE_SYM_DEFAULT, selects every kind: each is faster symmetric on gfx950.
+ * ERR_ARG for a null plan or unknown bits. */
 #define SDBIE_SYM_LAPLACE 1
 #define SDBIE_SYM_STOKES 2
 #define SDBIE_SYM_LAPLACE_F64 4

@@ -15,8 +15,9 @@
 // round-robin dispatch over the 8 XCDs gives each XCD a fixed subset of the
 // source chunks (and its L2 only those sources).  The float far-field kernel
 // stages source tiles in LDS and reads them back as broadcast loads into
-// VGPRs; the other kernels read source records at wave-uniform addresses
-// through the scalar cache into SGPRs.
+// VGPRs; the other one-direction kernels read source records at wave-uniform
+// addresses through the scalar cache into SGPRs.  The symmetric passes (the
+// default of the layer sums and most solves) walk work lists of tile pairs.
 // Partial sums per split go to a scratch array and an epilogue kernel adds
 // them in a fixed order (no atomics: results are bitwise reproducible).
 //
@@ -1646,8 +1647,9 @@ __device__ __forceinline__ double epi_completion(const double* __restrict__ comp
 template <int C>
 __device__ __forceinline__ void epi_finish(int64_t n, int64_t i, const double (&v)[C],
                                            const double* __restrict__ tw, const double* base,
-                                           const int32_t* __restrict__ bperm, double base_scale, bool comp, double cs, const double* __restrict__ nrm, double add0,
-                                           double add1, double add2, double* out, const int32_t* __restrict__ perm) {
+                                           const int32_t* __restrict__ bperm, double base_scale, bool comp, double cs,
+                                           const double* __restrict__ nrm, double add0, double add1, double add2,
+                                           double* out, const int32_t* __restrict__ perm) {
     const int64_t o = perm ? (int64_t)perm[i] : i, b = bperm ? (int64_t)bperm[i] : i;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
@@ -1678,15 +1680,16 @@ __global__ __launch_bounds__(kEpiThreads) void epilogue(int64_t n, int nslots, c
 #pragma unroll
             for (int c = 0; c < C; ++c) v[c] += partial[((int64_t)sl * C + c) * n + i];
     epi_combine<C>(v, g, jj);
-    if (g == 0 && i < n) epi_finish<C>(n, i, v, tw, base, nullptr, base_scale, comp != nullptr, cs, nrm, add0, add1, add2, out, perm);
+    if (g == 0 && i < n)
+        epi_finish<C>(n, i, v, tw, base, nullptr, base_scale, comp != nullptr, cs, nrm, add0, add1, add2, out, perm);
 }
 
 // --------------------------------------------------------------------------
-// Target-source symmetric far field.  The pair kernels are even (single
+// Target-source symmetric passes.  The pair kernels are even (single
 // layers) or odd (double layers) in D = x_i - x_j, so the two ordered pairs of
 // one unordered pair share the geometry (D, r, 1/r) and most of the kernel
-// algebra; the paper's CPU code halves its pair work this way.  Here each far
-// tile pair {a, b} (a < b, every pair beyond the cutoff) is evaluated once:
+// algebra; the paper's CPU code halves its pair work this way.  Here each
+// tile pair {a, b} (a <= b) is evaluated once (close pairs: see sym_body):
 // every lane of a block holds one target of tile a and, in turn, one source
 // of tile b.  Within a wave the sources rotate across the 16 lanes of each
 // row: at step K lane l meets the source of lane (l - K) mod 16, its fields
@@ -1694,13 +1697,12 @@ __global__ __launch_bounds__(kEpiThreads) void epilogue(int64_t n, int nslots, c
 // taken by DPP row rotations of the lane's own record), so at every step each lane
 // evaluates one pair, adds the forward contribution to its own target and
 // hands the reverse one back to the source's lane through the inverse
-// rotation.  A wave meets its 64
-// targets with a quarter of the 256 sources per phase (4 row rotations of 16
-// steps); the quarters' reverse sums pass between the waves in LDS, as double
-// sums to which each row rotation adds its 16 terms.
+// rotation.  A wave meets its 64 targets with a quarter of the 256 sources per
+// phase (4 row rotations of 16 steps); the quarters' reverse sums pass between
+// the waves in LDS, as double sums to which each row rotation adds its 16 terms.
 // Forward sums of the target tile go to one slot per block, reverse sums of
 // the source tile to one slot per tile pair; the symmetric epilogue adds them
-// (and the near-field slots) in a fixed order.
+// (of a far-only set with the near-field slots) in a fixed order.
 // --------------------------------------------------------------------------
 
 // lane l of a 16-lane row reads lane (l - K) mod 16 of the same row (DPP
@@ -2028,7 +2030,7 @@ struct SymArgs {
     const int32_t* items;   // [nitems][4]: target tile a, source tile b >= a, reverse slot, steps (kSym*)
     const int32_t* blocks;  // [nblocks][3]: first item, item count, forward slot
     double* fwd;            // [slots][C][kTile]
-    void* rev;              // [slots][C][kTile] of T
+    void* rev;              // see rev_slot
 };
 
 // The (wave, quarter, row rotation) steps of one tile pair: bit 4 ph + rr of an
@@ -2410,10 +2412,11 @@ __global__ __launch_bounds__(kTPB) void sym_far_near_small(KArgs a, SymArgs sa) 
 template <int C, typename RT>
 __global__ __launch_bounds__(kEpiThreads) void sym_epilogue(
     int64_t n, const int32_t* __restrict__ fwd_start, const double* __restrict__ fwd,
-    const int32_t* __restrict__ rev_start, void* rev, const uint8_t* __restrict__ mask, int ntiles, int parts, int nsplit,
-    const double* __restrict__ partial, const double* __restrict__ tw, const double* base,
-    const int32_t* __restrict__ bperm, double base_scale, const double* __restrict__ comp, double comp_scale, const double* __restrict__ nrm, double add0, double add1,
-    double add2, double* out, const int32_t* __restrict__ perm) {
+    const int32_t* __restrict__ rev_start, void* rev, const uint8_t* __restrict__ mask, int ntiles, int parts,
+    int nsplit, const double* __restrict__ partial, const double* __restrict__ tw, const double* base,
+    const int32_t* __restrict__ bperm, double base_scale, const double* __restrict__ comp, double comp_scale,
+    const double* __restrict__ nrm, double add0, double add1, double add2, double* out,
+    const int32_t* __restrict__ perm) {
     static_assert(kTile % kEpiTargets == 0, "a block's targets lie in one tile");
     const int g = threadIdx.x / kEpiTargets, jj = threadIdx.x % kEpiTargets;
     const int64_t i = (int64_t)blockIdx.x * kEpiTargets + jj;
@@ -2442,7 +2445,8 @@ __global__ __launch_bounds__(kEpiThreads) void sym_epilogue(
             for (int c = 0; c < C; ++c) v[c] += partial[((int64_t)(nsplit + sl) * C + c) * n + i];
     }
     epi_combine<C>(v, g, jj);
-    if (g == 0 && i < n) epi_finish<C>(n, i, v, tw, base, bperm, base_scale, comp != nullptr, cs, nrm, add0, add1, add2, out, perm);
+    if (g == 0 && i < n)
+        epi_finish<C>(n, i, v, tw, base, bperm, base_scale, comp != nullptr, cs, nrm, add0, add1, add2, out, perm);
 }
 
 int near_mode(const Plan& P, bool mixed);
