@@ -40,7 +40,7 @@ constexpr int64_t kSymMaxTiles = 2048;  // 524288 nodes: 14.7 GB of lists and sl
 bool sym_fits(int64_t nt) { return nt <= kSymMaxTiles; }
 int64_t sym_max_pairs(int64_t nt) { return nt * (nt - 1) / 2; }
 int64_t sym_max_items(int64_t nt, int k) {
-    return k == kSymFar64 ? sym_max_pairs(nt) : (k == kSymF32 ? nt * nt : nt * (nt + 1) / 2) * sym_parts(nt, k);
+    return k == kSymFar64 ? sym_max_pairs(nt) : (k == kSymF32 ? nt * nt : nt * (nt + 1) / 2) * sym_parts(nt);
 }
 int64_t sym_max_slots(int64_t nt) { return (sym_max_pairs(nt) + nt) / kSymChunk + 2 * nt; }
 
@@ -49,7 +49,7 @@ int64_t sym_max_slots(int64_t nt) { return (sym_max_pairs(nt) + nt) / kSymChunk 
 // block partials of the Krylov steps
 size_t min_partial(int64_t n) {
     const int64_t nt = (n + kTile - 1) / kTile;
-    const size_t slots = (size_t)(nt * nt + nt * (nt - 1) / 2) * sym_parts(nt, kSymF64) * kSymSlotBytes;
+    const size_t slots = (size_t)(nt * nt + nt * (nt - 1) / 2) * sym_parts(nt) * kSymSlotBytes;
     return std::max((size_t)1 << 20, std::min(slots, kMinPartial));
 }
 
@@ -225,17 +225,15 @@ void carve_common(Plan& P, const Layout& L, char* b) {
 }  // namespace
 
 // Tile pairs of small surfaces are cut so that a symmetric pass has about
-// SDBIE_SYM_PARTS_* blocks (8 per CU in float, 16 in double), room permitting: 16
-// parts of 16 steps up to 22 tiles in float and 31 in double, one part from 64 and
-// 91 tiles on.  The double blocks are the longer ones, so their last wave weighs
-// more: with 2048 and 4096 blocks the double passes of n = 17070 (67 tiles) take
-// 208 and 193 us (Laplace single layer), 242 and 229 (double layer), 327 and 316
-// (Stokes double layer), those of n = 4302 the same; the float ones gain nothing
-// and would pay for more slots.
-int sym_parts(int64_t nt, int k) {
+// SDBIE_SYM_PARTS blocks (16 per CU), room permitting: 16 parts of 16 steps up to
+// 31 tiles, one part from 91 tiles on.  With 2048 and 4096 blocks the double passes
+// of n = 17070 (67 tiles) take 208 and 193 us (Laplace single layer), 242 and 229
+// (double layer), 327 and 316 (Stokes double layer), the float ones 94 and 67, 113 and
+// 91, 183 and 172, the float slip sum 206 and 189; passes of n = 4302 the same.
+int sym_parts(int64_t nt) {
     const int64_t pairs = nt * (nt + 1) / 2;
     int parts = 1;
-    while (parts < kSymParts && pairs * parts < (k == kSymF32 ? SDBIE_SYM_PARTS_F32 : SDBIE_SYM_PARTS_F64)) parts *= 2;
+    while (parts < kSymParts && pairs * parts < SDBIE_SYM_PARTS) parts *= 2;
     return parts;
 }
 

@@ -77,11 +77,8 @@ constexpr int kSymParts = 16;
 #ifndef SDBIE_SYM_TARGET
 #define SDBIE_SYM_TARGET 16384
 #endif
-#ifndef SDBIE_SYM_PARTS_F64
-#define SDBIE_SYM_PARTS_F64 4096
-#endif
-#ifndef SDBIE_SYM_PARTS_F32
-#define SDBIE_SYM_PARTS_F32 2048
+#ifndef SDBIE_SYM_PARTS
+#define SDBIE_SYM_PARTS 4096
 #endif
 constexpr int kSymAll = 0xffff, kSymNear = 0x10000, kSymSelf = 0x03ff;
 constexpr size_t kSymSlotBytes = (size_t)3 * kTile * sizeof(double);
@@ -243,8 +240,8 @@ struct Plan {
 constexpr int kNumVec = 31;
 constexpr int kImageStride = 8;  // doubles per node of one image-basis slot: p, u, b_D, b_S
 
-// parts a tile pair of a symmetric pass (kSymF64, kSymF32) is cut into on a surface of nt tiles
-int sym_parts(int64_t nt, int k);
+// parts a tile pair of a symmetric pass is cut into on a surface of nt tiles
+int sym_parts(int64_t nt);
 size_t workspace_bytes(int64_t n, int max_restart);
 void carve_workspace(Plan& P, void* ws);
 // layer applies only (no solver vectors), at most nsplit_cap source splits and

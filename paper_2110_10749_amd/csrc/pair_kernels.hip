@@ -2245,7 +2245,7 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
     for (int c = 0; c < C; ++c) sa.fwd[((int64_t)slot * C + c) * kTile + tid] = acc[c];
 }
 
-// Far tile pairs of one part, two targets to a lane: a source read from LDS
+// Far tile pairs, two targets to a lane (an item's row rotations in pairs): a source read from LDS
 // serves two pairs, and their reverse terms travel home as one sum, so a pair
 // takes half the LDS reads and half the DPP moves and adds of sym_body's steps.
 // The pass is bound by its VALU instructions (and by the clock they leave).  Waves
@@ -2257,8 +2257,8 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
 // slip sum 2600 and 2520, Laplace double layer 1277 and 1140, single layer 948 and
 // 853; n = 272718 float Stokes double layer 28270 and 27430, Laplace single layer
 // 10700 and 9030.  Four targets to a lane lose again (Laplace double layer 1193:
-// registers), and so do sets of several parts (n = 9582 double slip sum 177 and 191):
-// they keep one.
+// registers), and so do the passes that form their records themselves (n = 9582
+// double slip sum 177 and 191): they keep one.
 constexpr int kSymTargets = 2;
 
 template <class Sym, typename T, int K, int E>
@@ -2312,7 +2312,7 @@ __device__ __forceinline__ void sym_multi_body(const KArgs& a, const SymArgs& sa
         for (int c = 0; c < C; ++c) acc[t][c] = 0.0;
     }
     for (int it = first; it < first + cnt; ++it) {
-        const int tb = sa.items[4 * it + 1], p = sa.items[4 * it + 2];
+        const int tb = sa.items[4 * it + 1], p = sa.items[4 * it + 2], steps = sa.items[4 * it + 3];
         if constexpr (sizeof(T) == 4) {  // the targets in the source tile's frame
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
@@ -2329,9 +2329,11 @@ __device__ __forceinline__ void sym_multi_body(const KArgs& a, const SymArgs& sa
         __syncthreads();
 #pragma unroll 1
         for (int ph = 0; ph < G; ++ph) {
-            const int q = wave ^ ph;
+            const int rots = (steps >> (4 * NT * ph)) & ((1 << (4 * NT)) - 1), q = wave ^ ph;
+            if (!rots) continue;  // uniform over the block
 #pragma unroll 1
             for (int rr = 0; rr < 4; ++rr) {
+                if (!((rots >> (NT * rr)) & 1)) continue;
                 const int jb = 64 * q + (((row + rr) & 3) << 4), j = jb + l16;
                 T facc[NT][C];
                 double rd[C];
@@ -2382,10 +2384,13 @@ void sym_pass_pairs(KArgs a, SymArgs sa) {
     __shared__ double sracc[Sym::C * kTile];
     if constexpr (PACK) {
         completion_partials(a);
-    } else if (sa.items[4 * sa.blocks[3 * blockIdx.x] + 3] == kSymAll) {
-        // far pairs of one part (near and far items share no block)
-        sym_multi_body<Sym, T>(a, sa, blockIdx.x, srec, sracc);
-        return;
+    } else {
+        const int steps = sa.items[4 * sa.blocks[3 * blockIdx.x] + 3];
+        if (!(steps & kSymNear) && (steps & (steps >> 1))) {
+            // far pairs of one or two parts (near and far items share no block)
+            sym_multi_body<Sym, T>(a, sa, blockIdx.x, srec, sracc);
+            return;
+        }
     }
     sym_body<Sym, T, true, PACK>(a, sa, blockIdx.x, srec, sracc);
 }
@@ -2518,9 +2523,13 @@ const SymSet& sym_set(const Plan& P, bool mixed) {
     return P.sym[mixed ? kSymF32 : P.far_only64 ? kSymFar64 : kSymF64];
 }
 
-// whether the blocks of a set's passes form the records (several parts to a tile
-// pair; the completion's partials then come from the pass's first blocks)
-bool sym_packs(const SymSet& S) { return S.parts > 1; }
+// whether the blocks of a set's passes form the records (the completion's partials
+// then come from the pass's first blocks): sets of several parts to a tile pair.
+// Float sets of two parts take a packing launch (5 us) and two targets to a lane
+// instead: 94 / 67 us a Laplace single layer, 205 / 189 a slip sum at n = 17070.  In
+// double the two are equal (Stokes single layer 305 / 285 and the launch, slip sum
+// 394 / 396 and the launch).
+bool sym_packs(const SymSet& S, bool mixed) { return S.parts > (mixed ? 2 : 1); }
 
 // pack and pair kernels of one pass, each timed on its own when kernel timing
 // is on (pairs: all N^2 for a pass kernel; with separate far and near
@@ -2542,7 +2551,7 @@ bool launch_pair_kernels(const Plan& P, const KArgs& a, hipStream_t st, int fami
         const int kind = mixed ? Sym::kFamilyBit : Sym::kFamilyBit << 2;  // SDBIE_SYM_* of this pass
         const SymSet& S = sym_set(P, mixed);
         sym = (P.symmetric & kind) && S.nblocks > 0 && !a.dl_tgt;
-        pack = !sym || !sym_packs(S) || cb > S.nblocks;
+        pack = !sym || !sym_packs(S, mixed) || cb > S.nblocks;
     }
     if (pack) {
         const int64_t pb = a.npad / 256 > cb ? a.npad / 256 : cb;
@@ -2639,7 +2648,7 @@ void launch_epilogue(const Plan& P, const PassDesc& d, int S, bool sym, hipStrea
         const SymSet& Y = sym_set(P, d.mixed);
         const int nsplit = !d.mixed && P.far_only64 ? S : 0;
         // without a packing launch a density in the caller's order has not been gathered
-        const bool raw = sym_packs(Y) && d.gather_src && d.base == d.gather_dst;
+        const bool raw = sym_packs(Y, d.mixed) && d.gather_src && d.base == d.gather_dst;
         const double* base = raw ? d.gather_src : d.base;
         const int32_t* bperm = raw ? (const int32_t*)P.perm : nullptr;
         if (d.mixed)

@@ -659,7 +659,7 @@ void build_symmetric_lists(Plan& P, int32_t* out, hipStream_t st) {
     for (int k = 0; k < 2; ++k) {
         SymSet& S = P.sym[k];
         const int64_t items = k == kSymF32 ? (int64_t)T * T : pairs + T;  // at most, of one part
-        S.parts = sym_parts(T, k);
+        S.parts = sym_parts(T);
         while (S.parts > 1 && (items + pairs) * S.parts * kSymSlotBytes > P.partial_bytes) S.parts /= 2;
         A.parts[k] = S.parts;
         const int width = 16 / S.parts;
