@@ -167,6 +167,9 @@ size_t sdbie_workspace_bytes(int64_t n, int max_restart);
  * weights), ERR_DEVICE. */
 int sdbie_plan_create(sdbie_plan* plan, const sdbie_surface* s, int max_restart,
                       void* ws, size_t ws_bytes, void* stream);
+/* Host work only: no device call, no synchronisation (also while a stream is
+ * captured).  Work that still reads the plan's workspace must have ended
+ * before that memory is reused. */
 int sdbie_plan_destroy(sdbie_plan plan);
 int64_t sdbie_plan_n(sdbie_plan plan);
 
@@ -219,6 +222,12 @@ int stokes_layer_apply(sdbie_plan plan, double mu, sdbie_layer layer, const doub
 #define SDBIE_NOALLOC_MAX_NODES 32768
 int stokes_layer_apply_noalloc(const sdbie_surface* s, double mu, sdbie_layer layer, const double* dens,
                                double* out, sdbie_precision prec, void* stream);
+
+/* Solves (darcy_solve, stokes_solve, ddm_solve, ddm_adjoint, ddm_dn_spectrum)
+ * synchronise `stream`.  Each uses 6 KB of pinned host memory while it runs,
+ * from a list of at most 16 blocks that the process keeps (a block is
+ * allocated when more solves run at once than ever before, and freed when
+ * more than 16 end together). */
 
 /* Darcy problem, eq. (Darcy_final): given v = u.n on the nodes (device [n]),
  * solve (1/2 - H) p = b_D with b_D = -L dp/dn, dp/dn = -(mu/K) v, as

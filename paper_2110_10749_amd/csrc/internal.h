@@ -94,7 +94,7 @@ constexpr int kRedBlocks = 512;  // blocks of the deterministic reductions
 // that the redundant reductions of every block would take longer than the
 // launches they save
 constexpr int kFuseCols = 64;
-// host memory of a plan's solves (doubles): what the fused kernels write for the host
+// host memory of a solve (doubles): what the fused kernels write for the host
 enum : int {
     kHostE = 0, kHostH1 = kFuseCols, kHostH2 = 2 * kFuseCols, kHostNorm = 3 * kFuseCols,
     kHostDot = 3 * kFuseCols + 8, kHostDoubles = kHostDot + kRedBlocks,
@@ -213,7 +213,7 @@ struct Plan {
     double* image_out = nullptr;  // local solutions (p, u) and right-hand sides (b_D, b_S) of each outer
                                   // basis vector [(max_restart+1)][8n]
     double* basis_rc = nullptr;   // recycled inner basis (deflation space) [(max_restart+1)][3n]
-    double* host_pinned = nullptr;  // [kHostDoubles] host memory the kernels write to (first solve on)
+    double* host_pinned = nullptr;  // [kHostDoubles] host memory the kernels write to (during a solve, see Ctx)
     // (target, source) pairs of real nodes in the near tile pairs (double, float masks)
     double near_pairs64 = 0.0, near_pairs32 = 0.0;
     // target-source symmetric passes (for the pass kinds whose SDBIE_SYM_* bit is
@@ -228,12 +228,6 @@ struct Plan {
     // bookkeeping for info
     int64_t applies_fp64 = 0, applies_mixed = 0;
     double pairs = 0.0;
-    Plan() = default;
-    Plan(const Plan&) = delete;
-    Plan& operator=(const Plan&) = delete;
-    ~Plan() {
-        if (host_pinned) (void)hipHostFree(host_pinned);
-    }
     double* vec(int k) const { return vecs + (size_t)k * 3 * n; }
 };
 

@@ -123,7 +123,7 @@ struct Ctx {
     Recycle* rc_cur = nullptr;
 
     Ctx(Plan& plan, hipStream_t st, const sdbie_opts& opts);
-    ~Ctx() { P.far_only64 = false; }
+    ~Ctx();
     Ctx(const Ctx&) = delete;
     Ctx& operator=(const Ctx&) = delete;
     // FP64 coupled solves and adjoints: the pair sums keep their order (see SymSet)

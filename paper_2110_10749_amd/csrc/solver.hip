@@ -14,6 +14,8 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
+#include <mutex>
 #include <vector>
 
 #include "solver.h"
@@ -1113,6 +1115,55 @@ void Ctx::compute_drag(const sdbie_params& prm, const double* p, const double* u
     for (int c = 0; c < 3; ++c) drag[c] = h[c];
 }
 
+// Pinned host memory of the solves.  A block belongs to one solve and goes back
+// to a list of at most kKeptHostBlocks (6 KB each) that every plan, thread and
+// device shares: freeing pinned memory waits for the whole device and is not
+// allowed while a stream is captured, so no plan owns any, and a block is freed
+// only when more solves than that end together.  The list lives as long as the
+// process.
+constexpr int kKeptHostBlocks = 16;
+struct HostBlocks {
+    std::mutex mutex;
+    double* block[kKeptHostBlocks];
+    int count = 0;
+};
+static HostBlocks& host_blocks() {
+    static HostBlocks* b = new HostBlocks;  // never destroyed: a solve may run while the process ends
+    return *b;
+}
+
+// allocation and release, also while another stream is captured
+struct AnyCaptureMode {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    AnyCaptureMode() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~AnyCaptureMode() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+static double* take_host_block() {
+    HostBlocks& b = host_blocks();
+    {
+        std::lock_guard<std::mutex> lock(b.mutex);
+        if (b.count > 0) return b.block[--b.count];
+    }
+    double* p = nullptr;
+    AnyCaptureMode any;
+    SDBIE_HIP(hipHostMalloc(reinterpret_cast<void**>(&p), kHostDoubles * sizeof(double), hipHostMallocPortable));
+    return p;
+}
+
+static void give_host_block(double* p) {
+    HostBlocks& b = host_blocks();
+    {
+        std::lock_guard<std::mutex> lock(b.mutex);
+        if (b.count < kKeptHostBlocks) {
+            b.block[b.count++] = p;
+            return;
+        }
+    }
+    AnyCaptureMode any;
+    (void)hipHostFree(p);
+}
+
 Ctx::Ctx(Plan& plan, hipStream_t st, const sdbie_opts& opts) : P(plan), s(st), o(opts) {
     std::memset(&info, 0, sizeof(info));
     rc_stokes.V = P.basis_rc;
@@ -1129,9 +1180,15 @@ Ctx::Ctx(Plan& plan, hipStream_t st, const sdbie_opts& opts) : P(plan), s(st), o
     outer.dy = P.scal + kScalGmres + 3 * (m + 2) + 2 * (m + 1) + 1;
     P.applies_fp64 = P.applies_mixed = 0;
     P.pairs = 0.0;
-    if (!P.host_pinned)
-        SDBIE_HIP(hipHostMalloc(reinterpret_cast<void**>(&P.host_pinned), kHostDoubles * sizeof(double),
-                                hipHostMallocDefault));
+    P.host_pinned = take_host_block();  // last: nothing after it may throw
+}
+
+Ctx::~Ctx() {
+    // an error may leave kernels in flight that write to the block
+    if (std::uncaught_exceptions() > 0) (void)hipStreamSynchronize(s);
+    give_host_block(P.host_pinned);
+    P.host_pinned = nullptr;
+    P.far_only64 = false;
 }
 
 void Ctx::finish() {
