@@ -130,13 +130,23 @@ def erfcx_fit(lo, hi, p, deg, ctype):
     return coef, worst
 
 
+def horner_double(coef, x):
+    """Horner's rule in double on an array, with the coefficients as the kernels hold them."""
+    import numpy as np
+    a = np.full_like(x, float(coef[-1]))
+    for v in reversed(coef[:-1]):
+        a = a * x + float(v)
+    return a
+
+
 def erfcx_weighted_fit(lo, hi, p, deg):
     """Coefficients (low to high) of g(t), t = 1/(1 + p rho), with exp(-rho^2) g
     ~ erfc(rho) on [lo, hi]: least squares of that absolute error at Chebyshev
     points of the t interval in 60-digit arithmetic.  erf = 1 - exp(-rho^2) g
     only sees the error times exp(-rho^2), so three degrees less than the fit of
     g itself keep erf at the rounding of double.  Returns (coefficients, max
-    absolute error of exp(-rho^2) g)."""
+    absolute error of exp(-rho^2) g as fitted, and by Horner's rule in double)."""
+    import numpy as np
     with mp.workdps(60):
         tlo, thi = 1 / (1 + p * mp.mpf(hi)), 1 / (1 + p * mp.mpf(lo))
         tm, th = (tlo + thi) / 2, (thi - tlo) / 2
@@ -158,22 +168,30 @@ def erfcx_weighted_fit(lo, hi, p, deg):
                 N[j, i] = N[i, j]
         c = mp.lu_solve(N, r)
         coef = [c[j] for j in range(deg + 1)]
-        worst = max(abs(w * sum(coef[j] * t ** j for j in range(deg + 1)) - f) for t, w, f in rows)
-    return coef, float(worst)
+        fit = max(abs(w * sum(coef[j] * t ** j for j in range(deg + 1)) - f) for t, w, f in rows)
+        rho = np.linspace(lo, hi, 3001)
+        g = horner_double(coef, 1.0 / (1.0 + p * rho))
+        worst = max(abs(mp.exp(-mp.mpf(float(r)) ** 2) * mp.mpf(float(a)) - mp.erfc(mp.mpf(float(r))))
+                    for r, a in zip(rho, g))
+    return coef, float(fit), float(worst)
 
 
 def exp_fit(deg):
     """Coefficients of a polynomial ~ e^y on |y| <= ln(2)/2 (interpolation at
-    the Chebyshev points), and its max relative error on a grid."""
+    the Chebyshev points), and its max relative error on a grid: as fitted, and
+    by Horner's rule in double."""
+    import numpy as np
     with mp.workdps(60):
         h = mp.log(2) / 2
         nodes = [h * mp.cos(mp.pi * (k + mp.mpf(1) / 2) / (deg + 1)) for k in range(deg + 1)]
         A = mp.matrix([[y ** j for j in range(deg + 1)] for y in nodes])
         c = mp.lu_solve(A, mp.matrix([mp.exp(y) for y in nodes]))
         coef = [c[j] for j in range(deg + 1)]
-        worst = max(abs(sum(coef[j] * y ** j for j in range(deg + 1)) / mp.exp(y) - 1)
-                    for y in [h * (mp.mpf(k) / 200 - 1) for k in range(401)])
-    return coef, float(worst)
+        fit = max(abs(sum(coef[j] * y ** j for j in range(deg + 1)) / mp.exp(y) - 1)
+                  for y in [h * (mp.mpf(k) / 200 - 1) for k in range(401)])
+        ys = np.linspace(-float(h), float(h), 3001)
+        worst = max(abs(mp.mpf(float(a)) / mp.exp(mp.mpf(float(y))) - 1) for y, a in zip(ys, horner_double(coef, ys)))
+    return coef, float(fit), float(worst)
 
 
 def emit_plain(name, vals, ctype, suffix):
@@ -211,9 +229,12 @@ def main():
     g32, e32 = erfcx_fit(rho_s32 - 0.01, sto32 + 0.1, p_fit, 8, "float")
     assert e64 < 1.5e-15 and e32 < 4e-7, (e64, e32)
     p_w = 0.4
-    gw, ew = erfcx_weighted_fit(rho_s64 - 0.01, sto + 0.1, p_w, 13)
-    ex, ee = exp_fit(11)
-    assert ew < 5e-18 and ee < 5e-18, (ew, ee)
+    gw, fw, ew = erfcx_weighted_fit(rho_s64 - 0.01, sto + 0.1, p_w, 13)
+    ex, fe, ee = exp_fit(11)
+    # the fits add nothing to the rounding of their evaluation: some 2^-53 of erfc (0.49) = 0.49
+    # and of the sum's partial values, and one or two of e^y
+    assert fw < 5e-18 and fe < 5e-18, (fw, fe)
+    assert ew < 4e-16 and ee < 4e-16, (ew, ee)
     # the adjoint's derivative factors also need s2 and s4 -> 1
     out.append(f"#define SDBIE_RHO_CUT_LAPLACE_F64 {lap}")
     out.append(f"#define SDBIE_RHO_CUT_STOKES_F64 {sto}")
@@ -230,11 +251,11 @@ def main():
     out.append(f"#define SDBIE_ERFCX_P {p_fit}")
     out.append(emit_plain("kERFCX_F64", g64, "double", ""))
     out.append(emit_plain("kERFCX_F32", g32, "float", "f"))
-    out.append(f"// exp(-rho^2) sum_j kERFCXW_F64[j] t^j is erfc(rho) to {ew:.0e} (absolute), t = 1/(1 +")
-    out.append("// SDBIE_ERFCXW_P rho), same range")
+    out.append(f"// exp(-rho^2) sum_j kERFCXW_F64[j] t^j is erfc(rho) to {ew:.1e} (absolute; Horner in double, the")
+    out.append(f"// coefficients before rounding {fw:.0e}), t = 1/(1 + SDBIE_ERFCXW_P rho), same range")
     out.append(f"#define SDBIE_ERFCXW_P {p_w}")
     out.append(emit_plain("kERFCXW_F64", gw, "double", ""))
-    out.append(f"// e^y on |y| <= ln(2)/2 to {ee:.0e} (relative)")
+    out.append(f"// e^y on |y| <= ln(2)/2 to {ee:.1e} (relative; Horner in double, before rounding {fe:.0e})")
     out.append(emit_plain("kEXP_F64", ex, "double", ""))
     for k in (2, 4):
         g = G_series(k)
