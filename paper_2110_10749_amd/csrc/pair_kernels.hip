@@ -234,9 +234,15 @@ __device__ __forceinline__ void horner_2n(const double (&ta)[MA], const double (
 
 // The same factors with fewer operations, for the symmetric passes: erfc from a
 // fit of 14 terms that is exact where exp(-rho^2) lets it show, e^y of 12 terms,
-// constants folded into the polynomials (43 double operations instead of 54 for
-// the stresslet factor; the error of each s_k against 60 digits is no larger:
-// largest 2.0e-15 against 3.0e-15 relative, near rho = 0.5, where s_4 = 0.1).
+// 1/3 and 1/9 folded into 2/sqrt(pi) (44 double operations instead of 54 for the
+// stresslet factor).  No s_k loses accuracy: against 60 digits its root mean square
+// error is 0.83 to 1.02 times near_factors' in every part of 0.5 <= rho <= 7.1, its
+// largest 2.6e-16, 1.8e-15, 5.2e-16, 2.9e-15 (relative, near rho = 0.5; near_factors
+// 3.6e-16, 2.1e-15, 4.7e-16, 2.4e-15).  Two things keep that.  The polynomials hold
+// whole numbers: with 2/3, 14/3 .. the error of s_3 was up to 2.2 and of s_4 1.8 times
+// as large near their zeros (rho = 1.8 .. 2.5).  And s_3 and s_4 take the low word of
+// ln 2, one fma, or s_4 loses 1.2 times from rho = 1.8 on.  Neither shows in a pass:
+// n = 42342 Stokes double layer 1467 and 1468 us, single layer 1314 and 1312.
 template <int N, bool K1, bool K2, bool K3, bool K4>
 __device__ __forceinline__ void near_factors_sym(const double (&r2)[N], const double (&inv_r)[N], double id, double id2,
                                                  double rc2, double (&k1)[N], double (&k2)[N], double (&k3)[N],
@@ -253,13 +259,15 @@ __device__ __forceinline__ void near_factors_sym(const double (&r2)[N], const do
     }
     if (!__any(any_in)) return;
     {
-        constexpr double kLog2e = 1.44269504088896340736, kLn2 = 0.693147180559945309417;
+        constexpr double kLog2e = 1.44269504088896340736;
+        constexpr double kLn2 = 0.693147180559945309417, kLn2Lo = 2.319046813846299558e-17;
         double n[N], y[N], E[N], t[N], g[N], rho[N];
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             rho[u] = r2[u] * inv_r[u] * id;
             n[u] = rint(x[u] * kLog2e);
-            y[u] = fma(n[u], kLn2, -x[u]);  // n (ln 2 - kLn2) < 2e-15: too small for erf where exp(-x) is that small
+            y[u] = fma(n[u], kLn2, -x[u]);
+            if (K3 || K4) y[u] = fma(n[u], kLn2Lo, y[u]);  // s_1 and s_2: nothing to gain
             const double v = fma(SDBIE_ERFCXW_P, rho[u], 1.0);
             const double h = __builtin_amdgcn_rcp(v), e = fma(-v, h, 1.0);
             t[u] = fma(h, fma(e, e, e), h);  // h (1 + e + e^2)
@@ -268,14 +276,14 @@ __device__ __forceinline__ void near_factors_sym(const double (&r2)[N], const do
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             const double e = ldexp(E[u], -(int)n[u]);
-            const double ef = fma(-e, g[u], 1.0), cE = kTwoOverSqrtPi * rho[u] * e;
+            const double ef = fma(-e, g[u], 1.0);
+            const double c3E = kTwoOverSqrtPi / 3.0 * rho[u] * e, c9E = kTwoOverSqrtPi / 9.0 * rho[u] * e;
             const bool c = in[u];
             // s_k times the plain factor
-            if (K1) k1[u] *= c ? fma(-cE, fma(x[u], 2.0 / 3.0, -5.0 / 3.0), ef) : 1.0;
-            if (K2) k2[u] *= c ? fma(cE, fma(x[u], 2.0 / 3.0, -1.0), ef) : 1.0;
-            if (K3) k3[u] *= c ? fma(-cE, fma(fma(x[u], 4.0 / 3.0, -14.0 / 3.0), x[u], 1.0), ef) : 1.0;
-            if (K4)
-                k4[u] *= c ? fma(-cE, fma(fma(fma(x[u], 8.0 / 9.0, -4.0), x[u], 2.0 / 3.0), x[u], 1.0), ef) : 1.0;
+            if (K1) k1[u] *= c ? fma(-c3E, fma(x[u], 2.0, -5.0), ef) : 1.0;
+            if (K2) k2[u] *= c ? fma(c3E, fma(x[u], 2.0, -3.0), ef) : 1.0;
+            if (K3) k3[u] *= c ? fma(-c3E, fma(fma(x[u], 4.0, -14.0), x[u], 3.0), ef) : 1.0;
+            if (K4) k4[u] *= c ? fma(-c9E, fma(fma(fma(x[u], 8.0, -36.0), x[u], 6.0), x[u], 9.0), ef) : 1.0;
         }
     }
     if (!__any(any_ser)) return;
