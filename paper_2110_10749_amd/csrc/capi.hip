@@ -36,7 +36,6 @@ struct Layout {
 // per block.  The lists and partial slots grow as T^2 (about 3495 bytes per
 // tile pair), so plans of more than kSymMaxTiles tiles hold none and run every
 // pass one direction at a time.
-constexpr int64_t kSymMaxTiles = 2048;  // 524288 nodes: 14.7 GB of lists and slots
 bool sym_fits(int64_t nt) { return nt <= kSymMaxTiles; }
 int64_t sym_max_pairs(int64_t nt) { return nt * (nt - 1) / 2; }
 int64_t sym_max_items(int64_t nt, int k) {

@@ -74,6 +74,14 @@ constexpr int kMaxRestart = 1000; // largest GMRES restart length of a plan
 // rotations of a tile against itself
 constexpr int kSymChunk = 8;
 constexpr int kSymParts = 16;
+// tiles up to which a plan holds the work lists: 524288 nodes, 14.7 GB of lists and
+// slots.  Staging sizes its arrays by it and ranks far pairs in the records' memory.
+#ifndef SDBIE_SYM_MAX_TILES
+#define SDBIE_SYM_MAX_TILES 2048
+#endif
+constexpr int kSymMaxTiles = SDBIE_SYM_MAX_TILES;
+static_assert(kSymMaxTiles % 256 == 0, "whole groups of 64 tiles, and rows per thread of a 256-thread block");
+static_assert((int64_t)kSymMaxTiles * sizeof(int32_t) <= (int64_t)kTile * kRecBytes, "T^2 ranks fit T tiles' records");
 #ifndef SDBIE_SYM_TARGET
 #define SDBIE_SYM_TARGET 16384
 #endif

@@ -371,7 +371,7 @@ __global__ __launch_bounds__(256) void k_mask_rows(int T, int64_t n, const doubl
     }
     if (a >= T) return;
     // wave v takes the 64-tile groups g = v, v + 4, ..; the counts stay in its scalars
-    __shared__ int cnt5[4][5], before[2048 / 64 + 1];
+    __shared__ int cnt5[4][5], before[kSymMaxTiles / 64 + 1];
     const double* A = boxes + (int64_t)a * 6;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, groups = (T + 63) / 64;
     int c[5] = {0, 0, 0, 0, 0};
@@ -460,7 +460,7 @@ struct ListArgs {
     double* area;
 };
 
-constexpr int kScanRows = 8;  // rows per thread of the scan (2048 tiles)
+constexpr int kScanRows = kSymMaxTiles / 256;  // rows per thread of the scan
 
 // exclusive prefix sums over the rows of v[0..kScanRows) (thread-consecutive), total over all
 __device__ __forceinline__ int block_scan(int (&v)[kScanRows], int* sh) {
@@ -644,7 +644,6 @@ __global__ __launch_bounds__(256) void k_list_fill(ListArgs A) {
 // own region, and the forward ones take the larger of the buffer and sym_fwd.
 void build_symmetric_lists(Plan& P, int32_t* out, hipStream_t st) {
     const int T = P.ntiles;
-    if (T > 256 * kScanRows) throw Error(SDBIE_ERR_ARG, "internal: symmetric lists of too many tiles");
     const int64_t pairs = (int64_t)T * (T - 1) / 2;
     ListArgs A;
     A.T = T;
@@ -729,6 +728,7 @@ void stage_surface(Plan& P, const sdbie_surface* s, hipStream_t st) {
     const double rc64 = SDBIE_RHO_CUT_STOKES_F64 * P.delta * (1.0 + 1e-6);
     const double rc32 = SDBIE_RHO_CUT_STOKES_F32 * P.delta * (1.0 + 1e-6);
     const bool lists = P.sym[0].items != nullptr;
+    if (lists && P.ntiles > kSymMaxTiles) throw Error(SDBIE_ERR_ARG, "internal: symmetric lists of too many tiles");
     hipLaunchKernelGGL(k_mask_rows, dim3((unsigned)(P.ntiles > kRedBlocks ? P.ntiles : kRedBlocks)), dim3(256), 0, st,
                        P.ntiles, n, (const double*)P.boxes, rc64, rc32, P.mask64, P.mask32,
                        reinterpret_cast<unsigned long long*>(stage + 10), lists ? P.sym_rows : nullptr,
