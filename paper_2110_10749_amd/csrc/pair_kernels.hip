@@ -232,6 +232,34 @@ __device__ __forceinline__ void horner_2n(const double (&ta)[MA], const double (
     }
 }
 
+// the series values of N pairs, where ser
+template <int N, bool K1, bool K2, bool K3, bool K4>
+__device__ __forceinline__ void series_n(const double (&x)[N], const bool (&ser)[N], double id, double id2,
+                                         double (&k1)[N], double (&k2)[N], double (&k3)[N], double (&k4)[N]) {
+    const double id3 = id * id2;
+    double f[N];
+    if (K1) {
+        horner_n<N>(kF1_F64, x, f);
+#pragma unroll
+        for (int u = 0; u < N; ++u) k1[u] = ser[u] ? f[u] * id : k1[u];
+    }
+    if (K2) {
+        horner_n<N>(kF2_F64, x, f);
+#pragma unroll
+        for (int u = 0; u < N; ++u) k2[u] = ser[u] ? f[u] * id3 : k2[u];
+    }
+    if (K3) {
+        horner_n<N>(kF3_F64, x, f);
+#pragma unroll
+        for (int u = 0; u < N; ++u) k3[u] = ser[u] ? f[u] * id3 : k3[u];
+    }
+    if (K4) {
+        horner_n<N>(kF4_F64, x, f);
+#pragma unroll
+        for (int u = 0; u < N; ++u) k4[u] = ser[u] ? f[u] * id3 * id2 : k4[u];
+    }
+}
+
 // The same factors with fewer operations, for the symmetric passes: erfc from a
 // fit of 14 terms that is exact where exp(-rho^2) lets it show, e^y of 12 terms,
 // 1/3 and 1/9 folded into 2/sqrt(pi) (44 double operations instead of 54 for the
@@ -286,29 +314,7 @@ __device__ __forceinline__ void near_factors_sym(const double (&r2)[N], const do
             if (K4) k4[u] *= c ? fma(-c9E, fma(fma(fma(x[u], 8.0, -36.0), x[u], 6.0), x[u], 9.0), ef) : 1.0;
         }
     }
-    if (!__any(any_ser)) return;
-    const double id3 = id * id2;
-    double f[N];
-    if (K1) {
-        horner_n<N>(kF1_F64, x, f);
-#pragma unroll
-        for (int u = 0; u < N; ++u) k1[u] = ser[u] ? f[u] * id : k1[u];
-    }
-    if (K2) {
-        horner_n<N>(kF2_F64, x, f);
-#pragma unroll
-        for (int u = 0; u < N; ++u) k2[u] = ser[u] ? f[u] * id3 : k2[u];
-    }
-    if (K3) {
-        horner_n<N>(kF3_F64, x, f);
-#pragma unroll
-        for (int u = 0; u < N; ++u) k3[u] = ser[u] ? f[u] * id3 : k3[u];
-    }
-    if (K4) {
-        horner_n<N>(kF4_F64, x, f);
-#pragma unroll
-        for (int u = 0; u < N; ++u) k4[u] = ser[u] ? f[u] * id3 * id2 : k4[u];
-    }
+    if (__any(any_ser)) series_n<N, K1, K2, K3, K4>(x, ser, id, id2, k1, k2, k3, k4);
 }
 
 template <int N, bool K1, bool K2, bool K3, bool K4>
@@ -358,29 +364,7 @@ __device__ __forceinline__ void near_factors_n(const double (&r2)[N], const doub
                           : k4[u];
         }
     }
-    if (!__any(any_ser)) return;
-    const double id3 = id * id2;
-    double f[N];
-    if (K1) {
-        horner_n<N>(kF1_F64, x, f);
-#pragma unroll
-        for (int u = 0; u < N; ++u) k1[u] = ser[u] ? f[u] * id : k1[u];
-    }
-    if (K2) {
-        horner_n<N>(kF2_F64, x, f);
-#pragma unroll
-        for (int u = 0; u < N; ++u) k2[u] = ser[u] ? f[u] * id3 : k2[u];
-    }
-    if (K3) {
-        horner_n<N>(kF3_F64, x, f);
-#pragma unroll
-        for (int u = 0; u < N; ++u) k3[u] = ser[u] ? f[u] * id3 : k3[u];
-    }
-    if (K4) {
-        horner_n<N>(kF4_F64, x, f);
-#pragma unroll
-        for (int u = 0; u < N; ++u) k4[u] = ser[u] ? f[u] * id3 * id2 : k4[u];
-    }
+    if (__any(any_ser)) series_n<N, K1, K2, K3, K4>(x, ser, id, id2, k1, k2, k3, k4);
 }
 
 struct KArgs {
@@ -1823,9 +1807,9 @@ struct SymLaplace {
         }
         rv[0] = r;
     }
-    // The same for a near pair with factors k1 .. k4: f for the target and, with
-    // REV, rv for the source (field F at s(F)).
-    template <bool REV, class Field>
+    // The same for a near pair with factors k1 .. k4: f for the target and rv for
+    // the source (field F at s(F)).
+    template <class Field>
     __device__ __forceinline__ static void near(const T (&tr)[R], const Field& s, T dx, T dy, T dz, T k1, T k2, T, T,
                                                 T (&f)[C], T (&rv)[C]) {
         f[0] = rv[0] = T(0);
@@ -1953,7 +1937,7 @@ struct SymStokes {
         for (int c = 0; c < 3; ++c) rv[c] = ADD ? fma(y[c], f, rv[c]) : y[c] * f;
     }
     // a near pair (see SymLaplace::near)
-    template <bool REV, class Field>
+    template <class Field>
     __device__ __forceinline__ static void near(const T (&tr)[R], const Field& s, T dx, T dy, T dz, T k1, T, T k3, T k4,
                                                 T (&f)[C], T (&rv)[C]) {
         T cf = T(0), cr = T(0);
@@ -2176,9 +2160,9 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
                 for (int u = 0; u < G; ++u) {
                     const int j = jb + ((src.l16 - k - u) & 15);
                     T f[C], rv[C];
-                    Sym::template near<kNearBoth>(
-                        tr, [&](int fld) { return srec[fld * kTile + j]; }, dx[u], dy[u], dz[u], k1[u], k2[u], k3[u],
-                        k4[u], f, rv);
+                    Sym::near(
+                        tr, [&](int fld) { return srec[fld * kTile + j]; }, dx[u], dy[u], dz[u], k1[u], k2[u],
+                        k3[u], k4[u], f, rv);
 #pragma unroll
                     for (int c = 0; c < C; ++c) facc[c] += f[c];
                     if (kNearBoth && reverse) {
