@@ -148,14 +148,14 @@ void sdbie_default_opts(sdbie_opts* o);
 /* Bytes of device workspace a plan for n nodes (1 <= n <= 2^23) and GMRES
  * restart length up to max_restart (1..1000) needs (0 if the arguments are
  * invalid).  Roughly (120 max_restart + 1185 + 96 S) n bytes plus
- * (n/256)^2 * 3471, with S the source splits of a pair pass (a multiple of 8
- * up to 64: 64 at n = 4096, 16 at n = 68166, 8 from n = 131072 on); the
- * quadratic term is the tile masks and the work lists and partial sums of the
- * symmetric passes (sdbie_plan_set_symmetric): 0.84 GB at n = 68166,
- * 9.4 GB at n = 351866 with max_restart = 50.  Small plans hold up to 12 MiB
- * more, the partial sums of tile pairs cut into parts.  Above n = 524288 a plan holds
- * no symmetric lists (the quadratic term drops to the masks, (n/256)^2 * 2)
- * and runs every pass one direction at a time. */
+ * (n/256)^2 * 3497 (to 1% from n = 20000 on), with S the source splits of a
+ * pair pass (a multiple of 8 up to 64: 64 at n = 4096, 16 at n = 68166, 8 from
+ * n = 131072 on); the quadratic term is the tile masks and the work lists and
+ * partial sums of the symmetric passes (sdbie_plan_set_symmetric): 0.84 GB at
+ * n = 68166, 9.4 GB at n = 351866 with max_restart = 50.  Small plans hold up
+ * to 12 MiB more, the partial sums of tile pairs cut into parts.  Above
+ * n = 524288 a plan holds no symmetric lists (the quadratic term drops to the
+ * masks, (n/256)^2 * 2) and runs every pass one direction at a time. */
 size_t sdbie_workspace_bytes(int64_t n, int max_restart);
 
 /* Stage a surface: spatial (Morton) ordering, double and float copies of the
@@ -185,8 +185,8 @@ int64_t sdbie_plan_n(sdbie_plan plan);
  * The double sums of FP64 coupled solves and adjoints evaluate only
  * the tile pairs whose node pairs all lie beyond the smoothing cutoff that
  * way: their inexact interface products make the result, within tol_ddm,
- * depend on the order of every sum, and that order is kept.  Same sums up to rounding.  0: every ordered pair in its own
- * pass.  Plans of more than 524288 nodes have no room for the symmetric lists
+ * depend on the order of every sum, and that order is kept.  Same sums up to
+ * rounding.  0: every ordered pair in its own pass.  Plans of more than 524288 nodes have no room for the symmetric lists
  * and keep every pass one-directional whatever the mask.  The default,
  * SDBIE_SYM_DEFAULT, selects every kind: each is faster symmetric on gfx950.
  * ERR_ARG for a null plan or unknown bits. */

@@ -228,8 +228,10 @@ class Plan:
         return self._h
 
     def set_symmetric(self, kinds=SYM_ALL) -> None:
-        """Evaluate the far tile pairs of the selected pass kinds once for both
-        directions (sdbie_plan_set_symmetric).  ``kinds``: a mask of
+        """Evaluate each pair of nodes once for both directions in the selected
+        pass kinds (sdbie_plan_set_symmetric; close pairs of some float double
+        layers, and of the double sums of FP64 coupled solves, stay one evaluation
+        per direction).  ``kinds``: a mask of
         SYM_LAPLACE, SYM_STOKES (float pairs), SYM_LAPLACE_F64, SYM_STOKES_F64
         (double pairs); True means all, False none.  A new plan starts at
         SYM_DEFAULT."""

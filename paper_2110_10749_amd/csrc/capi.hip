@@ -33,8 +33,8 @@ struct Layout {
 // bounds of the lists of the symmetric passes: T (T + 1) / 2 tile pairs in
 // double (a tile against itself counts as one) and up to T^2 in float (near
 // pairs in both orders), each in up to sym_parts(T) items, and a forward slot
-// per block.  The lists and partial slots grow as T^2 (about 3495 bytes per
-// tile pair), so plans of more than kSymMaxTiles tiles hold none and run every
+// per block.  The lists and partial slots grow as T^2 (about 3495 bytes of T^2,
+// and two of masks), so plans of more than kSymMaxTiles tiles hold none and run every
 // pass one direction at a time.
 bool sym_fits(int64_t nt) { return nt <= kSymMaxTiles; }
 int64_t sym_max_pairs(int64_t nt) { return nt * (nt - 1) / 2; }
@@ -224,11 +224,16 @@ void carve_common(Plan& P, const Layout& L, char* b) {
 }  // namespace
 
 // Tile pairs of small surfaces are cut so that a symmetric pass has about
-// SDBIE_SYM_PARTS blocks (16 per CU), room permitting: 16 parts of 16 steps up to
-// 31 tiles, one part from 91 tiles on.  With 2048 and 4096 blocks the double passes
-// of n = 17070 (67 tiles) take 208 and 193 us (Laplace single layer), 242 and 229
-// (double layer), 327 and 316 (Stokes double layer), the float ones 94 and 67, 113 and
-// 91, 183 and 172, the float slip sum 206 and 189; passes of n = 4302 the same.
+// SDBIE_SYM_PARTS blocks (16 per CU): this asks for 16 parts of 16 steps up to 31
+// tiles and for one from 91 on.  A plan gets fewer where the worst case of slots
+// (three components; in float every pair near, in both orders) does not fit the
+// partial buffer (build_symmetric_lists): in double 16 parts up to 11 tiles and at 16,
+// 8 at 12 to 15 and 17 to 32, 4 up to 63, 2 up to 90; in float 16 up to 9, 8 at 10 to
+// 13 and 16 to 21, 4 at 14, 15 and 22 to 43, 2 up to 75, one from 76 on (the buffer
+// doubles at 4096 nodes, 16 tiles, with the source splits).  With 2048 and 4096 blocks the
+// double passes of n = 17070 (67 tiles) take 208 and 193 us (Laplace single layer), 242
+// and 229 (double layer), 327 and 316 (Stokes double layer), the float ones 94 and 67,
+// 113 and 91, 183 and 172, the float slip sum 206 and 189; passes of n = 4302 the same.
 int sym_parts(int64_t nt) {
     const int64_t pairs = nt * (nt + 1) / 2;
     int parts = 1;

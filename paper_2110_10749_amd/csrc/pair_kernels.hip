@@ -2095,7 +2095,10 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
         const int tb = sa.items[4 * it + 1], p = sa.items[4 * it + 2];
         const bool self = tb == ta;
         const int steps = sa.items[4 * it + 3] & (kNearBoth && self ? kSymSelf | kSymNear : ~0);
-        if (kNearBoth && tb < ta) continue;  // float sets: the item of the other order
+        // float sets: the item of the other order (its block still loads the targets and
+        // writes a slot of zeros: 190 of the 400 blocks at n = 1062, half of the near items
+        // at any size)
+        if (kNearBoth && tb < ta) continue;
         if constexpr (sizeof(T) == 4) {  // the targets in the source tile's frame
 #pragma unroll
             for (int c = 0; c < 3; ++c) tr[c] = x0[c] + (float)(tile_centre(a, ta, c) - tile_centre(a, tb, c));
@@ -2240,7 +2243,10 @@ __device__ __forceinline__ void sym_body(const KArgs& a, const SymArgs& sa, int 
 // Far tile pairs, two targets to a lane (an item's row rotations in pairs): a source read from LDS
 // serves two pairs, and their reverse terms travel home as one sum, so a pair
 // takes half the LDS reads and half the DPP moves and adds of sym_body's steps.
-// The pass is bound by its VALU instructions (and by the clock they leave).  Waves
+// The passes are bound by VALU issue: at n = 272718 the double and the float Laplace
+// ones run at the rate of their instructions at 2.0 to 2.2 GHz; the float Stokes ones at
+// 3.1 to 3.3 cycles an instruction where theirs allow 2.4 to 2.5 (waves wait to issue in half of
+// their cycles, for the LDS in less than 1%).  Waves
 // w and w ^ 2 hold the targets of units 2 (w & 1) and 2 (w & 1) + 1 and meet source
 // quarters w and w ^ 1, so the four waves own the four quarters in each of two
 // phases; the forward sums of the two waves meet in LDS at the end.
